@@ -12,6 +12,14 @@
  *   Phase 3  CRT reconstruction of the exact integer, Eq. (garner) / (M-bound),
  *            one rounded conversion back to FP64, and the native-FP64
  *            fallback for rows the scaling cannot certify.
+ * The staged API (plans), OZ2_FUSED and OZ2_KEEP_RESIDUES run Phase 2 exactly
+ * so.  The one-call products (ozaki2_dgemm, _ex, _static, _strided_batched)
+ * form the same exact integers A~ B~ from byte residues instead: moduli of at
+ * most 256 whose product covers the integers' range, one int8 MFMA product
+ * with exact int32 sums per modulus (gfx950 multiplies int8 at the E4M3 rate,
+ * and E4M3 needs three products for a nine-bit modulus).  Integers, scales,
+ * flags, rounding and therefore C are the same bit for bit; num_moduli still
+ * fixes them.
  *
  * Conventions shared by every entry point
  * ---------------------------------------
@@ -67,9 +75,9 @@ enum {
   OZ2_NO_FALLBACK = 8u,    /* never recompute flagged rows natively */
   OZ2_FORCE_FALLBACK = 16u,/* recompute every row natively (testing aid) */
   OZ2_KEEP_RESIDUES = 32u, /* materialise the r residues of every output in the workspace
-                              (the staged route, which every call takes unless OZ2_FUSED is
-                              given or ozaki2_dgemm_ex takes its tall-skinny route: the flag
-                              forbids OZ2_FUSED alongside it and keeps that route off) */
+                              (the staged plane route, which plans always take; in
+                              ozaki2_dgemm_ex the flag keeps the byte-residue route and the
+                              tall-skinny route off, and it forbids OZ2_FUSED alongside) */
   OZ2_TIME_STAGES = 64u,   /* plans only: record HIP events between the stages on the
                               stream of each call (OZ2_Q_STAGE_TIMES) */
   OZ2_FUSED = 128u         /* the residue GEMMs and the reconstruction as one kernel that
@@ -100,7 +108,7 @@ int ozaki2_dgemm(int m, int n, int k, const double* A, int lda, const double* B,
 
 /* C = A*B, or C = C + A*B with OZ2_ACCUMULATE, using the caller's workspace
  * (device memory of at least ozaki2_workspace_bytes(m, n, k, r, flags) bytes,
- * 256-byte aligned; contents on entry are ignored and on exit undefined).
+ * sized for the staged API's larger layout too, 256-byte aligned; contents on entry are ignored and on exit undefined).
  * With OZ2_SCALE_FIXED, n <= 16 and none of OZ2_ACCUMULATE, OZ2_FUSED,
  * OZ2_KEEP_RESIDUES, the product runs as the fused GEMV of ozaki2_gemv_batched
  * (A deconstructed on the fly, the fused mode for tall-skinny products of
@@ -129,7 +137,8 @@ int ozaki2_dgemm_static(int m, int n, int k, const double* A, int lda, const dou
 
 /* batch independent products C_b = A_b * B_b, A_b = A + b*strideA (elements),
  * likewise B_b, C_b; each with the layout rules above.  Strides must keep the
- * output matrices disjoint. Internal workspace as for ozaki2_dgemm. */
+ * output matrices disjoint.  Internal workspace as for ozaki2_dgemm; beyond
+ * 64 x 64 x 64 as many problems run side by side as 512 MiB of it hold. */
 int ozaki2_dgemm_strided_batched(int m, int n, int k, const double* A, int lda,
                                  long long strideA, const double* B, int ldb,
                                  long long strideB, double* C, int ldc,

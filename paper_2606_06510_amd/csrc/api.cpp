@@ -193,6 +193,86 @@ bool build_const(int r, Oz2Const& c) {
   return true;
 }
 
+// the byte moduli, pairwise coprime, largest first
+const int kByteModuli[OZ2_MAXB] = {256, 255, 253, 251, 247, 241, 239, 233, 229, 227,
+                                   223, 217, 211, 199, 197, 193, 191, 181, 179};
+
+// 2^-k * floor-ish value of a big integer as a double (for ratios only)
+double big_double(const Big& b) {
+  double v = 0.0;
+  for (size_t i = b.w.size(); i-- > 0;) v = v * 4294967296.0 + (double)b.w[i];
+  return v;
+}
+
+bool build_byte(const Big& M, Oz2Byte& b) {
+  std::memset(&b, 0, sizeof(b));
+  Big M8(1);
+  while (b.n < OZ2_MAXB && big_double(M8) < 0.625 * big_double(M))
+    M8.mul_small((uint32_t)kByteModuli[b.n++]);
+  if (big_double(M8) < 0.625 * big_double(M)) return false;
+  const int nl = b.n <= 15 ? 3 : 4;
+  if (M8.bitlen() > 38 * (nl - 1) + 42) return false;   // top limbs: see the reconstruction
+  auto limbs = [nl](const Big& x, int64_t (&o)[4]) {
+    for (int l = 0; l < 4; ++l) o[l] = l < nl - 1 ? (int64_t)x.bits(38 * l, 38)
+                                     : l == nl - 1 ? (int64_t)x.bits(38 * l, 52) : 0;
+  };
+  int64_t ml[4];
+  limbs(M8, ml);
+  for (int l = 0; l < 4; ++l) b.M38[l] = (double)ml[l];
+  b.mtop = std::ldexp(1.0, 38 * (nl - 1)) / big_double(M8);
+  auto above = [](uint64_t lo, uint64_t m) { return (uint32_t)((lo + m - 1) / m * m); };
+  for (int i = 0; i < b.n; ++i) {
+    const int m = kByteModuli[i];
+    b.nm[i] = (1u << 24) - (uint32_t)m;
+    b.mg0[i] = (uint32_t)(((1ull << 32) + m - 1) / m);
+    b.mg7[i] = (uint32_t)(((1ull << 39) + m - 1) / m);
+    b.off0[i] = above(1u << 22, m);
+    b.off7[i] = above(1u << 29, m);
+    b.tof[i] = (int)above(1u << 17, m) + 128;
+    int p = 1;   // 256^j mod m
+    for (int j = 0; j < 8; ++j) {
+      const int cp = p > m / 2 ? p - m : p;
+      if (cp < -128 || cp > 127) return false;
+      b.dot[i][j / 4] = (int)((uint32_t)b.dot[i][j / 4] | ((uint32_t)(cp & 0xFF) << (8 * (j & 3))));
+      p = p * 256 % m;
+    }
+    Big Mi(1);
+    for (int j = 0; j < b.n; ++j)
+      if (j != i) Mi.mul_small((uint32_t)kByteModuli[j]);
+    const int64_t inv = m == 1 ? 0 : inv_mod(Mi.mod_small((uint32_t)m), m);
+    Big Wi = Mi;
+    Wi.mul_small((uint32_t)inv);
+    int64_t wl[4];
+    limbs(Wi, wl);
+    if (2 * inv > m) {   // W_i > M8/2: take W_i - M8, limbs below the top in [0, 2^38)
+      for (int l = 0; l < nl; ++l) wl[l] -= ml[l];
+      for (int l = 0; l < nl - 1; ++l)
+        if (wl[l] < 0) {
+          wl[l] += (int64_t)1 << 38;
+          wl[l + 1] -= 1;
+        }
+    }
+    for (int l = 0; l < 4; ++l) b.W38[i][l] = (double)wl[l];
+  }
+  return true;
+}
+
+bool make_byte(int r, Oz2Byte& b) {
+  static std::mutex mu;
+  static Oz2Byte cache[OZ2_MAXR + 1];
+  static bool ready[OZ2_MAXR + 1] = {false};
+  if (r < 8 || r > OZ2_MAXR) return false;
+  std::lock_guard<std::mutex> g(mu);
+  if (!ready[r]) {
+    Big M(1);
+    for (int i = 0; i < r; ++i) M.mul_small((uint32_t)kPool[i]);
+    if (!build_byte(M, cache[r])) return false;
+    ready[r] = true;
+  }
+  b = cache[r];
+  return true;
+}
+
 // The constants depend only on r: built once per r (bigint products and
 // inverses), then copied.
 bool make_const(int r, Oz2Const& c) {
@@ -261,6 +341,41 @@ Oz2Layout make_layout(const Oz2Dims& d, const Oz2Const& c) {
   L.total = o;
   return L;
 }
+
+// The byte-residue route's carve-up of the same workspace: c.n byte planes in
+// the place of the E4M3 planes, one byte per output and modulus in the place
+// of 12 bits; never larger than make_layout's (n <= P, n <= 1.5 r).
+Oz2Layout make_byte_layout(const Oz2Dims& d, const Oz2Byte& c) {
+  Oz2Layout L{};
+  size_t o = 0;
+  auto take = [&o](size_t bytes) { size_t at = o; o = align256(o + bytes); return at; };
+  L.rowbits = take((size_t)d.mp * 8);
+  L.colbits = take((size_t)d.np * 8);
+  L.flagsA = take((size_t)d.mp * 4);
+  L.flagsB = take((size_t)d.np * 4);
+  L.Rmax = take((size_t)d.cslabs * d.mp * 4);
+  L.Kmax = take((size_t)d.cslabs * d.np * 4);
+  L.sA = take((size_t)d.mp * 4);
+  L.tB = take((size_t)d.np * 4);
+  L.eA = take((size_t)d.mp * 4);
+  L.eB = take((size_t)d.np * 4);
+  L.counters = take(64);
+  L.listA = take((size_t)d.mp * 4);
+  L.listB = take((size_t)d.np * 4);
+  L.codesA = take((size_t)d.mp * d.kp);
+  L.codesB = take((size_t)d.np * d.kp);
+  L.etA = take((size_t)d.mp * (d.kp / 64) * 2);
+  L.etB = take((size_t)d.np * (d.kp / 64) * 2);
+  L.planesA = take((size_t)c.n * d.mp * d.kp);
+  L.planesB = take((size_t)c.n * d.np * d.kp);
+  L.res = take((size_t)c.n * d.mp * d.np);
+  L.panel = (d.flags & OZ2_NO_FALLBACK) ? 0 : take((size_t)std::min(d.mp, OZ2_FBCAP) * d.k * 8);
+  L.total = o;
+  return L;
+}
+
+// workspace of the problems that ozaki2_dgemm_strided_batched runs side by side
+constexpr size_t kBatchBytes = (size_t)512 << 20;
 
 // ------------------------------------------------------------ batched GEMV
 // Y = A X with X of nrhs <= 16 columns (the fused kernel of gemv.hip): k in
@@ -443,6 +558,8 @@ hipError_t mark(ozaki2_plan_s& p, int i, hipStream_t s) {
 // Phase 1 for the operands in `side` (OZ2_SIDE_A, OZ2_SIDE_B or both).  One
 // operand alone only under OZ2_SCALE_FIXED, where its scales do not depend on
 // the other operand (no max-magnitude pass).
+const Oz2Batch kOne{1, 0, 0, 0, 0};
+
 int run_deconstruct(ozaki2_plan_s& p, int side, hipStream_t s) {
   const Oz2Dims& d = p.d;
   // Each operand is read once for its scan and code bytes (one kernel), and
@@ -451,23 +568,46 @@ int run_deconstruct(ozaki2_plan_s& p, int side, hipStream_t s) {
   const bool codes = !(d.flags & OZ2_SCALE_FIXED);
   p.recorded = 0;
   hipError_t e = mark(p, 0, s);
-  if (e == hipSuccess) e = oz2_launch_init(d, p.L, p.ws, side, s);
+  if (e == hipSuccess) e = oz2_launch_init(d, p.L, p.ws, side, kOne, s);
   for (int one : {OZ2_SIDE_A, OZ2_SIDE_B}) {
     if (!(side & one) || e != hipSuccess) continue;
-    e = codes ? oz2_launch_scan_codes(d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, one, s)
-              : oz2_launch_scan(d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, one, s);
+    e = codes ? oz2_launch_scan_codes(d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, one, kOne, s)
+              : oz2_launch_scan(d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, one, kOne, s);
   }
-  if (codes && e == hipSuccess) e = oz2_launch_rebase(d, p.L, p.ws, side, s);
+  if (codes && e == hipSuccess) e = oz2_launch_rebase(d, p.L, p.ws, side, kOne, s);
   if (e == hipSuccess) e = mark(p, 1, s);
-  if (codes && e == hipSuccess) e = oz2_launch_codegemm(d, p.L, p.ws, s);
+  if (codes && e == hipSuccess) e = oz2_launch_codegemm(d, p.L, p.ws, kOne, s);
   if (e == hipSuccess) e = mark(p, 2, s);
-  if (e == hipSuccess) e = oz2_launch_scales(d, p.L, p.c, p.ws, side, s);
+  if (e == hipSuccess) e = oz2_launch_scales(d, p.L, p.c, p.ws, side, kOne, s);
   if (e == hipSuccess && !p.tables) {
     e = oz2_launch_tables(p.L, p.c, p.ws, s);
     p.tables = e == hipSuccess;
   }
   if (e == hipSuccess) e = oz2_launch_split(d, p.L, p.c, p.ws, p.A, p.lda, p.B, p.ldb, side, s);
   if (e == hipSuccess) e = mark(p, 3, s);
+  return hip_status(e);
+}
+
+// C = A B (or C + A B) on byte residues, for the bt.count problems of a batch
+// (one: kOne): phase 1 with the byte split in the place of the plane split,
+// the byte products, the reconstruction and the fallback.
+int run_bytes(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c, const Oz2Byte& b,
+              uint8_t* ws, const double* A, int lda, const double* B, int ldb, double* C, int ldc,
+              const Oz2Batch& bt, hipStream_t s) {
+  const bool codes = !(d.flags & OZ2_SCALE_FIXED);
+  const int both = OZ2_SIDE_A | OZ2_SIDE_B;
+  hipError_t e = oz2_launch_init(d, L, ws, both, bt, s);
+  if (e == hipSuccess)
+    e = codes ? oz2_launch_scan_codes(d, L, ws, A, lda, B, ldb, both, bt, s)
+              : oz2_launch_scan(d, L, ws, A, lda, B, ldb, both, bt, s);
+  if (codes && e == hipSuccess) e = oz2_launch_rebase(d, L, ws, both, bt, s);
+  if (codes && e == hipSuccess) e = oz2_launch_codegemm(d, L, ws, bt, s);
+  if (e == hipSuccess) e = oz2_launch_scales(d, L, c, ws, both, bt, s);
+  if (e == hipSuccess) e = oz2_launch_byte_split(d, L, b, ws, A, lda, B, ldb, bt, s);
+  if (e == hipSuccess) e = oz2_launch_bytegemm(d, L, b, ws, bt, s);
+  if (e == hipSuccess) e = oz2_launch_byte_crt(d, L, b, ws, A, lda, C, ldc, bt, s);
+  if (e == hipSuccess && !(d.flags & OZ2_NO_FALLBACK))
+    e = oz2_launch_fallback(d, L, ws, A, lda, B, ldb, C, ldc, bt, s);
   return hip_status(e);
 }
 
@@ -480,7 +620,7 @@ int run_reconstruct(ozaki2_plan_s& p, double* C, int ldc, hipStream_t s) {
   if (e == hipSuccess) e = mark(p, 7, s);
   if (e == hipSuccess && !(p.d.flags & OZ2_NO_FALLBACK))
     e = fused ? oz2_launch_fallback_direct(p.d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, C, ldc, s)
-              : oz2_launch_fallback(p.d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, C, ldc, s);
+              : oz2_launch_fallback(p.d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, C, ldc, kOne, s);
   if (e == hipSuccess) e = mark(p, 8, s);
   return hip_status(e);
 }
@@ -719,6 +859,12 @@ int ozaki2_dgemm_ex(int m, int n, int k, const double* A, int lda, const double*
     return (flags & OZ2_KEEP_RESIDUES) ? OZ2_E_INVALID : OZ2_E_UNSUPPORTED;
   p.L = make_layout(p.d, p.c);
   if (!workspace || ws_bytes < p.L.total || ((uintptr_t)workspace & 255)) return OZ2_E_WORKSPACE;
+  if (!(flags & (OZ2_FUSED | OZ2_KEEP_RESIDUES))) {
+    Oz2Byte b;
+    if (!make_byte(num_moduli, b)) return OZ2_E_INVALID;
+    return run_bytes(p.d, make_byte_layout(p.d, b), p.c, b, (uint8_t*)workspace, A, lda, B, ldb, C, ldc,
+                     kOne, s);
+  }
   p.ws = (uint8_t*)workspace;
   p.A = A;
   p.B = B;
@@ -797,17 +943,46 @@ int ozaki2_dgemm_strided_batched(int m, int n, int k, const double* A, int lda, 
                              (const uint32_t*)ws, nullptr, s);
     return e == hipSuccess ? OZ2_OK : OZ2_E_DEVICE;
   }
-  size_t need = ozaki2_workspace_bytes(m, n, k, num_moduli, 0);
-  if (need == 0) return OZ2_E_INVALID;
+  for (int b = 1; b < batch; ++b) {   // each problem's C apart from its own A and B
+    st = check_mats(m, n, k, A + (size_t)b * strideA, lda, B + (size_t)b * strideB, ldb,
+                    C + (size_t)b * strideC, ldc);
+    if (st != OZ2_OK) return st;
+  }
   st = device_ok();
   if (st != OZ2_OK) return st;
+  hipStream_t s = (hipStream_t)stream;
+  if (k == 0) {
+    for (int b = 0; b < batch; ++b) {
+      st = hip_status(oz2_launch_fill(C + (size_t)b * strideC, m, n, ldc, s));
+      if (st != OZ2_OK) return st;
+    }
+    return OZ2_OK;
+  }
+  Oz2Const c;
+  Oz2Byte by;
+  Oz2Dims d;
+  if (!make_const(num_moduli, c) || !make_byte(num_moduli, by) || !make_dims(m, n, k, 0, d))
+    return OZ2_E_INVALID;
+  const Oz2Layout L = make_byte_layout(d, by);
+  // As many problems side by side (the z dimension of every launch, a
+  // workspace each) as kBatchBytes of workspace hold: 24 products of
+  // 200 x 136 x 300 one after the other took 1.27 ms, launches of single tiles.
+  // Operands that reach into another problem's C keep the problems in order.
+  const size_t ca = (size_t)(batch - 1) * strideC * sizeof(double) + span_bytes(m, n, ldc);
+  const bool apart =
+      !overlaps(C, ca, A, (size_t)(batch - 1) * strideA * sizeof(double) + span_bytes(m, k, lda)) &&
+      !overlaps(C, ca, B, (size_t)(batch - 1) * strideB * sizeof(double) + span_bytes(k, n, ldb));
+  const int side = apart ? (int)std::min<size_t>({(size_t)batch, (size_t)65535,
+                                                  std::max<size_t>(1, kBatchBytes / L.total)})
+                         : 1;
   std::lock_guard<std::mutex> g(g_pool_mu);
   void* ws = nullptr;
-  st = pool_get(need, &ws);
+  st = pool_get((size_t)side * L.total, &ws);
   if (st != OZ2_OK) return st;
-  for (int b = 0; b < batch; ++b) {
-    st = ozaki2_dgemm_ex(m, n, k, A + (size_t)b * strideA, lda, B + (size_t)b * strideB, ldb,
-                         C + (size_t)b * strideC, ldc, num_moduli, 0, ws, need, stream);
+  for (int b = 0; b < batch; b += side) {
+    const Oz2Batch bt{std::min(side, batch - b), strideA, strideB, strideC, L.total};
+    st = run_bytes(d, L, c, by, (uint8_t*)ws, A + (size_t)b * strideA, lda, B + (size_t)b * strideB,
+                   ldb, C + (size_t)b * strideC, ldc, bt, s);
     if (st != OZ2_OK) return st;
   }
   return OZ2_OK;
@@ -851,9 +1026,9 @@ int ozaki2_gemv_batched(int m, int k, int nrhs, const double* A, int lda, const 
   // plane tables are the previous call's
   const bool reuse = (flags & OZ2_REUSE_A_SCALES) != 0;
   const int sides = reuse ? OZ2_SIDE_B : (OZ2_SIDE_A | OZ2_SIDE_B);
-  hipError_t e = oz2_launch_init(d, L, ws, sides, s);
-  if (e == hipSuccess) e = oz2_launch_scan(d, L, ws, A, lda, X, ldx, sides, s);
-  if (e == hipSuccess) e = oz2_launch_scales(d, L, c, ws, sides, s);
+  hipError_t e = oz2_launch_init(d, L, ws, sides, kOne, s);
+  if (e == hipSuccess) e = oz2_launch_scan(d, L, ws, A, lda, X, ldx, sides, kOne, s);
+  if (e == hipSuccess) e = oz2_launch_scales(d, L, c, ws, sides, kOne, s);
   if (e == hipSuccess && !reuse) e = oz2_launch_tables(L, c, ws, s);
   if (e == hipSuccess)
     e = oz2_launch_gemv_xplanes(c, X, ldx, k, nrhs, (const int32_t*)(ws + L.tB),

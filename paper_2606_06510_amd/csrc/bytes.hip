@@ -1,0 +1,280 @@
+// Phases 1 (last step) and 3 of Alg. 1 on byte residues: the quantise ->
+// residue split of A and B, and the CRT reconstruction of C, of the one-call
+// products (bytegemm.hip is the GEMM between them; Oz2Byte the residue
+// system).  The quantised integers A~, B~ (Eq. (scale)), the flags and the
+// integer C~ are those of the plane route, so C is the same bit for bit.
+#include "oz2_device.h"
+
+namespace {
+
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+// ---------------------------------------------------------------- split
+// One workgroup of 256 threads per 64 x 64 tile: thread t quantises row t/4,
+// k 16 (t%4) .. +15, and writes its 16 bytes of every modulus's plane (1 KiB
+// contiguous per wave store).
+//
+// The residue of the quantised integer a (|a| <= 2^62): its eight balanced
+// base-256 digits (bytes of a + 0x0080..80, each minus 128) against the
+// centred residues of 256^j, two dot4 instructions on top of tof = 128 + K m
+// (K m >= 2^17 > |sum|): t' >= 0 and below 2^19, so floor(t'/m) is one exact
+// high multiply with ceil(2^32/m), and t' - m floor(t'/m) - 128 lies in
+// [-128, m - 129]: an int8 congruent to a.  Six instructions per element and
+// modulus, packing included, and no table: the split stays bound by its
+// stores.
+struct ByteSide {
+  const double* X;
+  int ld, rows, rows_pad, ntiles;
+  const int32_t* scale;
+  uint32_t* flags;
+  uint8_t* planes;
+  unsigned vec;
+  int* count;
+  int* list;
+  int listed;
+  long long stride;    // elements between the problems of a batch
+};
+
+__device__ __forceinline__ uint32_t low4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  const uint32_t lo = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);
+  const uint32_t hi = __builtin_amdgcn_perm(d, c, 0x04000c0cu);
+  return lo | hi;
+}
+
+template <bool TRANS>
+__device__ __forceinline__ void byte_tile(const Oz2Byte& c, const ByteSide& S, int tl, int k, int kp,
+                                          unsigned quant_tz, size_t z) {
+  const int nrb = S.rows_pad / 64;
+  const int t = threadIdx.x;
+  const int row = (tl % nrb) * 64 + (t >> 2), l0 = (tl / nrb) * 64 + (t & 3) * 16;
+  const bool inrow = row < S.rows;
+  uint32_t* flags = zws(S.flags, z);
+  const uint32_t f = inrow ? flags[row] : 0u;
+  const int sc = inrow ? zws(S.scale, z)[row] : 0;
+  const bool zero = !inrow || (f & OZ2_T1);
+  const double* X = S.X + (size_t)blockIdx.z * S.stride;
+  double x[16];
+  if (!TRANS && S.vec && !zero && l0 + 16 <= k) {
+    const double2* p = reinterpret_cast<const double2*>(X + (size_t)row * S.ld + l0);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const double2 v = p[j];
+      x[2 * j] = v.x;
+      x[2 * j + 1] = v.y;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int l = l0 + j;
+      const size_t off = TRANS ? ((size_t)row + (size_t)l * S.ld) : ((size_t)l + (size_t)row * S.ld);
+      x[j] = (!zero && l < k) ? X[off] : 0.0;
+    }
+  }
+  uint32_t lo[16], hi[16];
+  bool t2 = false;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const double y = ldexp(x[j], sc);
+    const double a = quant_tz ? trunc(y) : rint(y);
+    t2 |= (x[j] != 0.0) && (a == 0.0);
+    const double h = floor(a * 0x1p-32);
+    const uint64_t v = (((uint64_t)(uint32_t)(int)h << 32) | (uint32_t)fma(-h, 0x1p32, a)) +
+                       0x0080808080808080ull;
+    lo[j] = (uint32_t)v ^ 0x80808080u;
+    hi[j] = (uint32_t)(v >> 32) ^ 0x00808080u;
+  }
+  // the first tile to flag a row adds it to the fallback list (unless every
+  // row is listed already)
+  if (t2 && !(atomicOr(flags + row, OZ2_T2) & (OZ2_T1 | OZ2_T2)) && !S.listed)
+    zws(S.list, z)[atomicAdd(zws(S.count, z), 1)] = row;
+  uint8_t* dst = zws(S.planes, z) + ((size_t)(l0 >> 6) * S.rows_pad + row) * OZ2_KBLK + (l0 & 63);
+  const size_t pstride = (size_t)S.rows_pad * kp;
+  for (int i = 0; i < c.n; ++i) {
+    const int w0 = c.dot[i][0], w1 = c.dot[i][1], tof = c.tof[i];
+    const uint32_t mg = c.mg0[i], nm = c.nm[i];
+    uint32_t u[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      int s = __builtin_amdgcn_sdot4((int)lo[j], w0, tof, false);
+      s = __builtin_amdgcn_sdot4((int)hi[j], w1, s, false);
+      u[j] = __umul24(__umulhi((uint32_t)s, mg), nm) + (uint32_t)s;
+    }
+    u32x4 v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      v[q] = low4(u[4 * q], u[4 * q + 1], u[4 * q + 2], u[4 * q + 3]) ^ 0x80808080u;
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
+    dst += pstride;
+  }
+}
+
+// B's tiles first (B was read last by the scans and may still be in the
+// memory-side cache), then A's
+__global__ void __launch_bounds__(256)
+k_byte_split(Oz2Byte c, ByteSide SA, ByteSide SB, int k, int kp, unsigned quant_tz, size_t wsz) {
+  const int t = blockIdx.x;
+  const size_t z = (size_t)blockIdx.z * wsz;
+  if (t < SB.ntiles) byte_tile<false>(c, SB, t, k, kp, quant_tz, z);
+  else byte_tile<true>(c, SA, t - SB.ntiles, k, kp, quant_tz, z);
+}
+
+// ---------------------------------------------------------------- reconstruction
+// X = sum_i u_i W_i - q M over the N moduli, with W_i the representative of
+// smallest magnitude, in radix-2^38 fp64 limbs (NB of them; the top limb
+// signed).  Exact: u_i <= 255 and at most 16 moduli with |W_i| top limbs
+// below 2^41 (NB = 3) or 19 with lower limbs below 2^38: every sum is an
+// integer below 2^53.  |X| <= 0.41 M (the host's choice of moduli), so the
+// quotient estimate (error below 2^-24) is never ambiguous.
+//
+// A workgroup of 256 threads takes 128 rows x 16 columns: thread t the 8
+// outputs of column t%64/4%16.. held by half a lane's 16 bytes of a unit
+// (see bytegemm.hip); moduli outermost, so that each is loaded and used once
+// and its weights stay in scalar registers.  The results go through LDS, so
+// that a store instruction writes 512 contiguous bytes of a column.
+template <int N, bool ACC>
+__global__ void __launch_bounds__(256)
+k_byte_crt(Oz2Byte c, Oz2Dims d, const uint8_t* __restrict__ res, const int32_t* __restrict__ sA,
+           const int32_t* __restrict__ tB, const uint32_t* __restrict__ fA,
+           const uint32_t* __restrict__ fB, double* C, int ldc, const double* __restrict__ A,
+           int lda, const int* __restrict__ counters, const int* __restrict__ listA,
+           double* __restrict__ panel, int cap, int nrow, Oz2Batch bt) {
+  constexpr int NB = N <= 15 ? 3 : 4;
+  __shared__ double tr[16][129];
+  const size_t z = (size_t)blockIdx.z * bt.ws;
+  counters = zws(counters, z);
+  sA = zws(sA, z);
+  tB = zws(tB, z);
+  fA = zws(fA, z);
+  fB = zws(fB, z);
+  C += (size_t)blockIdx.z * bt.sC;
+  const int nflag = panel ? counters[0] : 0;   // used at the end; loaded early
+  const int t = threadIdx.x;
+  const int rb = (int)(blockIdx.x % (unsigned)nrow), cb = (int)(blockIdx.x / (unsigned)nrow);
+  // store phase: row t%128, columns t/128 + 2 j
+  const int srow = rb * 128 + (t & 127);
+  double cin[8];
+  if constexpr (ACC) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int col = cb * 16 + (t >> 7) + 2 * j;
+      cin[j] = (srow < d.m && col < d.n) ? __builtin_nontemporal_load(C + (size_t)col * ldc + srow) : 0.0;
+    }
+  }
+  {
+    // unit u = t / 128 (rows 64 u ..), lane L = (t % 128) / 2, half h = t % 2
+    const int u = t >> 7, L = (t & 127) >> 1, h = t & 1;
+    const uint8_t* q = res + z + ((size_t)cb * (d.mp / 64) + rb * 2 + u) * 1024 + 16 * L + 8 * h;
+    const size_t plane = (size_t)d.mp * d.np;
+    double S[8][NB];
+#pragma unroll
+    for (int I = 0; I < 8; ++I)
+#pragma unroll
+      for (int l = 0; l < NB; ++l) S[I][l] = 0.0;
+    u32x2 x[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      x[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(q + (size_t)i * plane));
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+#pragma unroll
+      for (int I = 0; I < 8; ++I) {
+        const double v = (double)(float)((x[i][I >> 2] >> (8 * (I & 3))) & 0xFFu);
+#pragma unroll
+        for (int l = 0; l < NB; ++l) S[I][l] = fma(v, c.W38[i][l], S[I][l]);
+      }
+    }
+    const int col = cb * 16 + (L & 15);
+    const int tj = col < d.n ? tB[col] : 0;
+#pragma unroll
+    for (int I = 0; I < 8; ++I) {
+      const int rr = 64 * u + 16 * (2 * h + (I >> 2)) + 4 * (L >> 4) + (I & 3);
+      const int row = rb * 128 + rr;
+      const int si = row < d.m ? sA[row] : 0;
+      const double f = fma(S[I][NB - 2], 0x1p-38, S[I][NB - 1]) * c.mtop;
+      const double qq = rint(f);
+#pragma unroll
+      for (int l = 0; l < NB; ++l) S[I][l] = fma(-qq, c.M38[l], S[I][l]);
+      normalise38<NB>(S[I]);
+      tr[L & 15][rr] = round38<NB>(S[I], si + tj);
+    }
+  }
+  __syncthreads();
+  const bool nofb = (d.flags & 8u) != 0;       // OZ2_NO_FALLBACK
+  const bool force = (d.flags & 16u) != 0;     // OZ2_FORCE_FALLBACK
+  if (srow < d.m && !(!nofb && (force || (fA[srow] & (OZ2_T1 | OZ2_T2))))) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int cc = (t >> 7) + 2 * j, col = cb * 16 + cc;
+      if (col < d.n && (nofb || !(fB[col] & (OZ2_T1 | OZ2_T2)))) {
+        const double v = tr[cc][t & 127];
+        __builtin_nontemporal_store(ACC ? cin[j] + v : v, C + (size_t)col * ldc + srow);
+      }
+    }
+  }
+  // the fallback's panel: the first `cap` flagged rows of A, gathered once
+  // (grid-stride over (row of the list, k); nothing to do without flags)
+  if (nflag > 0) {
+    panel = zws(panel, z);
+    listA = zws(listA, z);
+    A += (size_t)blockIdx.z * bt.sA;
+    const int na = min(nflag, cap);
+    const size_t total = (size_t)na * d.k, step = (size_t)gridDim.x * blockDim.x;
+    for (size_t idx = (size_t)blockIdx.x * blockDim.x + t; idx < total; idx += step) {
+      const size_t l = idx / na;
+      const int r = (int)(idx - l * na);
+      panel[r + l * cap] = A[(size_t)listA[r] + l * lda];
+    }
+  }
+}
+
+template <int N>
+void launch_crt_n(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
+                  const double* A, int lda, double* C, int ldc, const Oz2Batch& bt, hipStream_t s) {
+  const int nrow = (d.m + 127) / 128, ncol = (d.n + 15) / 16;
+  const bool gather = !(d.flags & 8u);   // OZ2_NO_FALLBACK: no fallback, no panel
+  auto kern = (d.flags & 1u) ? k_byte_crt<N, true> : k_byte_crt<N, false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((size_t)nrow * ncol), 1, bt.count), dim3(256), 0, s, c, d,
+                     ws + L.res, (const int32_t*)(ws + L.sA), (const int32_t*)(ws + L.tB),
+                     (const uint32_t*)(ws + L.flagsA), (const uint32_t*)(ws + L.flagsB), C, ldc, A,
+                     lda, (const int*)(ws + L.counters), (const int*)(ws + L.listA),
+                     gather ? (double*)(ws + L.panel) : nullptr, d.mp < OZ2_FBCAP ? d.mp : OZ2_FBCAP,
+                     nrow, bt);
+}
+
+}  // namespace
+
+hipError_t oz2_launch_byte_split(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
+                                 const double* A, int lda, const double* B, int ldb,
+                                 const Oz2Batch& bt, hipStream_t s) {
+  const unsigned tz = (d.flags & 4u) ? 1u : 0u;   // OZ2_QUANT_TZ
+  const int listed = (d.flags & 16u) ? 1 : 0;     // OZ2_FORCE_FALLBACK
+  const bool vec = (uintptr_t)B % 16 == 0 && ldb % 2 == 0 && bt.sB % 2 == 0;
+  ByteSide SA{A, lda, d.m, d.mp, (d.mp / 64) * (d.kp / 64), (const int32_t*)(ws + L.sA),
+              (uint32_t*)(ws + L.flagsA), ws + L.planesA, 0u, (int*)(ws + L.counters),
+              (int*)(ws + L.listA), listed, bt.sA};
+  ByteSide SB{B, ldb, d.n, d.np, (d.np / 64) * (d.kp / 64), (const int32_t*)(ws + L.tB),
+              (uint32_t*)(ws + L.flagsB), ws + L.planesB, vec ? 1u : 0u,
+              (int*)(ws + L.counters) + 1, (int*)(ws + L.listB), listed, bt.sB};
+  hipLaunchKernelGGL(k_byte_split, dim3(SA.ntiles + SB.ntiles, 1, bt.count), dim3(256), 0, s, c, SA,
+                     SB, d.k, d.kp, tz, bt.ws);
+  return hipGetLastError();
+}
+
+hipError_t oz2_launch_byte_crt(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
+                               const double* A, int lda, double* C, int ldc, const Oz2Batch& bt,
+                               hipStream_t s) {
+  switch (c.n) {
+    case 10: launch_crt_n<10>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
+    case 11: launch_crt_n<11>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
+    case 12: launch_crt_n<12>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
+    case 13: launch_crt_n<13>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
+    case 15: launch_crt_n<15>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
+    case 16: launch_crt_n<16>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
+    case 17: launch_crt_n<17>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
+    case 18: launch_crt_n<18>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
+    case 19: launch_crt_n<19>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}

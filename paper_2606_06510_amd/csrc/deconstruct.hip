@@ -19,7 +19,13 @@ namespace {
 // accumulate with atomics, and the operand's fallback-list count (the list
 // is filled by k_scales (T1) and k_split (T2) of this deconstruction)
 __global__ void k_init(unsigned long long* rowbits, int mp, unsigned long long* colbits, int np,
-                       uint32_t* Rmax, uint32_t* Kmax, int cslabs, int* counters, int side) {
+                       uint32_t* Rmax, uint32_t* Kmax, int cslabs, int* counters, int side, size_t wsz) {
+  const size_t z = (size_t)blockIdx.z * wsz;
+  rowbits = zws(rowbits, z);
+  colbits = zws(colbits, z);
+  Rmax = zws(Rmax, z);
+  Kmax = zws(Kmax, z);
+  counters = zws(counters, z);
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   size_t nR = (size_t)cslabs * mp, nK = (size_t)cslabs * np;
   if (side & OZ2_SIDE_A) {
@@ -39,7 +45,9 @@ __global__ void k_init(unsigned long long* rowbits, int mp, unsigned long long* 
 // eight loads in flight; one k-chunk per grid row, combined with atomicMax.
 __global__ void __launch_bounds__(256) k_scan_rows(const double* __restrict__ A, int lda, int m, int k,
                                                    int kchunk, unsigned vec,
-                                                   unsigned long long* rowbits) {
+                                                   unsigned long long* rowbits, Oz2Batch bt) {
+  A += (size_t)blockIdx.z * bt.sA;
+  rowbits = zws(rowbits, (size_t)blockIdx.z * bt.ws);
   const int i = 2 * (blockIdx.x * blockDim.x + threadIdx.x);
   if (i >= m) return;
   const int l0 = blockIdx.y * kchunk;
@@ -73,7 +81,10 @@ __global__ void __launch_bounds__(256) k_scan_rows(const double* __restrict__ A,
 // contiguous columns: one wave per column, 16-byte loads (1 KiB per wave
 // instruction), four in flight per lane
 __global__ void __launch_bounds__(256) k_scan_cols(const double* __restrict__ B, int ldb, int n, int k,
-                                                   unsigned vec, unsigned long long* colbits) {
+                                                   unsigned vec, unsigned long long* colbits,
+                                                   Oz2Batch bt) {
+  B += (size_t)blockIdx.z * bt.sB;
+  colbits = zws(colbits, (size_t)blockIdx.z * bt.ws);
   int j = (int)((blockIdx.x * (size_t)blockDim.x + threadIdx.x) >> 6);
   int lane = threadIdx.x & 63;
   if (j >= n) return;
@@ -227,7 +238,12 @@ __device__ __forceinline__ uint32_t local_code(unsigned long long b, int Et) {
 __global__ void __launch_bounds__(256) k_scan_codes_rows(const double* __restrict__ X, int ld,
                                                          int rows, int nrb, int k, unsigned vec,
                                                          unsigned long long* bits, int16_t* et,
-                                                         uint8_t* __restrict__ codes) {
+                                                         uint8_t* __restrict__ codes,
+                                                         Oz2Batch bt) {
+  X += (size_t)blockIdx.z * bt.sA;
+  bits = zws(bits, (size_t)blockIdx.z * bt.ws);
+  et = zws(et, (size_t)blockIdx.z * bt.ws);
+  codes = zws(codes, (size_t)blockIdx.z * bt.ws);
   __shared__ __attribute__((aligned(16))) uint8_t T[64][80];
   __shared__ unsigned long long mx[8][64];
   const int rows_pad = nrb * 64;
@@ -296,7 +312,12 @@ __global__ void __launch_bounds__(256) k_scan_codes_rows(const double* __restric
 __global__ void __launch_bounds__(256) k_scan_codes_cols(const double* __restrict__ X, int ld,
                                                          int rows, int nrb, int k, unsigned vec,
                                                          unsigned long long* bits, int16_t* et,
-                                                         uint8_t* __restrict__ codes) {
+                                                         uint8_t* __restrict__ codes,
+                                                         Oz2Batch bt) {
+  X += (size_t)blockIdx.z * bt.sB;
+  bits = zws(bits, (size_t)blockIdx.z * bt.ws);
+  et = zws(et, (size_t)blockIdx.z * bt.ws);
+  codes = zws(codes, (size_t)blockIdx.z * bt.ws);
   __shared__ __attribute__((aligned(16))) uint8_t T[64][80];
   const int rows_pad = nrb * 64;
   const int t = threadIdx.x;
@@ -367,13 +388,14 @@ __global__ void __launch_bounds__(256) k_rebase(uint8_t* codesA, const int16_t* 
                                                 int mp, size_t nA, uint8_t* codesB,
                                                 const int16_t* __restrict__ etB,
                                                 const unsigned long long* __restrict__ bitsB,
-                                                int np, size_t nB) {
+                                                int np, size_t nB, size_t wsz) {
   __shared__ uint8_t lut[5 * 256];
   for (int e = threadIdx.x; e < 5 * 256; e += blockDim.x)
     lut[e] = (uint8_t)(__builtin_amdgcn_cvt_pk_fp8_f32(rebase_code((uint32_t)(e & 255), e >> 8),
                                                        0.0f, 0, false) & 0xFF);
   __syncthreads();
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const size_t z = (size_t)blockIdx.z * wsz;
   uint8_t* codes = codesA;
   const int16_t* et = etA;
   const unsigned long long* bits = bitsA;
@@ -386,6 +408,9 @@ __global__ void __launch_bounds__(256) k_rebase(uint8_t* codesA, const int16_t* 
     bits = bitsB;
     rp = np;
   }
+  codes = zws(codes, z);
+  et = zws(et, z);
+  bits = zws(bits, z);
   // segment i = (k-block, row): et is [k/64][rows], the codes [k/64][rows][64];
   // every load first (one round of latency), then the lookups
   const int row = (int)(i % (size_t)rp);
@@ -415,7 +440,21 @@ __global__ void k_scales(Oz2Dims d, const unsigned long long* __restrict__ rowbi
                          const uint32_t* __restrict__ Rmax, const uint32_t* __restrict__ Kmax,
                          int32_t* sA, int32_t* tB, int32_t* eA, int32_t* eB, uint32_t* fA,
                          uint32_t* fB, int cA, int cB, int* counters, int* listA, int* listB,
-                         int side) {
+                         int side, size_t wsz) {
+  const size_t z = (size_t)blockIdx.z * wsz;
+  rowbits = zws(rowbits, z);
+  colbits = zws(colbits, z);
+  Rmax = zws(Rmax, z);
+  Kmax = zws(Kmax, z);
+  sA = zws(sA, z);
+  tB = zws(tB, z);
+  eA = zws(eA, z);
+  eB = zws(eB, z);
+  fA = zws(fA, z);
+  fB = zws(fB, z);
+  counters = zws(counters, z);
+  listA = zws(listA, z);
+  listB = zws(listB, z);
   int idx = blockIdx.x * blockDim.x + threadIdx.x;
   bool fixed = (d.flags & 2u) != 0;   // OZ2_SCALE_FIXED
   const bool force = (d.flags & 16u) != 0;   // OZ2_FORCE_FALLBACK: every row of A natively
@@ -594,82 +633,82 @@ __global__ void __launch_bounds__(256) k_split(Oz2Const c, SplitSide SA, SplitSi
 }  // namespace
 
 hipError_t oz2_launch_init(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, int side,
-                           hipStream_t s) {
+                           const Oz2Batch& bt, hipStream_t s) {
   size_t n = (size_t)d.cslabs * (size_t)(d.mp > d.np ? d.mp : d.np);
   if ((size_t)d.mp > n) n = d.mp;
   if ((size_t)d.np > n) n = d.np;
   unsigned blocks = (unsigned)((n + 255) / 256);
-  hipLaunchKernelGGL(k_init, dim3(blocks), dim3(256), 0, s,
+  hipLaunchKernelGGL(k_init, dim3(blocks, 1, bt.count), dim3(256), 0, s,
                      (unsigned long long*)(ws + L.rowbits), d.mp,
                      (unsigned long long*)(ws + L.colbits), d.np, (uint32_t*)(ws + L.Rmax),
-                     (uint32_t*)(ws + L.Kmax), d.cslabs, (int*)(ws + L.counters), side);
+                     (uint32_t*)(ws + L.Kmax), d.cslabs, (int*)(ws + L.counters), side, bt.ws);
   return hipGetLastError();
 }
 
 hipError_t oz2_launch_scan(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, const double* A,
-                           int lda, const double* B, int ldb, int side, hipStream_t s) {
+                           int lda, const double* B, int ldb, int side, const Oz2Batch& bt, hipStream_t s) {
   if (side & OZ2_SIDE_A) {
     // rows: 512 per workgroup; k chunks sized for >= ~2048 workgroups when k allows
     const int gx = (d.m + 511) / 512;
     int kchunk = 32;
     while ((long long)gx * ((d.k + kchunk - 1) / kchunk) > 4096 && kchunk < 4096) kchunk *= 2;
     while ((d.k + kchunk - 1) / kchunk > 65535) kchunk *= 2;
-    const unsigned vecA = ((uintptr_t)A % 16 == 0 && lda % 2 == 0) ? 1u : 0u;
-    dim3 ga(gx, (d.k + kchunk - 1) / kchunk);
+    const unsigned vecA = ((uintptr_t)A % 16 == 0 && lda % 2 == 0 && bt.sA % 2 == 0) ? 1u : 0u;
+    dim3 ga(gx, (d.k + kchunk - 1) / kchunk, bt.count);
     hipLaunchKernelGGL(k_scan_rows, ga, dim3(256), 0, s, A, lda, d.m, d.k, kchunk, vecA,
-                       (unsigned long long*)(ws + L.rowbits));
+                       (unsigned long long*)(ws + L.rowbits), bt);
   }
   if (side & OZ2_SIDE_B) {
-    dim3 gb((d.n + 3) / 4);
-    const unsigned vecB = ((uintptr_t)B % 16 == 0 && ldb % 2 == 0) ? 1u : 0u;
+    dim3 gb((d.n + 3) / 4, 1, bt.count);
+    const unsigned vecB = ((uintptr_t)B % 16 == 0 && ldb % 2 == 0 && bt.sB % 2 == 0) ? 1u : 0u;
     hipLaunchKernelGGL(k_scan_cols, gb, dim3(256), 0, s, B, ldb, d.n, d.k, vecB,
-                       (unsigned long long*)(ws + L.colbits));
+                       (unsigned long long*)(ws + L.colbits), bt);
   }
   return hipGetLastError();
 }
 
 hipError_t oz2_launch_scan_codes(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
                                  const double* A, int lda, const double* B, int ldb, int side,
-                                 hipStream_t s) {
+                                 const Oz2Batch& bt, hipStream_t s) {
   if (side & OZ2_SIDE_A) {
-    dim3 ga((d.mp / 64) * (d.kp / 64));
-    const unsigned vecA = ((uintptr_t)A % 16 == 0 && lda % 2 == 0) ? 1u : 0u;
+    dim3 ga((d.mp / 64) * (d.kp / 64), 1, bt.count);
+    const unsigned vecA = ((uintptr_t)A % 16 == 0 && lda % 2 == 0 && bt.sA % 2 == 0) ? 1u : 0u;
     hipLaunchKernelGGL(k_scan_codes_rows, ga, dim3(256), 0, s, A, lda, d.m, d.mp / 64, d.k, vecA,
                        (unsigned long long*)(ws + L.rowbits), (int16_t*)(ws + L.etA),
-                       ws + L.codesA);
+                       ws + L.codesA, bt);
   }
   if (side & OZ2_SIDE_B) {
-    dim3 gb((d.np / 64) * (d.kp / 64));
-    const unsigned vecB = ((uintptr_t)B % 16 == 0 && ldb % 2 == 0) ? 1u : 0u;
+    dim3 gb((d.np / 64) * (d.kp / 64), 1, bt.count);
+    const unsigned vecB = ((uintptr_t)B % 16 == 0 && ldb % 2 == 0 && bt.sB % 2 == 0) ? 1u : 0u;
     hipLaunchKernelGGL(k_scan_codes_cols, gb, dim3(256), 0, s, B, ldb, d.n, d.np / 64, d.k, vecB,
                        (unsigned long long*)(ws + L.colbits), (int16_t*)(ws + L.etB),
-                       ws + L.codesB);
+                       ws + L.codesB, bt);
   }
   return hipGetLastError();
 }
 
 hipError_t oz2_launch_rebase(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, int side,
-                             hipStream_t s) {
+                             const Oz2Batch& bt, hipStream_t s) {
   const size_t nA = (side & OZ2_SIDE_A) ? (size_t)d.mp * (d.kp / 64) : 0;
   const size_t nB = (side & OZ2_SIDE_B) ? (size_t)d.np * (d.kp / 64) : 0;
   if (nA + nB == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_rebase, dim3((unsigned)((nA + nB + 255) / 256)), dim3(256), 0, s,
+  hipLaunchKernelGGL(k_rebase, dim3((unsigned)((nA + nB + 255) / 256), 1, bt.count), dim3(256), 0, s,
                      ws + L.codesA, (const int16_t*)(ws + L.etA),
                      (const unsigned long long*)(ws + L.rowbits), d.mp, nA, ws + L.codesB,
                      (const int16_t*)(ws + L.etB), (const unsigned long long*)(ws + L.colbits),
-                     d.np, nB);
+                     d.np, nB, bt.ws);
   return hipGetLastError();
 }
 
 hipError_t oz2_launch_scales(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c,
-                             uint8_t* ws, int side, hipStream_t s) {
+                             uint8_t* ws, int side, const Oz2Batch& bt, hipStream_t s) {
   unsigned blocks = (unsigned)((d.mp + d.np + 255) / 256);
-  hipLaunchKernelGGL(k_scales, dim3(blocks), dim3(256), 0, s, d,
+  hipLaunchKernelGGL(k_scales, dim3(blocks, 1, bt.count), dim3(256), 0, s, d,
                      (const unsigned long long*)(ws + L.rowbits),
                      (const unsigned long long*)(ws + L.colbits), (const uint32_t*)(ws + L.Rmax),
                      (const uint32_t*)(ws + L.Kmax), (int32_t*)(ws + L.sA), (int32_t*)(ws + L.tB),
                      (int32_t*)(ws + L.eA), (int32_t*)(ws + L.eB), (uint32_t*)(ws + L.flagsA), (uint32_t*)(ws + L.flagsB), c.cA, c.cB,
-                     (int*)(ws + L.counters), (int*)(ws + L.listA), (int*)(ws + L.listB), side);
+                     (int*)(ws + L.counters), (int*)(ws + L.listA), (int*)(ws + L.listB), side, bt.ws);
   return hipGetLastError();
 }
 

@@ -26,7 +26,7 @@
 // c_this / c_next (mod m), so the next product continues the same residue.
 #include <algorithm>
 
-#include "oz2_internal.h"
+#include "oz2_tile.h"
 
 namespace {
 
@@ -34,7 +34,6 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
 constexpr int TILE = OZ2_TILE;   // 256
 constexpr int KS = OZ2_KBLK;     // 64 k bytes per stage
@@ -42,31 +41,6 @@ constexpr int OPB = TILE * KS;   // 16 KiB per operand per stage
 constexpr int STB = 2 * OPB;     // 32 KiB per stage
 constexpr int NB = 4;            // ring depth
 constexpr int NT = 512;          // threads per workgroup
-
-// s_barrier pinned in the instruction stream: the scheduler moves nothing
-// (not even register-only MFMAs) across it, so the phases below stay phases
-__device__ __forceinline__ void bar() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_barrier" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-__device__ __forceinline__ void wait_lgkm0() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// chunk swizzle of LDS row r: conflict free for 16 consecutive rows
-__device__ __forceinline__ int swz(int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); }
-
-// global_load_lds_dwordx4: lane L's 16 bytes land at M0 + 16 L.  The sc1
-// cache policy (streaming operands with no reuse inside the CU's vector L1)
-// measured 10-12% faster than the default policy on the 4096^3 residue GEMMs.
-__device__ __forceinline__ void dma16(const uint8_t* sbase, uint32_t voff, uint32_t m0) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 sc1" ::"v"(voff), "s"(sbase),
-               "s"(m0)
-               : "memory");
-}
 
 // Per-wave DMA stream over a sequence of plane products.  The code GEMM is a
 // single product; a residue-GEMM workgroup walks moduli mi0 .. mi1-1 of its
@@ -166,18 +140,6 @@ __device__ __forceinline__ void frags(const uint8_t* st, v8i (&fa)[4], v8i (&fb)
   for (int y = 0; y < 2; ++y) fb[y] = ldfrag(sb + y * 32 * KS, o0, o1);
 }
 
-// Tile of block b.  Blocks are dispatched round-robin over the 8 XCDs (each
-// with its own L2); when the grid allows it each XCD gets a 4x8 group of
-// tiles per 256-block round (4 A row panels, 8 B column panels).
-__device__ __forceinline__ int tile_of(int b, int ntm, int ntn) {
-  if ((ntm % 4) || (ntn % 8) || ((ntm * ntn) % 256)) return b;
-  const int xcd = b & 7, slot = b >> 3;
-  const int grp = slot >> 5, in = slot & 31;
-  const int gid = grp * 8 + xcd, ngx = ntm / 4;
-  const int gm = gid % ngx, gn = gid / ngx;
-  return (gm * 4 + (in & 3)) + (gn * 8 + (in >> 2)) * ntm;
-}
-
 // Wait until this wave's DMA share of stage s has landed.  When it waits
 // for stage s the wave has issued its shares up to stage min(s + 2, T - 1)
 // (four DMA instructions each, returning in order); stages below `landed`
@@ -260,18 +222,21 @@ __device__ __forceinline__ void halve(float (&u)[64], int lane) {
 // G'[i][j] <= 256 * 65536 = 2^24: exact in FP32.
 __global__ void __launch_bounds__(NT, 1)
 k_codegemm(const uint8_t* __restrict__ cA, const uint8_t* __restrict__ cB, int mp, int np,
-           int kp, uint32_t* Rmax, uint32_t* Kmax, int tbase) {
+           int kp, uint32_t* Rmax, uint32_t* Kmax, int tbase, size_t wsz) {
   __shared__ __attribute__((aligned(16))) uint8_t LB[NB * STB];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)LB;
   const int ntm = mp / TILE, ntn = np / TILE;
   const int tile = tile_of(tbase + blockIdx.x, ntm, ntn), slab = blockIdx.y;
   const int tm = tile % ntm, tn = tile / ntm;
   const int kbeg = slab * OZ2_CSLAB, kend = min(kp, kbeg + OZ2_CSLAB);
+  const size_t z = (size_t)blockIdx.z * wsz;
+  Rmax = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(Rmax) + z);
+  Kmax = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(Kmax) + z);
   Ctx x;
   x.kbA = (size_t)mp * KS;
   x.kbB = (size_t)np * KS;
-  x.a0 = cA + (size_t)tm * TILE * KS + (size_t)(kbeg / KS) * x.kbA;
-  x.b0 = cB + (size_t)tn * TILE * KS + (size_t)(kbeg / KS) * x.kbB;
+  x.a0 = cA + z + (size_t)tm * TILE * KS + (size_t)(kbeg / KS) * x.kbA;
+  x.b0 = cB + z + (size_t)tn * TILE * KS + (size_t)(kbeg / KS) * x.kbB;
   x.psA = x.psB = 0;
   x.nk = (kend - kbeg) / KS;
   x.T = x.nk;
@@ -747,13 +712,14 @@ static int launch_tiles(int rounds) {
   return std::max(256, (rounds * oz2_device_cus() + 255) / 256 * 256);
 }
 
-hipError_t oz2_launch_codegemm(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, hipStream_t s) {
+hipError_t oz2_launch_codegemm(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
+                               const Oz2Batch& bt, hipStream_t s) {
   const int tiles = (d.mp / TILE) * (d.np / TILE);
   const int chunk = launch_tiles(4);
   for (int tb = 0; tb < tiles; tb += chunk) {
-    dim3 grid(std::min(chunk, tiles - tb), d.cslabs);
+    dim3 grid(std::min(chunk, tiles - tb), d.cslabs, bt.count);
     hipLaunchKernelGGL(k_codegemm, grid, dim3(NT), 0, s, ws + L.codesA, ws + L.codesB, d.mp,
-                       d.np, d.kp, (uint32_t*)(ws + L.Rmax), (uint32_t*)(ws + L.Kmax), tb);
+                       d.np, d.kp, (uint32_t*)(ws + L.Rmax), (uint32_t*)(ws + L.Kmax), tb, bt.ws);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

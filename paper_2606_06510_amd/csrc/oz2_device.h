@@ -7,6 +7,12 @@ namespace {
 
 constexpr int NL = OZ2_NLIMB;
 
+// a workspace pointer moved to the workspace of another problem of the batch
+template <class T>
+__device__ __forceinline__ T* zws(T* p, size_t z) {
+  return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(p) + z);
+}
+
 constexpr unsigned long long kAbsMask = 0x7FFFFFFFFFFFFFFFull;
 constexpr unsigned long long kInfBits = 0x7FF0000000000000ull;
 

@@ -61,6 +61,36 @@ struct Oz2Const {
   int kcheap[OZ2_MAXR];
 };
 
+// The byte residue system of the one-call products (passed by value): the
+// fewest of the pairwise coprime moduli <= 256 below, largest first, whose
+// product M8 is at least 0.625 M, so that |C~| <= M/4 (1 + 2^-10) is at most
+// 0.41 M8 and unique in it: 10, 11, 12, 13, 15, 16, 17, 18, 19 moduli for
+// r = 8..16.
+#define OZ2_MAXB 19
+struct Oz2Byte {
+  int n;
+  uint32_t nm[OZ2_MAXB];          // 2^24 - m
+  uint32_t mg0[OZ2_MAXB];         // ceil(2^32 / m)
+  uint32_t mg7[OZ2_MAXB];         // ceil(2^39 / m)
+  uint32_t off0[OZ2_MAXB];        // the least multiple of m >= 2^22
+  uint32_t off7[OZ2_MAXB];        // the least multiple of m >= 2^29
+  int dot[OZ2_MAXB][2];           // centred residues of 256^0..3 and 256^4..7, a byte each
+  int tof[OZ2_MAXB];              // 128 + the least multiple of m >= 2^17
+  // W_i = (M8/m_i) ((M8/m_i)^-1 mod m_i), less M8 where above M8/2, in
+  // radix-2^38 limbs (the top one signed); M8 likewise
+  double W38[OZ2_MAXB][4];
+  double M38[4];
+  double mtop;                    // 2^(38 (limbs - 1)) / M8, limbs = 3 for n <= 15, else 4
+};
+
+// Problems of a batch in the z dimension of a grid: elements between their
+// operands and bytes between their workspaces (count 1, the rest 0: one product).
+struct Oz2Batch {
+  int count;
+  long long sA, sB, sC;
+  size_t ws;
+};
+
 struct Oz2Dims {
   int m, n, k;
   int mp, np, kp;             // padded: mp, np multiples of OZ2_TILE; kp of OZ2_KPAD
@@ -113,20 +143,20 @@ int oz2_device_cus();
 #define OZ2_SIDE_A 1
 #define OZ2_SIDE_B 2
 hipError_t oz2_launch_init(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, int side,
-                           hipStream_t s);
+                           const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_scan(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
                            const double* A, int lda, const double* B, int ldb, int side,
-                           hipStream_t s);
+                           const Oz2Batch& bt, hipStream_t s);
 // scan + per-tile code bytes in one read of each operand, then the bytes
 // rebased to the row exponents (the codes of the max-magnitude pass)
 hipError_t oz2_launch_scan_codes(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
                                  const double* A, int lda, const double* B, int ldb, int side,
-                                 hipStream_t s);
+                                 const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_rebase(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, int side,
-                             hipStream_t s);
-hipError_t oz2_launch_codegemm(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, hipStream_t s);
+                             const Oz2Batch& bt, hipStream_t s);
+hipError_t oz2_launch_codegemm(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_scales(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c,
-                             uint8_t* ws, int side, hipStream_t s);
+                             uint8_t* ws, int side, const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_tables(const Oz2Layout& L, const Oz2Const& c, uint8_t* ws, hipStream_t s);
 hipError_t oz2_launch_split(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c, uint8_t* ws,
                             const double* A, int lda, const double* B, int ldb, int side,
@@ -138,7 +168,7 @@ hipError_t oz2_launch_reconstruct(const Oz2Dims& d, const Oz2Layout& L, const Oz
                                   hipStream_t s);
 hipError_t oz2_launch_fallback(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
                                const double* A, int lda, const double* B, int ldb,
-                               double* C, int ldc, hipStream_t s);
+                               double* C, int ldc, const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_integers(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c,
                                uint8_t* ws, uint32_t* out, hipStream_t s);
 // the reconstruction's integer and rounding routines on n given residue
@@ -169,6 +199,16 @@ hipError_t oz2_launch_gemv(const Oz2Const& c, const double* A, int lda, int m, i
 hipError_t oz2_launch_gemv_crt(const Oz2Const& c, const int16_t* part, int splits, int mp, int m,
                                int nrhs, const int32_t* sA, const int32_t* tB, const uint32_t* fA,
                                const uint32_t* fB, int nofb, double* Y, int ldy, hipStream_t s);
+// the byte-residue route: the split of both operands, the residue products,
+// the CRT reconstruction with the gather of the fallback's panel
+hipError_t oz2_launch_byte_split(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
+                                 const double* A, int lda, const double* B, int ldb,
+                                 const Oz2Batch& bt, hipStream_t s);
+hipError_t oz2_launch_bytegemm(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
+                               const Oz2Batch& bt, hipStream_t s);
+hipError_t oz2_launch_byte_crt(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
+                               const double* A, int lda, double* C, int ldc, const Oz2Batch& bt,
+                               hipStream_t s);
 // all of Alg. 1 for `batch` problems of m, n, k <= 64 in one launch; tab = the
 // residue -> plane-byte tables (oz2_launch_tables); iout (normally null, a
 // diagnostic): write the exact integers of the unflagged outputs there,

@@ -269,10 +269,21 @@ __global__ void __launch_bounds__(256)
 k_fallback(Oz2Dims d, const double* __restrict__ A, int lda, const double* __restrict__ B, int ldb,
            double* C, int ldc, const int* __restrict__ counters, const int* __restrict__ listA,
            const int* __restrict__ listB, const uint32_t* __restrict__ fA,
-           const double* __restrict__ panel, int cap) {
+           const double* __restrict__ panel, int cap, Oz2Batch bt) {
   __shared__ double sa[FB_K][FB_T + 2];   // [k][row]
   __shared__ double sb[FB_K][FB_T + 2];   // [k][column]
   __shared__ int rowid[FB_T], colid[FB_T], arow[FB_T];
+  {
+    const size_t z = (size_t)blockIdx.z * bt.ws;
+    counters = zws(counters, z);
+    listA = zws(listA, z);
+    listB = zws(listB, z);
+    fA = zws(fA, z);
+    if (panel) panel = zws(panel, z);
+    A += (size_t)blockIdx.z * bt.sA;
+    B += (size_t)blockIdx.z * bt.sB;
+    C += (size_t)blockIdx.z * bt.sC;
+  }
   const int na = counters[0], nb = counters[1];
   const bool acc = (d.flags & 1u) != 0;
   const bool force = (d.flags & 16u) != 0;
@@ -447,13 +458,14 @@ hipError_t oz2_launch_crt_probe(const Oz2Const& c, const int16_t* res, const int
 
 hipError_t oz2_launch_fallback(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, const double* A,
                                int lda, const double* B, int ldb, double* C, int ldc,
-                               hipStream_t s) {
+                               const Oz2Batch& bt, hipStream_t s) {
   // the lists were filled by the deconstruction (k_scales: T1, k_split: T2)
   // the panel of flagged rows was gathered by the reconstruction launch
-  hipLaunchKernelGGL(k_fallback, dim3(1024), dim3(256), 0, s, d, A, lda, B, ldb, C, ldc,
-                     (const int*)(ws + L.counters), (const int*)(ws + L.listA),
-                     (const int*)(ws + L.listB), (const uint32_t*)(ws + L.flagsA),
-                     (const double*)(ws + L.panel), std::min(d.mp, OZ2_FBCAP));
+  hipLaunchKernelGGL(k_fallback, dim3(std::max(1, 1024 / bt.count), 1, bt.count), dim3(256), 0, s, d,
+                     A, lda, B, ldb, C, ldc, (const int*)(ws + L.counters),
+                     (const int*)(ws + L.listA), (const int*)(ws + L.listB),
+                     (const uint32_t*)(ws + L.flagsA), (const double*)(ws + L.panel),
+                     std::min(d.mp, OZ2_FBCAP), bt);
   return hipGetLastError();
 }
 
@@ -463,7 +475,7 @@ hipError_t oz2_launch_fallback_direct(const Oz2Dims& d, const Oz2Layout& L, uint
   hipLaunchKernelGGL(k_fallback, dim3(1024), dim3(256), 0, s, d, A, lda, B, ldb, C, ldc,
                      (const int*)(ws + L.counters), (const int*)(ws + L.listA),
                      (const int*)(ws + L.listB), (const uint32_t*)(ws + L.flagsA),
-                     (const double*)nullptr, 0);
+                     (const double*)nullptr, 0, Oz2Batch{1, 0, 0, 0, 0});
   return hipGetLastError();
 }
 

@@ -1,0 +1,110 @@
+"""The byte-residue route of the one-call products against the plane route of
+the staged API: the same integers, so the same bits in every unflagged entry
+(and the same fallback in the others)."""
+import numpy as np
+import pytest
+
+import synth
+from tests.gpu_util import bits, device
+
+pytestmark = pytest.mark.gpu
+
+
+def _both(m, n, k, r, flags=0, seed=0, pad=0, edit=None):
+    import paper_2606_06510_amd as oz
+    import torch
+    dev = device()
+    rng = np.random.default_rng(seed)
+    A = (rng.random((m, k)) - 0.5) * np.exp(0.5 * rng.standard_normal((m, k)))
+    B = (rng.random((k, n)) - 0.5) * np.exp(0.5 * rng.standard_normal((k, n)))
+    if edit:
+        edit(A, B)
+    Cin = rng.standard_normal((m, n))
+
+    def put(X):
+        T = torch.zeros((X.shape[1], X.shape[0] + pad), dtype=torch.float64, device=dev)
+        T[:, :X.shape[0]] = torch.from_numpy(np.ascontiguousarray(X.T)).to(dev)
+        return T[:, :X.shape[0]].t()
+    Ad, Bd, C1, C2 = put(A), put(B), put(Cin), put(Cin)
+    oz.matmul(Ad, Bd, r, flags=flags, C=C1)
+    plan = oz.Plan(m, n, k, r, flags, device=dev)
+    plan.deconstruct(Ad, Bd)
+    plan.residue_gemm()
+    plan.reconstruct(C2)
+    torch.cuda.synchronize()
+    return (oz.from_device_colmajor(C1), oz.from_device_colmajor(C2))
+
+
+def _same(x, y):
+    assert np.array_equal(np.isnan(x), np.isnan(y))
+    ok = ~np.isnan(x)
+    assert np.array_equal(bits(x)[ok], bits(y)[ok])
+
+
+@pytest.mark.parametrize("r", range(8, 17))
+def test_every_moduli_count(r):
+    _same(*_both(150, 90, 300, r, seed=r))
+
+
+# tile edges of both kernels, one and several K-stages, the 256-k bound of the
+# short reduction and the 32768-k bound of an exact slab
+@pytest.mark.parametrize("shape", [(1, 1, 1), (17, 3, 63), (64, 16, 64), (129, 127, 65),
+                                   (256, 256, 256), (257, 255, 257), (300, 270, 320),
+                                   (1100, 1030, 700), (130, 70, 32768), (140, 60, 32833),
+                                   (70, 260, 70000)])
+@pytest.mark.parametrize("r", [12, 16])
+def test_shapes(shape, r):
+    _same(*_both(*shape, r, seed=sum(shape)))
+
+
+@pytest.mark.parametrize("shape", [(2048, 2304, 192), (4352, 4096, 128), (2100, 2100, 4300)])
+def test_many_tiles(shape):
+    """the launches of whole rounds, several moduli per workgroup, an
+    incomplete last share of the XCDs"""
+    _same(*_both(*shape, 13, seed=5))
+
+
+@pytest.mark.parametrize("name", ["ACCUMULATE", "SCALE_FIXED", "QUANT_TZ", "NO_FALLBACK",
+                                  "FORCE_FALLBACK"])
+def test_flags(name):
+    import paper_2606_06510_amd as oz
+
+    def edit(A, B):
+        A[3, ::2] *= 1e200      # T2
+        A[7, 5] = np.nan        # T1
+        B[2, 9] = np.inf
+        A[11] = 0.0
+    flags = getattr(oz, "OZ2_" + name)
+    _same(*_both(210, 140, 330, 12, flags=flags, seed=3, pad=3, edit=edit))
+
+
+def test_extreme_digits():
+    """entries whose quantised integers reach the widest digits: powers of two
+    and their neighbours, both signs, against a constant operand"""
+    def edit(A, B):
+        v = np.array([1.0, -1.0, 1 - 2.0 ** -53, -(1 - 2.0 ** -53), 0.5, 2.0 ** -40])
+        A[:] = np.resize(v, A.shape)
+        B[:] = np.where(np.arange(B.shape[1]) % 2, 1.0, -1.0 + 2.0 ** -52)
+    for r in (8, 12, 15):
+        _same(*_both(130, 130, 2000, r, edit=edit))
+
+
+@pytest.mark.parametrize("case", [(5, 70, 90, 33, 12), (3, 200, 66, 129, 15), (40, 65, 64, 64, 8)])
+def test_batches_side_by_side(case):
+    import paper_2606_06510_amd as oz
+    import torch
+    b, m, n, k, r = case
+    dev = device()
+    gen = torch.Generator(device=dev).manual_seed(1)
+    A = torch.rand((b, k + 1, m + 3), generator=gen, dtype=torch.float64, device=dev) - 0.5
+    B = torch.rand((b, n, k + 2), generator=gen, dtype=torch.float64, device=dev) - 0.5
+    A[1, :, 4] *= 1e-30
+    A[1, 3, 4] = 1e200          # a fallback row in one problem only
+    C = torch.full((b, n + 1, m + 1), 7.0, dtype=torch.float64, device=dev)
+    oz.ozaki2_dgemm_strided_batched(m, n, k, A, m + 3, A.stride(0), B, k + 2, B.stride(0), C, m + 1,
+                                    C.stride(0), b, r)
+    torch.cuda.synchronize()
+    assert torch.all(C[:, n] == 7.0) and torch.all(C[:, :, m] == 7.0)
+    for i in range(b):
+        D = oz.matmul(A[i, :k, :m].t(), B[i, :, :k].t(), r)
+        assert torch.equal(C[i, :n, :m].t(), D), i
