@@ -149,10 +149,11 @@ int ozaki2_dgemm_strided_batched(int m, int n, int k, const double* A, int lda,
  * 1: Batched GEMV"): Y = A X for A (m x k, lda), X (k x nrhs, ldx) with
  * 1 <= nrhs <= 16 right-hand sides, Y (m x nrhs, ldy), all column-major FP64
  * device memory.  A is read twice in FP64 -- once for its row exponents,
- * once by the fused kernel that quantises, reduces and splits it into E4M3
- * digit planes on the fly and multiplies them on FP8 MFMA against X's planes
- * with all r moduli's accumulators in registers -- and never written in any
- * other form.  The scaling is the fixed rule (Alg. 1's mu = k max|A~| max|X~|,
+ * once by the fused kernel that quantises it on the fly into base-256 digits
+ * and multiplies them on int8 MFMA against X's, the products of digits of
+ * equal weight summed exactly in int32 -- and never written in any other
+ * form (the integers are those of Alg. 2's residues; digits cost one
+ * conversion per element instead of r).  The scaling is the fixed rule (Alg. 1's mu = k max|A~| max|X~|,
  * as OZ2_SCALE_FIXED): entries of unflagged rows and columns are the IEEE
  * RN-even value of D^-1 (A~ X~) E^-1 exactly as ozaki2_dgemm_ex with
  * OZ2_SCALE_FIXED computes it; flagged rows of A / columns of X (T1, T2) are

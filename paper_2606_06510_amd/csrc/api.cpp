@@ -1011,42 +1011,18 @@ int ozaki2_gemv_batched(int m, int k, int nrhs, const double* A, int lda, const 
   Oz2Const c;
   GemvShape g;
   if (!make_const(num_moduli, c) || !gemv_shape(m, k, nrhs, flags, g)) return OZ2_E_INVALID;
-  // the fused kernel treats moduli r-6 .. r-1 (the six squares) as square
-  for (int i = 0; i < c.r; ++i)
-    if ((c.sq[i] != 0) != (i >= c.r - 6)) return OZ2_E_UNSUPPORTED;
   const Oz2Layout L = make_gemv_layout(g, c);
   if (!workspace || ws_bytes < L.total || ((uintptr_t)workspace & 255)) return OZ2_E_WORKSPACE;
   st = device_ok();
   if (st != OZ2_OK) return st;
   uint8_t* ws = (uint8_t*)workspace;
   const Oz2Dims& d = g.d;
-  const unsigned tz = (flags & OZ2_QUANT_TZ) ? 1u : 0u;
-  const int listed = (flags & OZ2_FORCE_FALLBACK) ? 1 : 0;
-  // with OZ2_REUSE_A_SCALES, A's side (scales, flags, list, counter) and the
-  // plane tables are the previous call's
-  const bool reuse = (flags & OZ2_REUSE_A_SCALES) != 0;
-  const int sides = reuse ? OZ2_SIDE_B : (OZ2_SIDE_A | OZ2_SIDE_B);
-  hipError_t e = oz2_launch_init(d, L, ws, sides, kOne, s);
-  if (e == hipSuccess) e = oz2_launch_scan(d, L, ws, A, lda, X, ldx, sides, kOne, s);
-  if (e == hipSuccess) e = oz2_launch_scales(d, L, c, ws, sides, kOne, s);
-  if (e == hipSuccess && !reuse) e = oz2_launch_tables(L, c, ws, s);
-  if (e == hipSuccess)
-    e = oz2_launch_gemv_xplanes(c, X, ldx, k, nrhs, (const int32_t*)(ws + L.tB),
-                                (uint32_t*)(ws + L.flagsB), (int*)(ws + L.counters) + 1,
-                                (int*)(ws + L.listB), listed, (const uint32_t*)(ws + L.tabs), tz,
-                                ws + L.xfrag, s);
-  if (e == hipSuccess)
-    e = oz2_launch_gemv(c, A, lda, m, k, g.splits, (const int32_t*)(ws + L.sA),
-                        (uint32_t*)(ws + L.flagsA), (int*)(ws + L.counters), (int*)(ws + L.listA),
-                        listed, ws + L.xfrag, (const uint32_t*)(ws + L.tabs), tz,
-                        (int16_t*)(ws + L.part), d.mp, s);
-  const int nofb = (flags & OZ2_NO_FALLBACK) ? 1 : 0;
-  if (e == hipSuccess)
-    e = oz2_launch_gemv_crt(c, (const int16_t*)(ws + L.part), g.splits, d.mp, m, nrhs,
-                            (const int32_t*)(ws + L.sA), (const int32_t*)(ws + L.tB),
-                            (const uint32_t*)(ws + L.flagsA), (const uint32_t*)(ws + L.flagsB),
-                            nofb, Y, ldy, s);
-  if (e == hipSuccess && !nofb) e = oz2_launch_fallback_direct(d, L, ws, A, lda, X, ldx, Y, ldy, s);
+  // with OZ2_REUSE_A_SCALES, A's side (row maxima, flags, list, counter) is
+  // the previous call's
+  hipError_t e = oz2_launch_gemv(c, d, L, ws, A, lda, X, ldx, Y, ldy, g.splits,
+                                 (flags & OZ2_REUSE_A_SCALES) != 0, s);
+  if (e == hipSuccess && !(flags & OZ2_NO_FALLBACK))
+    e = oz2_launch_fallback_direct(d, L, ws, A, lda, X, ldx, Y, ldy, s);
   return hip_status(e);
 }
 

@@ -40,42 +40,11 @@ __global__ void k_init(unsigned long long* rowbits, int mp, unsigned long long* 
   }
 }
 
-// rows of a column-major matrix: lanes along the (contiguous) row index, two
-// rows per thread (16-byte loads when the caller has checked the alignment),
-// eight loads in flight; one k-chunk per grid row, combined with atomicMax.
 __global__ void __launch_bounds__(256) k_scan_rows(const double* __restrict__ A, int lda, int m, int k,
                                                    int kchunk, unsigned vec,
                                                    unsigned long long* rowbits, Oz2Batch bt) {
-  A += (size_t)blockIdx.z * bt.sA;
-  rowbits = zws(rowbits, (size_t)blockIdx.z * bt.ws);
-  const int i = 2 * (blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= m) return;
-  const int l0 = blockIdx.y * kchunk;
-  const int l1 = min(k, l0 + kchunk);
-  const bool pair = vec && i + 1 < m;
-  unsigned long long m0 = 0, m1 = 0;
-  int l = l0;
-  if (pair) {
-    const double* p = A + i + (size_t)l0 * lda;
-    for (; l + 8 <= l1; l += 8) {
-      double2 v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const double2*>(p + (size_t)u * lda);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        m0 = max(m0, abs_bits(v[u].x));
-        m1 = max(m1, abs_bits(v[u].y));
-      }
-      p += 8 * (size_t)lda;
-    }
-  }
-  for (; l < l1; ++l) {
-    const double* p = A + i + (size_t)l * lda;
-    m0 = max(m0, abs_bits(p[0]));
-    if (i + 1 < m) m1 = max(m1, abs_bits(p[1]));
-  }
-  atomicMax(rowbits + i, m0);
-  if (i + 1 < m) atomicMax(rowbits + i + 1, m1);
+  scan_rows_block(A + (size_t)blockIdx.z * bt.sA, lda, m, k, kchunk, vec,
+                  zws(rowbits, (size_t)blockIdx.z * bt.ws), blockIdx.x, blockIdx.y);
 }
 
 // contiguous columns: one wave per column, 16-byte loads (1 KiB per wave

@@ -1,408 +1,391 @@
-// Batched GEMV Y = A X (X: k x nrhs, nrhs <= 16) as the paper's fused Ozaki-II
-// GEMV (Alg. 2, section "Strategy 1: Batched GEMV"): every element of A is
-// read once in FP64 and deconstructed on the fly -- quantised with its row's
-// scale, reduced modulo each m_i, split into E4M3 digit planes -- and the
-// planes of every modulus go straight into FP8 MFMAs against the planes of X,
-// with all r sets of accumulators held in registers (the paper's
-// C_acc^(1..r)).  Nothing of A is written back.  The scaling diagonals D, E
-// are inputs of Alg. 2; here they are the fixed rule of Alg. 1's bound
-// mu = k max|A~| max|X~| (OZ2_SCALE_FIXED: a row's scale depends on that row
-// alone), computed by the staged path's scan and scale kernels.
+// Batched GEMV Y = A X (X: k x nrhs, nrhs <= 16), Alg. 2's fused form: every
+// element of A is read in FP64, quantised on the fly and multiplied on the
+// matrix units, and nothing of A is written back.  The scaling is the fixed
+// rule of Alg. 1's bound mu = k max|A~| max|X~| (OZ2_SCALE_FIXED: a row's scale
+// depends on that row alone), so A is read twice: for its row maxima, then by
+// the product.
 //
-// Kernels (after the scan and scale kernels and the plane tables):
-//  * k_gemv_xplanes: X quantised, reduced and split once into MFMA operand
-//    fragments [chunk][plane][half][lane][16 B] (k in chunks of 128);
-//  * k_gemv<R>: a workgroup of 8 waves (2 per SIMD) owns 128 rows of A (wave
-//    w rows 16w..16w+15) and a range of chunks (split-K); per 32-k quarter of
-//    a chunk each lane loads 8 elements of its row (row L%16, k 8(L/16)..+7:
-//    exactly its operand bytes of v_mfma_f32_16x16x32_fp8_fp8), the next
-//    quarter's loads in flight, quantises them once, then per modulus forms
-//    their residues (exact fp64), looks the E4M3 plane bytes up in an LDS
-//    table and issues the modulus's three plane products against the X
-//    fragments (staged in LDS, shared by the 8 waves).  Square m = s^2:
-//    acc0 += d0 e0, acc1 += d1 e0 + d0 e1; nonsquare (Eq. (kar), b = 4):
-//    acc0 += (d0+d1)(e0+e1), acc1 += d0 e0, acc2 += d1 e1.  Every partial
-//    sum is an integer below 2^24 while a split spans at most 32768 k
-//    (Eq. (accum-exact)).  The epilogue combines them with the coefficients
-//    (1, s) or (16, -15, 240) modulo m and stores a representative per
-//    output and modulus (int16, |x| <= m/2 + 2);
-//  * k_gemv_crt<R>: sums the splits' residues modulo m, reconstructs the
-//    exact integer with the reconstruction's own CRT routine, rounds it once
-//    with the shift -(s_i + t_b) and writes Y (rows and columns flagged for
-//    the native fallback are left to it).
+// The integers Y~ = A~ X~ are formed exactly.  With at most 16 columns every
+// element of A meets few multiplications, so what an element costs is its
+// conversion, and residues modulo r moduli cost r conversions (127 operations
+// per element at r = 13: 1.53 ms for 16384^2 x 8, 1.4 TB/s).  Here an element
+// is its eight balanced base-256 digits -- the bytes of a + 0x0080..80, two
+// instructions -- and the products of digits of equal weight are summed in
+// int32 by v_mfma_i32_16x16x64_i8:
+//     Y~ = sum_w 256^w sum_l sum_p a_p(l) x_{w-p}(l).
+// The inner sums over (l, p) are ONE contraction: the A operand is the
+// elements' bytes as they stand, and column (w, b) of the B operand holds the
+// reversed digits of x(l, b) shifted by 7 - w bytes (two 64-bit shifts of the
+// same registers for each w).  A wave's 64 k-bytes are 8 elements of 16 rows.
+// The weights needed are 2 D - 1 or fewer, D the digits of the widths (7 for r
+// = 12; 4 for r = 8).  |sums| <= 8 * 2^14 per element stay below 2^31 for the
+// at most 8200 elements a wave takes.
+//
+// What bounds it: the two reads of A.  Per 8 x 16 elements the matrix unit
+// takes 16 NT cycles (NT tiles of 16 columns, 7 for 8 right-hand sides), the
+// conversion some 20 instructions per element.
+#include <algorithm>
+
 #include "oz2_device.h"
 
 namespace {
 
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v4f __attribute__((ext_vector_type(4)));
+typedef int v4i __attribute__((ext_vector_type(4)));
 
-constexpr int GV_ROWS = 128;   // rows of A per workgroup
-constexpr int GV_K = 128;      // k per chunk (X's fragments are staged per chunk)
-constexpr int GV_NT = 512;     // threads per workgroup (8 waves)
-constexpr int GV_FRAG = 2048;  // bytes of one plane's operand fragments per chunk
+constexpr int GT = 256;        // threads per workgroup: 4 waves, each a quarter of k
 
-// 16 x 16 x 32 E4M3 product: lane L holds row (A) / column (B) L%16,
-// k 8(L/16) .. +7; the result lane L column L%16, rows 4(L/16) .. +3
-__device__ __forceinline__ v4f mfma16k32(long a, long b, v4f c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(a, b, c, 0, 0, 0);
+// digits of a finite x scaled by 2^sc, rounded (RN-even, or toward zero), as
+// the eight bytes of a two's complement number; t2: a nonzero x gives zero
+__device__ __forceinline__ uint64_t digits(double x, int sc, unsigned tz, bool& t2) {
+  const double y = ldexp(x, sc);
+  const double a = tz ? trunc(y) : rint(y);
+  t2 = (x != 0.0) && (a == 0.0);
+  const double h = floor(a * 0x1p-32);
+  const uint64_t v = (((uint64_t)(uint32_t)(int)h << 32) | (uint32_t)fma(-h, 0x1p32, a)) +
+                     0x0080808080808080ull;
+  return v ^ 0x0080808080808080ull;
 }
 
-// Quantise 32 elements with the power-of-two scale sc (Eq. (scale)): a =
-// RN(x 2^sc) (or truncation) = ah 2^32 + al, exact; t2 is set when a nonzero
-// element quantises to zero.
-__device__ __forceinline__ void quantise32(const double (&x)[32], int sc, unsigned tz, bool& t2,
-                                           double (&ah)[32], double (&al)[32]) {
-#pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    const double y = ldexp(x[j], sc);
-    const double a = tz ? trunc(y) : rint(y);
-    t2 |= (x[j] != 0.0) && (a == 0.0);
-    const double h = floor(a * 0x1p-32);
-    ah[j] = h;
-    al[j] = fma(-h, 0x1p32, a);
+__device__ __forceinline__ int row_scale(unsigned long long b, int width) {
+  return b >= kInfBits ? 0 : width - (b ? exp_of_bits(b) : 0);
+}
+
+// ---------------------------------------------------------------- scan
+__global__ void k_gemv_init(unsigned long long* rowbits, uint32_t* flagsA, int mp, int m, int* counters,
+                            int* listA, int keepA, int force) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) counters[1] = 0;
+  if (keepA) return;
+  if (i == 0) counters[0] = force ? m : 0;
+  if (i < mp) {
+    rowbits[i] = 0;
+    flagsA[i] = 0;
   }
+  if (force && i < m) listA[i] = i;
 }
 
-// Operand bytes of the planes of modulus i for 32 quantised elements: word g
-// of plane p holds the E4M3 digit bytes of elements 4g..4g+3 (table entry
-// byte p: d0, d1, d0 + d1).
-template <bool SQ>
-__device__ __forceinline__ void planes32(const Oz2Const& c, int i, const uint32_t* tab,
-                                         const double (&ah)[32], const double (&al)[32],
-                                         v8i& p0, v8i& p1, v8i& p2) {
-  const double m = (double)c.m[i], c32 = (double)c.c32[i], dinv = c.dinv[i];
-  const int to = c.toff[i];
-#pragma unroll
-  for (int g = 0; g < 8; ++g) {
-    uint32_t e[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) e[u] = tab[to + centred_residue(ah[4 * g + u], al[4 * g + u], m, c32, dinv)];
-    p0[g] = (int)gather_byte(e[0], e[1], e[2], e[3], 0x05010400u);
-    p1[g] = (int)gather_byte(e[0], e[1], e[2], e[3], 0x05010501u);
-    if (!SQ) p2[g] = (int)gather_byte(e[0], e[1], e[2], e[3], 0x05010602u);
-  }
-}
-
-// Quantise 8 elements (as quantise32).
-__device__ __forceinline__ void quantise8(const double (&x)[8], int sc, unsigned tz, bool& t2,
-                                          double (&ah)[8], double (&al)[8]) {
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const double y = ldexp(x[j], sc);
-    const double a = tz ? trunc(y) : rint(y);
-    t2 |= (x[j] != 0.0) && (a == 0.0);
-    const double h = floor(a * 0x1p-32);
-    ah[j] = h;
-    al[j] = fma(-h, 0x1p32, a);
-  }
-}
-
-// Operand bytes of the planes of modulus i for 8 quantised elements (byte j
-// of plane p: table entry byte p of element j: d0, d1, d0 + d1).
-template <bool SQ>
-__device__ __forceinline__ void planes8(const Oz2Const& c, int i, const uint32_t* tab,
-                                        const double (&ah)[8], const double (&al)[8], long& p0,
-                                        long& p1, long& p2) {
-  const double m = (double)c.m[i], c32 = (double)c.c32[i], dinv = c.dinv[i];
-  const int to = c.toff[i];
-  uint32_t e[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) e[j] = tab[to + centred_residue(ah[j], al[j], m, c32, dinv)];
-  auto word = [&](int g, uint32_t sel) { return gather_byte(e[4 * g], e[4 * g + 1], e[4 * g + 2], e[4 * g + 3], sel); };
-  p0 = (long)(((uint64_t)word(1, 0x05010400u) << 32) | word(0, 0x05010400u));
-  p1 = (long)(((uint64_t)word(1, 0x05010501u) << 32) | word(0, 0x05010501u));
-  if (!SQ) p2 = (long)(((uint64_t)word(1, 0x05010602u) << 32) | word(0, 0x05010602u));
-}
-
-// X's operand bytes of plane p for quarter q of the chunk staged in LDS:
-// lane L needs column L%16, k 32 q + 8 (L/16) .. +7, which the chunk's
-// fragment layout ([half][lane'][16 B], lane' holding column lane'%16, k
-// 32 (lane'/16) .. +31) keeps in lane' = 16 q + L%16, byte 8 (L/16); a
-// wave's 8-byte reads cover 2 x 256 contiguous bytes
-__device__ __forceinline__ long xfrag8(const uint8_t* xs, int p, int q, int lane) {
-  const int u = lane >> 4;
-  const uint8_t* a = xs + (size_t)p * GV_FRAG + (u >> 1) * 1024 + 16 * (16 * q + (lane & 15)) + 8 * (u & 1);
-  return *reinterpret_cast<const long*>(a);
-}
-
-// x - m rint(x/m) in fp32: a representative of magnitude <= m/2 + 1 for an
-// integer |x| <= 2^24 (the quotient estimate is within 2^-7 of the exact one)
-__device__ __forceinline__ float red32(float x, float fm, float inv) {
-  return __builtin_fmaf(-rintf(x * inv), fm, x);
-}
-
-// ---------------------------------------------------------------- X planes
-// Thread (chunk c, lane L) quantises column b = L%16 of X at k = 128c +
-// 32(L/16) .. +31 with its scale and writes its 32 operand bytes of every
-// plane.  Columns b >= nrhs and T1 columns are zeros.  T2 columns are
-// flagged and listed for the native fallback (once per column).
+// Workgroups 0 .. nrb-1: column b of X, its maximum, scale, flags and
+// reversed digits: 8 bytes per (l, b) at [l/2][b][l%2], zeros for b >= nrhs and
+// l >= k.  The others: the row maxima of A, 512 rows x kchunk columns each
+// (hidden under them, one workgroup per column is enough for X).
 __global__ void __launch_bounds__(256)
-k_gemv_xplanes(Oz2Const c, const double* __restrict__ X, int ldx, int k, int nrhs, int chunks,
-               const int32_t* __restrict__ tB, uint32_t* flagsB, int* countB, int* listB,
-               int listed, const uint32_t* __restrict__ tab, unsigned tz, uint8_t* __restrict__ xf) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= chunks * 64) return;
-  const int ch = t >> 6, lane = t & 63, b = lane & 15;
-  const int l0 = ch * GV_K + 32 * (lane >> 4);
-  const bool cok = b < nrhs;
-  const uint32_t f = cok ? flagsB[b] : 0u;
-  const bool zero = !cok || (f & OZ2_T1);
-  double x[32];
-#pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    const int l = l0 + j;
-    x[j] = (!zero && l < k) ? X[(size_t)l + (size_t)b * ldx] : 0.0;
+k_gemv_scan(const double* __restrict__ A, int lda, int m, int k, int kchunk, unsigned vec, int gx,
+            unsigned long long* rowbits, const double* __restrict__ X, int ldx, int nrhs, int nrb,
+            int kp, int width, unsigned tz, int force, int32_t* tB, uint32_t* flagsB, int* countB,
+            int* listB, uint64_t* __restrict__ xd) {
+  const int blk = (int)blockIdx.x - nrb;
+  if (blk >= 0) {
+    scan_rows_block(A, lda, m, k, kchunk, vec, rowbits, blk % gx, blk / gx);
+    return;
   }
-  bool t2 = false;
-  double ah[32], al[32];
-  quantise32(x, zero ? 0 : tB[b], tz, t2, ah, al);
-  if (t2 && !(atomicOr(flagsB + b, OZ2_T2) & (OZ2_T1 | OZ2_T2)) && !listed)
-    listB[atomicAdd(countB, 1)] = b;
-  uint8_t* base = xf + (size_t)ch * c.P * GV_FRAG + 16 * lane;
-  for (int i = 0; i < c.r; ++i) {
-    v8i p0, p1, p2;
-    if (c.sq[i]) planes32<true>(c, i, tab, ah, al, p0, p1, p2);
-    else planes32<false>(c, i, tab, ah, al, p0, p1, p2);
-    const int np = c.sq[i] ? 2 : 3;
-    for (int p = 0; p < np; ++p) {
-      const v8i v = p == 0 ? p0 : (p == 1 ? p1 : p2);
-      uint8_t* d = base + (size_t)(c.pbase[i] + p) * GV_FRAG;
-      *reinterpret_cast<uint4*>(d) = make_uint4((uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]);
-      *reinterpret_cast<uint4*>(d + 1024) = make_uint4((uint32_t)v[4], (uint32_t)v[5], (uint32_t)v[6], (uint32_t)v[7]);
-    }
+  __shared__ unsigned long long red[4];
+  __shared__ unsigned flagged;
+  const int b = blockIdx.x, t = threadIdx.x;
+  const double* x = X + (size_t)b * ldx;
+  unsigned long long mx = 0;
+  if (b < nrhs)
+    for (int l = t; l < k; l += 256) mx = max(mx, abs_bits(x[l]));
+  for (int off = 32; off; off >>= 1) mx = max(mx, (unsigned long long)__shfl_xor((long long)mx, off));
+  if ((t & 63) == 0) red[t >> 6] = mx;
+  if (t == 0) flagged = 0;
+  __syncthreads();
+  mx = max(max(red[0], red[1]), max(red[2], red[3]));
+  const bool t1 = mx >= kInfBits;
+  const int sc = row_scale(mx, width);
+  bool any = false;
+  for (int l = t; l < kp; l += 256) {
+    bool t2 = false;
+    const uint64_t v = (b < nrhs && l < k && !t1) ? digits(x[l], sc, tz, t2) : 0ull;
+    any |= t2;
+    xd[((size_t)(l >> 1) * nrb + b) * 2 + (l & 1)] = __builtin_bswap64(v);
+  }
+  if (any) atomicOr(&flagged, 1u);
+  __syncthreads();
+  if (t == 0 && b < nrhs) {
+    const uint32_t f = (t1 ? OZ2_T1 : 0u) | (flagged ? OZ2_T2 : 0u);
+    tB[b] = sc;
+    flagsB[b] = f;
+    if (f && !force) listB[atomicAdd(countB, 1)] = b;
   }
 }
 
-// ---------------------------------------------------------------- fused GEMV
-// grid (row blocks of 64, splits); split s covers chunks s*cps .. +cps-1.
-// The moduli come in ascending order and the six squares of the set are the
-// six largest, so modulus i is square exactly when i >= R - 6 (the host
-// checks this against the constants before launching).
-template <int R>
-__global__ void __launch_bounds__(GV_NT, 1)
-k_gemv(Oz2Const c, const double* __restrict__ A, int lda, int m, int k, int chunks, int cps,
-       const int32_t* __restrict__ sA, uint32_t* flagsA, int* countA, int* listA, int listed,
-       const uint8_t* __restrict__ xf, const uint32_t* __restrict__ gtab, unsigned tz,
-       int16_t* __restrict__ part, int mp) {
-  extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
-  uint32_t* tab = smem;
-  uint8_t* xs = reinterpret_cast<uint8_t*>(smem + ((c.tabsz + 3) & ~3));
-  for (int i = threadIdx.x; i < c.tabsz; i += GV_NT) tab[i] = gtab[i];
-  const int split = blockIdx.y;
-  const int c0 = split * cps, c1 = min(chunks, c0 + cps);
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int row = blockIdx.x * GV_ROWS + 16 * w + (lane & 15);
-  const int kq = 8 * (lane >> 4);
-  const bool rok = row < m;
-  const uint32_t f0 = rok ? flagsA[row] : 0u;
-  const bool zero = !rok || (f0 & OZ2_T1);
-  const int sc = zero ? 0 : sA[row];
-  const int fbytes = c.P * GV_FRAG;
-  const double* arow = A + (size_t)row;
+// ---------------------------------------------------------------- product
+// The exact integer of weights' sums Y_w (from LDS, stride st), in NW words.
+template <int NW>
+__device__ __forceinline__ void carry(const long long* y, int nw, int nrb, uint32_t (&o)[NW]) {
+  uint32_t byte[4 * NW];
+  long long acc = 0;
+  const int per = 16 / nrb;
+#pragma unroll
+  for (int w = 0; w < 4 * NW; ++w) {
+    if (w < nw) acc += y[(w / per) * 16 + (w % per) * nrb];
+    byte[w] = (uint32_t)acc & 0xFFu;
+    acc >>= 8;
+  }
+#pragma unroll
+  for (int q = 0; q < NW; ++q)
+    o[q] = byte[4 * q] | (byte[4 * q + 1] << 8) | (byte[4 * q + 2] << 16) | (byte[4 * q + 3] << 24);
+}
 
-  v4f acc[R][3];
+// grid (blocks of 16 RB rows, splits of k).  Lane L = (g, i) of a wave: rows
+// row0 + RB i + q (q < RB, contiguous: 16-byte loads when aligned) and elements
+// l = 8 c + 2 g, + 1 of every chunk c of 8; the wave takes chunks c0 + wave,
+// + 4, .... NRB: columns of X rounded up to a power of two; NT tiles of 16
+// columns (w, b), 16 / NRB weights each.
+template <int NRB, int NT, int RB, int NW>
+__global__ void __launch_bounds__(GT, 2)
+k_gemv(const double* __restrict__ A, int lda, int m, int k, int cps, int width, unsigned vec,
+       unsigned tz, int nweights, const unsigned long long* __restrict__ rowbits, uint32_t* flagsA,
+       int* countA, int* listA, int listed, const uint4* __restrict__ xd, int nrhs,
+       const int32_t* __restrict__ tB, uint32_t* __restrict__ part, int mp, double* Y, int ldy) {
+  constexpr int PER = 16 / NRB, ROWS = 16 * RB;
+  __shared__ unsigned long long sums[ROWS * NT * 16];
+  const int t = threadIdx.x, lane = t & 63, i = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int row0 = (int)blockIdx.x * ROWS, rl = row0 + RB * i;
+  for (int e = t; e < ROWS * NT * 16; e += GT) sums[e] = 0;
+  __syncthreads();
+  int sc[RB];
+  unsigned t1 = 0;        // bit q: row rl + q is T1 or beyond m
 #pragma unroll
-  for (int i = 0; i < R; ++i)
+  for (int q = 0; q < RB; ++q) {
+    const unsigned long long b = rowbits[min(rl + q, m - 1)];
+    sc[q] = row_scale(b, width);
+    if (b >= kInfBits || rl + q >= m) t1 |= 1u << q;
+  }
+  const bool special = __any(t1 != 0);
+  const int chunks = (k + 7) >> 3;
+  const int c0 = (int)blockIdx.y * cps, c1 = min(chunks, c0 + cps);
+  const bool wide = vec && row0 + ROWS <= m;   // uniform
+  v4i acc[RB][NT];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) acc[i][q] = v4f{0.f, 0.f, 0.f, 0.f};
-  bool t2 = false;
-  // the lane's 8 elements of quarter q of chunk ch
-  auto load8 = [&](int ch, int q, double (&x)[8]) {
-    const int l0 = ch * GV_K + 32 * q + kq;
+  for (int q = 0; q < RB; ++q)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int l = l0 + j;
-      x[j] = (!zero && l < k) ? arow[(size_t)l * lda] : 0.0;
-    }
-  };
-  for (int ch = c0; ch < c1; ++ch) {
-    __syncthreads();   // every wave is done with the previous chunk's fragments
-    const uint4* src = reinterpret_cast<const uint4*>(xf + (size_t)ch * fbytes);
-    for (int q = threadIdx.x; q < fbytes / 16; q += GV_NT) reinterpret_cast<uint4*>(xs)[q] = src[q];
-    __syncthreads();   // the fragments (and, at first, the tables) are in LDS
-#pragma unroll 1
-    for (int q = 0; q < 4; ++q) {
-      double xq[8], ah[8], al[8];
-      load8(ch, q, xq);
-      quantise8(xq, sc, tz, t2, ah, al);
+    for (int n = 0; n < NT; ++n) acc[q][n] = v4i{0, 0, 0, 0};
+  unsigned t2 = 0;
+  // columns beyond k are clamped (X's digits are zeros there)
+  auto load = [&](int c, double (&x)[2][RB], uint4& xr) {
 #pragma unroll
-      for (int i = 0; i < R; ++i) {
-        const int pb = c.pbase[i];
-        long p0, p1, p2;
-        if (i >= R - 6) {
-          planes8<true>(c, i, tab, ah, al, p0, p1, p2);
-          const long x0 = xfrag8(xs, pb, q, lane), x1 = xfrag8(xs, pb + 1, q, lane);
-          acc[i][0] = mfma16k32(p0, x0, acc[i][0]);
-          acc[i][1] = mfma16k32(p1, x0, acc[i][1]);
-          acc[i][1] = mfma16k32(p0, x1, acc[i][1]);
-        } else {
-          planes8<false>(c, i, tab, ah, al, p0, p1, p2);
-          const long x0 = xfrag8(xs, pb, q, lane), x1 = xfrag8(xs, pb + 1, q, lane),
-                     x2 = xfrag8(xs, pb + 2, q, lane);
-          acc[i][0] = mfma16k32(p2, x2, acc[i][0]);
-          acc[i][1] = mfma16k32(p0, x0, acc[i][1]);
-          acc[i][2] = mfma16k32(p1, x1, acc[i][2]);
+    for (int u = 0; u < 2; ++u) {
+      const double* p = A + (size_t)min(8 * c + 2 * g + u, k - 1) * lda;
+      if (wide) {
+#pragma unroll
+        for (int q = 0; q < RB; q += 2) {
+          const double2 v = *reinterpret_cast<const double2*>(p + rl + q);
+          x[u][q] = v.x;
+          x[u][q + 1] = v.y;
         }
-      }
-    }
-  }
-  if (t2 && !(atomicOr(flagsA + row, OZ2_T2) & (OZ2_T1 | OZ2_T2)) && !listed)
-    listA[atomicAdd(countA, 1)] = row;
-  // epilogue: lane L holds column L%16, rows 4(L/16) + e of the wave's 16;
-  // stored as [split][modulus][row block of 16][lane][4]
-  const size_t tile = (size_t)blockIdx.x * (GV_ROWS / 16) + w;
-#pragma unroll
-  for (int i = 0; i < R; ++i) {
-    const float fm = (float)c.m[i], inv = c.finv[i];
-    int16_t r4[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float v;
-      if (i >= R - 6) {
-        const float s = (float)c.sq[i];
-        v = red32(acc[i][0][e], fm, inv) + s * red32(acc[i][1][e], fm, inv);
       } else {
-        v = 16.0f * red32(acc[i][0][e], fm, inv) - 15.0f * red32(acc[i][1][e], fm, inv) +
-            240.0f * red32(acc[i][2][e], fm, inv);
+#pragma unroll
+        for (int q = 0; q < RB; ++q) x[u][q] = p[min(rl + q, m - 1)];
       }
-      r4[e] = (int16_t)(int)red32(v, fm, inv);
     }
-    int16_t* dst = part + (((size_t)split * R + i) * (mp / 16) + tile) * 256 + (size_t)lane * 4;
-    *reinterpret_cast<uint2*>(dst) =
-        make_uint2(((uint32_t)(uint16_t)r4[0]) | ((uint32_t)(uint16_t)r4[1] << 16),
-                   ((uint32_t)(uint16_t)r4[2]) | ((uint32_t)(uint16_t)r4[3] << 16));
+    xr = xd[(size_t)(c * 4 + g) * NRB + (i & (NRB - 1))];
+  };
+  const int wl = i / NRB;   // the lane's weight within a tile
+  double x[2][RB];
+  uint4 xr;
+  if (c0 + w < c1) load(c0 + w, x, xr);
+  for (int c = c0 + w; c < c1; c += 4) {
+    double xn[2][RB];
+    uint4 xrn = xr;
+    if (c + 4 < c1) load(c + 4, xn, xrn);
+    const bool tail = 8 * c + 8 > k;   // uniform
+    if (special || tail) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int q = 0; q < RB; ++q)
+          if (((t1 >> q) & 1) || 8 * c + 2 * g + u >= k) x[u][q] = 0.0;
+    }
+    v4i fa[RB];
+#pragma unroll
+    for (int q = 0; q < RB; ++q)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        bool z;
+        const uint64_t v = digits(x[u][q], sc[q], tz, z);
+        t2 |= z ? 1u << q : 0u;
+        fa[q][2 * u] = (int)(uint32_t)v;
+        fa[q][2 * u + 1] = (int)(uint32_t)(v >> 32);
+      }
+    const uint64_t r0 = ((uint64_t)xr.y << 32) | xr.x, r1 = ((uint64_t)xr.w << 32) | xr.z;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      // byte p of column (wt, b) is digit wt - p: the reversed digits (byte p
+      // holds digit 7 - p) moved down by 7 - wt bytes, up where negative
+      const int sh = 8 * (7 - n * PER - (NRB == 16 ? 0 : wl));
+      const int dn = max(sh, 0), up = max(-sh, 0) & 63;   // (a 16th weight is not used)
+      const uint64_t b0 = (r0 >> dn) << up, b1 = (r1 >> dn) << up;
+      const v4i fb{(int)(uint32_t)b0, (int)(uint32_t)(b0 >> 32), (int)(uint32_t)b1,
+                   (int)(uint32_t)(b1 >> 32)};
+#pragma unroll
+      for (int q = 0; q < RB; ++q)
+        acc[q][n] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[q], fb, acc[q][n], 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int q = 0; q < RB; ++q) x[u][q] = xn[u][q];
+    xr = xrn;
+  }
+  // flags and the fallback list: T1 rows once, T2 rows by the first to flag them
+#pragma unroll
+  for (int q = 0; q < RB; ++q) {
+    const int row = rl + q;
+    if (row >= m) continue;
+    const bool is1 = (t1 >> q) & 1;
+    const uint32_t f = is1 ? (g == 0 && w == 0 && blockIdx.y == 0 ? OZ2_T1 : 0u)
+                           : (((t2 >> q) & 1) ? OZ2_T2 : 0u);
+    if (f && !(atomicOr(flagsA + row, f) & (OZ2_T1 | OZ2_T2)) && !listed)
+      listA[atomicAdd(countA, 1)] = row;
+  }
+  // the four waves' sums in 64 bits; lane (g, i) holds column i of tile n, rows
+  // RB (4 g + e) + q
+#pragma unroll
+  for (int q = 0; q < RB; ++q)
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        atomicAdd(&sums[(RB * (4 * g + e) + q) * (NT * 16) + n * 16 + i],
+                  (unsigned long long)(long long)acc[q][n][e]);
+  __syncthreads();
+  for (int o = t; o < ROWS * NRB; o += GT) {
+    const int rr = o / NRB, b = o % NRB, row = row0 + rr;
+    if (row >= m || b >= nrhs) continue;
+    uint32_t v[NW];
+    carry<NW>(reinterpret_cast<const long long*>(sums) + rr * (NT * 16) + b, nweights, NRB, v);
+    if (gridDim.y == 1) {   // flagged entries are overwritten by the fallback
+      Y[(size_t)row + (size_t)b * ldy] = round_scaled<NW>(v, row_scale(rowbits[row], width) + tB[b]);
+    } else {
+      uint32_t* dst = part + (((size_t)blockIdx.y * mp + row) * NRB + b) * NW;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) dst[q] = v[q];
+    }
   }
 }
 
-// ---------------------------------------------------------------- reconstruction
-template <int R, int I>
-struct GvOut {
-  __device__ __forceinline__ static void run(const Oz2Const& c, const uint4 (&x)[R], int row0, int b,
-                                             int m, int nrhs, const int32_t* __restrict__ sA,
-                                             const int32_t* __restrict__ tB,
-                                             const uint32_t* __restrict__ fA,
-                                             const uint32_t* __restrict__ fB, bool nofb,
-                                             double* Y, int ldy) {
-    const int row = row0 + I;
-    if (row < m && b < nrhs && (nofb || !((fA[row] | fB[b]) & (OZ2_T1 | OZ2_T2)))) {
-      const int e = sA[row] + tB[b];
-      double v;
-      v = crt38_rounded<R, I>(c, x, e);
-      Y[(size_t)row + (size_t)b * ldy] = v;
-    }
-    GvOut<R, I + 1>::run(c, x, row0, b, m, nrhs, sA, tB, fA, fB, nofb, Y, ldy);
-  }
-};
-template <int R>
-struct GvOut<R, 4> {
-  __device__ __forceinline__ static void run(const Oz2Const&, const uint4 (&)[R], int, int, int, int,
-                                             const int32_t*, const int32_t*, const uint32_t*,
-                                             const uint32_t*, bool, double*, int) {}
-};
-
-// thread (row block of 16, lane): the 4 outputs of rows 4(L/16) + e, column
-// L%16; the splits' representatives are summed and centred exactly
-template <int R>
+// the splits' integers summed and rounded once
+template <int NW>
 __global__ void __launch_bounds__(256)
-k_gemv_crt(Oz2Const c, const int16_t* __restrict__ part, int splits, int mp, int m, int nrhs,
-           const int32_t* __restrict__ sA, const int32_t* __restrict__ tB,
-           const uint32_t* __restrict__ fA, const uint32_t* __restrict__ fB, int nofb, double* Y,
+k_gemv_sum(const uint32_t* __restrict__ part, int splits, int mp, int nrb, int m, int nrhs, int width,
+           const unsigned long long* __restrict__ rowbits, const int32_t* __restrict__ tB, double* Y,
            int ldy) {
-  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t tiles = (size_t)mp / 16;
-  if (t >= tiles * 64) return;
-  const size_t tile = t >> 6;
-  const int lane = (int)(t & 63);
-  uint4 x[R];
+  const size_t o = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int row = (int)(o / nrb), b = (int)(o % nrb);
+  if (row >= m || b >= nrhs) return;
+  uint32_t v[NW];
 #pragma unroll
-  for (int i = 0; i < R; ++i) {
-    int s4[4] = {0, 0, 0, 0};
-    for (int sp = 0; sp < splits; ++sp) {
-      const uint2 v = *reinterpret_cast<const uint2*>(
-          part + (((size_t)sp * R + i) * tiles + tile) * 256 + (size_t)lane * 4);
-      s4[0] += (int16_t)(v.x & 0xFFFFu);
-      s4[1] += (int16_t)(v.x >> 16);
-      s4[2] += (int16_t)(v.y & 0xFFFFu);
-      s4[3] += (int16_t)(v.y >> 16);
-    }
-    const int mi = c.m[i];
-    uint32_t h[4];
+  for (int q = 0; q < NW; ++q) v[q] = 0;
+  for (int s = 0; s < splits; ++s) {
+    const uint32_t* p = part + (((size_t)s * mp + row) * nrb + b) * NW;
+    uint64_t cy = 0;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      int r = s4[e] % mi;
-      r += r < 0 ? mi : 0;
-      r -= r >= ((mi + 1) >> 1) ? mi : 0;   // centred: [-floor(m/2), ceil(m/2) - 1]
-      h[e] = (uint32_t)(uint16_t)(int16_t)r;
+    for (int q = 0; q < NW; ++q) {
+      cy += (uint64_t)v[q] + p[q];
+      v[q] = (uint32_t)cy;
+      cy >>= 32;
     }
-    x[i] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), 0u, 0u);
   }
-  GvOut<R, 0>::run(c, x, (int)tile * 16 + 4 * (lane >> 4), lane & 15, m, nrhs, sA, tB, fA, fB,
-                   nofb != 0, Y, ldy);
+  Y[(size_t)row + (size_t)b * ldy] = round_scaled<NW>(v, row_scale(rowbits[row], width) + tB[b]);
 }
 
-template <int R>
-hipError_t launch_gemv_r(const Oz2Const& c, const double* A, int lda, int m, int k, int chunks,
-                         int cps, int splits, const int32_t* sA, uint32_t* flagsA, int* countA,
-                         int* listA, int listed, const uint8_t* xf, const uint32_t* tab,
-                         unsigned tz, int16_t* part, int mp, hipStream_t s) {
-  const size_t lds = (size_t)((c.tabsz + 3) & ~3) * 4 + (size_t)c.P * GV_FRAG;
-  (void)hipFuncSetAttribute((const void*)k_gemv<R>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds);
-  hipLaunchKernelGGL(k_gemv<R>, dim3(mp / GV_ROWS, splits), dim3(GV_NT), lds, s, c, A, lda, m, k,
-                     chunks, cps, sA, flagsA, countA, listA, listed, xf, tab, tz, part, mp);
+struct GemvArgs {
+  const double* A;
+  int lda, m, k, nrhs, splits, widthA, nweights, mp, listed, ldy;
+  unsigned tz;
+  const unsigned long long* rowbits;
+  uint32_t* flagsA;
+  int* countA;
+  int* listA;
+  const uint4* xd;
+  const int32_t* tB;
+  uint32_t* part;
+  double* Y;
+};
+
+template <int NRB, int NT, int RB, int NW>
+hipError_t launch_product(const GemvArgs& a, hipStream_t s) {
+  const int chunks = (a.k + 7) / 8, cps = (chunks + a.splits - 1) / a.splits;
+  const unsigned vec = ((uintptr_t)a.A % 16 == 0 && a.lda % 2 == 0) ? 1u : 0u;
+  hipLaunchKernelGGL((k_gemv<NRB, NT, RB, NW>), dim3((a.m + 16 * RB - 1) / (16 * RB), a.splits),
+                     dim3(GT), 0, s, a.A, a.lda, a.m, a.k, cps, a.widthA, vec, a.tz, a.nweights,
+                     a.rowbits, a.flagsA, a.countA, a.listA, a.listed, a.xd, a.nrhs, a.tB, a.part,
+                     a.mp, a.Y, a.ldy);
   return hipGetLastError();
 }
 
-template <int R>
-hipError_t launch_gemv_crt_r(const Oz2Const& c, const int16_t* part, int splits, int mp, int m,
-                             int nrhs, const int32_t* sA, const int32_t* tB, const uint32_t* fA,
-                             const uint32_t* fB, int nofb, double* Y, int ldy, hipStream_t s) {
-  const size_t threads = (size_t)mp / 16 * 64;
-  hipLaunchKernelGGL(k_gemv_crt<R>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, c,
-                     part, splits, mp, m, nrhs, sA, tB, fA, fB, nofb, Y, ldy);
-  return hipGetLastError();
+// tiles for 2 D - 1 <= 9, 13, 15 weights
+template <int NW>
+hipError_t launch_columns(int nrb, const GemvArgs& a, hipStream_t s) {
+  const int w = a.nweights;
+  switch (nrb) {
+    case 1: return launch_product<1, 1, 4, NW>(a, s);
+    case 2: return launch_product<2, 2, 4, NW>(a, s);
+    case 4: return launch_product<4, 4, 4, NW>(a, s);
+    case 8:
+      return w <= 10 ? launch_product<8, 5, 4, NW>(a, s)
+           : w <= 14 ? launch_product<8, 7, 4, NW>(a, s) : launch_product<8, 8, 4, NW>(a, s);
+    default:
+      return w <= 9 ? launch_product<16, 9, 2, NW>(a, s)
+           : w <= 13 ? launch_product<16, 13, 2, NW>(a, s) : launch_product<16, 15, 2, NW>(a, s);
+  }
 }
 
 }  // namespace
 
-hipError_t oz2_launch_gemv_xplanes(const Oz2Const& c, const double* X, int ldx, int k, int nrhs,
-                                   const int32_t* tB, uint32_t* flagsB, int* countB, int* listB,
-                                   int listed, const uint32_t* tab, unsigned tz, uint8_t* xf,
-                                   hipStream_t s) {
-  const int chunks = (k + GV_K - 1) / GV_K;
-  const int threads = chunks * 64;
-  hipLaunchKernelGGL(k_gemv_xplanes, dim3((threads + 255) / 256), dim3(256), 0, s, c, X, ldx, k,
-                     nrhs, chunks, tB, flagsB, countB, listB, listed, tab, tz, xf);
-  return hipGetLastError();
+// columns of X rounded up to a power of two
+static int gemv_columns(int nrhs) {
+  int b = 1;
+  while (b < nrhs) b *= 2;
+  return b;
 }
 
-#define OZ2_GV_SWITCH(FN, ...)                      \
-  switch (c.r) {                                    \
-    case 8: return FN<8>(__VA_ARGS__);              \
-    case 9: return FN<9>(__VA_ARGS__);              \
-    case 10: return FN<10>(__VA_ARGS__);            \
-    case 11: return FN<11>(__VA_ARGS__);            \
-    case 12: return FN<12>(__VA_ARGS__);            \
-    case 13: return FN<13>(__VA_ARGS__);            \
-    case 14: return FN<14>(__VA_ARGS__);            \
-    case 15: return FN<15>(__VA_ARGS__);            \
-    case 16: return FN<16>(__VA_ARGS__);            \
-    default: return hipErrorInvalidValue;           \
+hipError_t oz2_launch_gemv(const Oz2Const& c, const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
+                           const double* A, int lda, const double* X, int ldx, double* Y, int ldy,
+                           int splits, bool reuse, hipStream_t s) {
+  const int nrb = gemv_columns(d.n);
+  const int force = (d.flags & 16u) ? 1 : 0;     // OZ2_FORCE_FALLBACK
+  const unsigned tz = (d.flags & 4u) ? 1u : 0u;   // OZ2_QUANT_TZ
+  // the fixed rule: ceil(log2(256 k)) halved (rounded up) off each budget
+  int ell = 0;
+  while ((1ull << ell) < 256ull * (unsigned long long)d.k) ++ell;
+  const int wa = std::min(62, c.cA - ((ell + 1) >> 1)), wb = std::min(62, c.cB - ((ell + 1) >> 1));
+  // |a| <= 2^w takes D balanced base-256 digits: 2^w <= 127/255 256^D
+  const int da = (wa + 9) / 8, db = (wb + 9) / 8;
+  auto* rowbits = (unsigned long long*)(ws + L.rowbits);
+  auto* flagsA = (uint32_t*)(ws + L.flagsA);
+  auto* counters = (int*)(ws + L.counters);
+  auto* listA = (int*)(ws + L.listA);
+  auto* tB = (int32_t*)(ws + L.tB);
+  hipLaunchKernelGGL(k_gemv_init, dim3((d.mp + 255) / 256), dim3(256), 0, s, rowbits, flagsA, d.mp,
+                     d.m, counters, listA, reuse ? 1 : 0, force);
+  // rows: 512 per workgroup; k chunks sized for at most about 4096 workgroups
+  const int gx = (d.m + 511) / 512;
+  int kchunk = 32;
+  while ((long long)gx * ((d.k + kchunk - 1) / kchunk) > 4096 && kchunk < 4096) kchunk *= 2;
+  const int gy = (d.k + kchunk - 1) / kchunk;
+  const unsigned vec = ((uintptr_t)A % 16 == 0 && lda % 2 == 0) ? 1u : 0u;
+  hipLaunchKernelGGL(k_gemv_scan, dim3((unsigned)(nrb + (reuse ? 0 : gx * gy))), dim3(256), 0, s, A, lda,
+                     d.m, d.k, kchunk, vec, gx, rowbits, X, ldx, d.n, nrb, d.kp, wb, tz, force, tB,
+                     (uint32_t*)(ws + L.flagsB), counters + 1, (int*)(ws + L.listB),
+                     (uint64_t*)(ws + L.xfrag));
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const GemvArgs a{A, lda, d.m, d.k, d.n, splits, wa, da + db - 1, d.mp, force, ldy, tz, rowbits,
+                   flagsA, counters, listA, (const uint4*)(ws + L.xfrag), tB,
+                   (uint32_t*)(ws + L.part), Y};
+  const unsigned blocks = (unsigned)(((size_t)d.m * nrb + 255) / 256);
+#define OZ2_GV_WORDS(NW)                                                                          \
+  {                                                                                               \
+    e = launch_columns<NW>(nrb, a, s);                                                            \
+    if (e == hipSuccess && splits > 1) {                                                          \
+      hipLaunchKernelGGL(k_gemv_sum<NW>, dim3(blocks), dim3(256), 0, s, a.part, splits, d.mp, nrb, \
+                         d.m, d.n, wa, rowbits, tB, Y, ldy);                                      \
+      e = hipGetLastError();                                                                      \
+    }                                                                                             \
   }
-
-hipError_t oz2_launch_gemv(const Oz2Const& c, const double* A, int lda, int m, int k, int splits,
-                           const int32_t* sA, uint32_t* flagsA, int* countA, int* listA,
-                           int listed, const uint8_t* xf, const uint32_t* tab, unsigned tz,
-                           int16_t* part, int mp, hipStream_t s) {
-  const int chunks = (k + GV_K - 1) / GV_K;
-  const int cps = (chunks + splits - 1) / splits;
-  OZ2_GV_SWITCH(launch_gemv_r, c, A, lda, m, k, chunks, cps, splits, sA, flagsA, countA, listA,
-                listed, xf, tab, tz, part, mp, s)
-}
-
-hipError_t oz2_launch_gemv_crt(const Oz2Const& c, const int16_t* part, int splits, int mp, int m,
-                               int nrhs, const int32_t* sA, const int32_t* tB, const uint32_t* fA,
-                               const uint32_t* fB, int nofb, double* Y, int ldy, hipStream_t s) {
-  OZ2_GV_SWITCH(launch_gemv_crt_r, c, part, splits, mp, m, nrhs, sA, tB, fA, fB, nofb, Y, ldy, s)
+  if (c.nw == 3) OZ2_GV_WORDS(3) else if (c.nw == 4) OZ2_GV_WORDS(4) else OZ2_GV_WORDS(5)
+  return e;
 }

@@ -28,6 +28,42 @@ __device__ __forceinline__ int exp_of_bits(unsigned long long b) {
   return (64 - __clzll((long long)b)) - 1074;
 }
 
+// rows of a column-major matrix, block (bx, by): lanes along the (contiguous)
+// row index, two rows per thread (16-byte loads when the caller has checked
+// the alignment), eight loads in flight; k chunk by, combined with atomicMax.
+__device__ __forceinline__ void scan_rows_block(const double* __restrict__ A, int lda, int m, int k,
+                                                int kchunk, unsigned vec,
+                                                unsigned long long* rowbits, int bx, int by) {
+  const int i = 2 * (bx * 256 + threadIdx.x);
+  if (i >= m) return;
+  const int l0 = by * kchunk;
+  const int l1 = min(k, l0 + kchunk);
+  const bool pair = vec && i + 1 < m;
+  unsigned long long m0 = 0, m1 = 0;
+  int l = l0;
+  if (pair) {
+    const double* p = A + i + (size_t)l0 * lda;
+    for (; l + 8 <= l1; l += 8) {
+      double2 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const double2*>(p + (size_t)u * lda);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        m0 = max(m0, abs_bits(v[u].x));
+        m1 = max(m1, abs_bits(v[u].y));
+      }
+      p += 8 * (size_t)lda;
+    }
+  }
+  for (; l < l1; ++l) {
+    const double* p = A + i + (size_t)l * lda;
+    m0 = max(m0, abs_bits(p[0]));
+    if (i + 1 < m) m1 = max(m1, abs_bits(p[1]));
+  }
+  atomicMax(rowbits + i, m0);
+  if (i + 1 < m) atomicMax(rowbits + i + 1, m1);
+}
+
 // 4-bit magnitude code c = ceil(16 |x| 2^-E), 0 iff x == 0, else in [1, 16].
 // |x| < 2^E so c <= 16; the scaled value is exact whenever it is >= 1.
 __device__ __forceinline__ float code_of(double x, int E) {
