@@ -930,17 +930,8 @@ int ozaki2_dgemm_strided_batched(int m, int n, int k, const double* A, int lda, 
     if (!make_const(num_moduli, c)) return OZ2_E_INVALID;
     st = device_ok();
     if (st != OZ2_OK) return st;
-    std::lock_guard<std::mutex> g(g_pool_mu);
-    void* ws = nullptr;
-    st = pool_get(align256((size_t)c.tabsz * 4), &ws);
-    if (st != OZ2_OK) return st;
-    Oz2Layout L{};
-    L.tabs = 0;
-    hipStream_t s = (hipStream_t)stream;
-    hipError_t e = oz2_launch_tables(L, c, (uint8_t*)ws, s);
-    if (e == hipSuccess)
-      e = oz2_launch_batched(c, m, n, k, batch, A, lda, strideA, B, ldb, strideB, C, ldc, strideC,
-                             (const uint32_t*)ws, nullptr, s);
+    const hipError_t e = oz2_launch_batched(c, m, n, k, batch, A, lda, strideA, B, ldb, strideB, C,
+                                            ldc, strideC, nullptr, (hipStream_t)stream);
     return e == hipSuccess ? OZ2_OK : OZ2_E_DEVICE;
   }
   for (int b = 1; b < batch; ++b) {   // each problem's C apart from its own A and B
@@ -1216,18 +1207,9 @@ int ozaki2_probe_batched_integers(int m, int n, int k, const double* A, int lda,
   if (!A || !B || !words) return OZ2_E_INVALID;
   int st = device_ok();
   if (st != OZ2_OK) return st;
-  std::lock_guard<std::mutex> g(g_pool_mu);
-  void* ws = nullptr;
-  st = pool_get(align256((size_t)c.tabsz * 4), &ws);
-  if (st != OZ2_OK) return st;
-  Oz2Layout L{};
-  L.tabs = 0;
-  hipStream_t s = (hipStream_t)stream;
-  hipError_t e = oz2_launch_tables(L, c, (uint8_t*)ws, s);
   // C is not written on this path (the kernel writes the integers instead)
-  if (e == hipSuccess)
-    e = oz2_launch_batched(c, m, n, k, batch, A, lda, strideA, B, ldb, strideB, nullptr, m, 0,
-                           (const uint32_t*)ws, (uint32_t*)words, s);
+  const hipError_t e = oz2_launch_batched(c, m, n, k, batch, A, lda, strideA, B, ldb, strideB, nullptr,
+                                          m, 0, (uint32_t*)words, (hipStream_t)stream);
   return hip_status(e);
 }
 

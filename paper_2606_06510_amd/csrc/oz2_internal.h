@@ -201,14 +201,12 @@ hipError_t oz2_launch_bytegemm(const Oz2Dims& d, const Oz2Layout& L, const Oz2By
 hipError_t oz2_launch_byte_crt(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
                                const double* A, int lda, double* C, int ldc, const Oz2Batch& bt,
                                hipStream_t s);
-// all of Alg. 1 for `batch` problems of m, n, k <= 64 in one launch; tab = the
-// residue -> plane-byte tables (oz2_launch_tables); iout (normally null, a
-// diagnostic): write the exact integers of the unflagged outputs there,
-// uint32 [batch][n][m][5], instead of C
+// all of Alg. 1 for `batch` problems of m, n, k <= 64 in one launch; iout
+// (normally null, a diagnostic): write the exact integers of the unflagged
+// outputs there, uint32 [batch][n][m][5], instead of C
 hipError_t oz2_launch_batched(const Oz2Const& c, int m, int n, int k, int batch, const double* A,
                               int lda, long long sA, const double* B, int ldb, long long sB,
-                              double* C, int ldc, long long sC, const uint32_t* tab, uint32_t* iout,
-                              hipStream_t s);
+                              double* C, int ldc, long long sC, uint32_t* iout, hipStream_t s);
 
 // ---------------------------------------------------------------- digit rule
 // Digit planes of a centred residue d of m (the E4M3-exact layouts of the

@@ -108,3 +108,35 @@ def test_batches_side_by_side(case):
     for i in range(b):
         D = oz.matmul(A[i, :k, :m].t(), B[i, :, :k].t(), r)
         assert torch.equal(C[i, :n, :m].t(), D), i
+
+
+@pytest.mark.parametrize("m,n,k", [(64, 64, 64), (1, 1, 1), (17, 64, 3), (64, 15, 33), (50, 49, 64)])
+@pytest.mark.parametrize("r", [8, 11, 12, 13, 16])
+def test_small_batches_digit_counts(m, n, k, r):
+    """the single-launch kernel (six, seven or eight digits by the widest
+    entry of a problem) against the byte-residue route, problem by problem:
+    full-mantissa entries, powers of two next to their neighbours, one
+    nonzero per row (the widest scales), unaligned leading dimensions"""
+    import paper_2606_06510_amd as oz
+    import torch
+    dev = device()
+    rng = np.random.default_rng(r + m)
+    A = rng.random((4, k, m)) - 0.5
+    B = rng.random((4, n, k)) - 0.5
+    v = np.array([1.0, -1.0, 1 - 2.0 ** -53, -(1 - 2.0 ** -53), 0.5, 2.0 ** -40])
+    A[1], B[1] = np.resize(v, (k, m)), np.resize(v[::-1], (n, k))
+    A[2] *= np.arange(k)[:, None] == np.arange(m)[None, :] % k
+    B[2] *= np.arange(k)[None, :] == np.arange(n)[:, None] % k
+    A[3], B[3] = np.abs(A[3]) + 1, -np.abs(B[3]) - 1
+    for pad in (0, 1):
+        Ap, Bp = np.zeros((4, k, m + pad)), np.zeros((4, n, k + pad))
+        Ap[:, :, :m], Bp[:, :, :k] = A, B
+        Ad, Bd = torch.from_numpy(Ap).to(dev), torch.from_numpy(Bp).to(dev)
+        C = torch.full((4, n, m + pad), 7.0, dtype=torch.float64, device=dev)
+        oz.ozaki2_dgemm_strided_batched(m, n, k, Ad, m + pad, Ad.stride(0), Bd, k + pad, Bd.stride(0),
+                                        C, m + pad, C.stride(0), 4, r)
+        torch.cuda.synchronize()
+        assert torch.all(C[:, :, m:] == 7.0)
+        for i in range(4):
+            D = oz.matmul(Ad[i, :, :m].t(), Bd[i, :, :k].t(), r)
+            assert torch.equal(C[i, :, :m].t(), D), (i, pad)
