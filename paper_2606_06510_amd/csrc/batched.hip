@@ -39,13 +39,13 @@ struct Smem {
 };
 
 __device__ __forceinline__ uint8_t* spot(uint8_t (*pl)[64], int row, int ch) {   // ch: multiple of 8
-  return pl[row] + 16 * ((ch >> 4) ^ swz(row & 15)) + (ch & 8);
+  return pl[row] + 16 * ((ch >> 4) ^ swz16(row & 15)) + (ch & 8);
 }
 
 // fragment: rows base + L%16, k 16 (L/16) .. +15
 __device__ __forceinline__ v4i frag(const uint8_t (*pl)[64], int base, int lane) {
   const int r = lane & 15;
-  const uint4 v = *reinterpret_cast<const uint4*>(pl[base + r] + 16 * ((lane >> 4) ^ swz(r)));
+  const uint4 v = *reinterpret_cast<const uint4*>(pl[base + r] + 16 * ((lane >> 4) ^ swz16(r)));
   return v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w};
 }
 

@@ -180,7 +180,7 @@ k_bytegemm(Oz2Byte c, const uint8_t* __restrict__ PA, const uint8_t* __restrict_
   Stream d;
   {
     const int rb = lane >> 2;
-    d.vo = (uint32_t)(rb * KS + 16 * ((lane & 3) ^ swz(rb))) + (uint32_t)w * 1024u;
+    d.vo = (uint32_t)(rb * KS + 16 * ((lane & 3) ^ swz16(rb))) + (uint32_t)w * 1024u;
     d.mw = (uint32_t)w * 1024u;
     const size_t z = (size_t)blockIdx.z * wsz;
     d.pa = PA + z + (size_t)tm * BT * KS + (size_t)mi0 * nk * kbA;
@@ -195,7 +195,7 @@ k_bytegemm(Oz2Byte c, const uint8_t* __restrict__ PA, const uint8_t* __restrict_
   if (g) bar();
 
   const int wr = w >> 2, wc = w & 3;
-  const int fo = (lane & 15) * KS + 16 * ((lane >> 4) ^ swz(lane & 15));
+  const int fo = (lane & 15) * KS + 16 * ((lane >> 4) ^ swz16(lane & 15));
   const uint8_t* fa0 = LB + wr * 128 * KS + fo;
   const uint8_t* fb0 = LB + BOP + wc * 64 * KS + fo;
   // first unit of the wave's outputs: column block 4 wc (of 16 columns), row block 2 wr (of 64)
@@ -275,7 +275,7 @@ k_bytegemm128(Oz2Byte c, const uint8_t* __restrict__ PA, const uint8_t* __restri
   Stream d;
   {
     const int rb = lane >> 2;
-    d.vo = (uint32_t)(rb * KS + 16 * ((lane & 3) ^ swz(rb))) + (uint32_t)w * 1024u;
+    d.vo = (uint32_t)(rb * KS + 16 * ((lane & 3) ^ swz16(rb))) + (uint32_t)w * 1024u;
     d.mw = (uint32_t)w * 1024u;
     const size_t z = (size_t)blockIdx.z * wsz;
     d.pa = PA + z + (size_t)tm * ST * KS + (size_t)mi * T * kbA;
@@ -286,7 +286,7 @@ k_bytegemm128(Oz2Byte c, const uint8_t* __restrict__ PA, const uint8_t* __restri
   for (int t = 0; t < SNB - 1; ++t)
     if (t < T) small_issue(d, kbA, kbB, lds0 + t * SST);
   const int wr = w >> 1, wc = w & 1;
-  const int fo = (lane & 15) * KS + 16 * ((lane >> 4) ^ swz(lane & 15));
+  const int fo = (lane & 15) * KS + 16 * ((lane >> 4) ^ swz16(lane & 15));
   const uint8_t* fa0 = LB + wr * 64 * KS + fo;
   const uint8_t* fb0 = LB + SOP + wc * 64 * KS + fo;
   const size_t cbs = (size_t)(mp / 64) * 1024;

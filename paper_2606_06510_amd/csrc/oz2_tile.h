@@ -24,6 +24,13 @@ __device__ __forceinline__ void wait_vm() {
 // chunk swizzle of LDS row r: conflict free for 16 consecutive rows
 __device__ __forceinline__ int swz(int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); }
 
+// The same for fragments of 16 rows x 64 k bytes (lane L: row L%16, chunk L/16):
+// a 16-byte LDS read serves lanes 0-3, 12-15 and 20-27 together (likewise the
+// complements), rows 0-3, 12-15 of one chunk and 4-11 of the next; the swizzle
+// of 32-row fragments above is two-way conflicted there (four extra cycles
+// per read, the matrix unit busy 60% of the cycles at 4096^3).
+__device__ __forceinline__ int swz16(int r) { return (-(r >> 2)) & 3; }
+
 // global_load_lds_dwordx4: lane L's 16 bytes land at M0 + 16 L.  The sc1
 // cache policy (streaming operands with no reuse inside the CU's vector L1)
 // measured 10-12% faster than the default policy on the 4096^3 residue GEMMs.
