@@ -253,7 +253,27 @@ bool build_byte(const Big& M, Oz2Byte& b) {
         }
     }
     for (int l = 0; l < 4; ++l) b.W38[i][l] = (double)wl[l];
+    if (b.n <= 15) {
+      // W_i (or W_i - M8) as bytes, two's complement over 16 bytes, then balanced
+      // digits in [-128, 127] with carries; exact below 2^127 in magnitude
+      int carry = 0, borrow = 0;
+      for (int r = 0; r < 16; ++r) {
+        int v = (int)((Wi.word(r / 4) >> (8 * (r & 3))) & 0xFF);
+        if (2 * inv > m) {
+          v -= (int)((M8.word(r / 4) >> (8 * (r & 3))) & 0xFF) + borrow;
+          borrow = v < 0;
+          v &= 0xFF;
+        }
+        v += carry;
+        carry = v >= 128;
+        v -= 256 * carry;
+        b.wb[r][i / 4] = (int)((uint32_t)b.wb[r][i / 4] | ((uint32_t)(v & 0xFF) << (8 * (i & 3))));
+        b.woff[r] += 128 * v;
+      }
+    }
   }
+  for (int l = 0; l < 4; ++l) b.M32[l] = (double)M8.word(l);
+  b.mtop32 = std::ldexp(1.0, 96) / big_double(M8);
   return true;
 }
 
@@ -604,6 +624,12 @@ int run_bytes(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c, const Oz2
   if (codes && e == hipSuccess) e = oz2_launch_codegemm(d, L, ws, bt, s);
   if (e == hipSuccess) e = oz2_launch_scales(d, L, c, ws, both, bt, s);
   if (e == hipSuccess) e = oz2_launch_byte_split(d, L, b, ws, A, lda, B, ldb, bt, s);
+  if (bt.count == 1 && oz2_byte_fused_fits(d, b)) {
+    if (e == hipSuccess) e = oz2_launch_byte_fused(d, L, b, ws, C, ldc, s);
+    if (e == hipSuccess && !(d.flags & OZ2_NO_FALLBACK))
+      e = oz2_launch_fallback_direct(d, L, ws, A, lda, B, ldb, C, ldc, s);
+    return hip_status(e);
+  }
   if (e == hipSuccess) e = oz2_launch_bytegemm(d, L, b, ws, bt, s);
   if (e == hipSuccess) e = oz2_launch_byte_crt(d, L, b, ws, A, lda, C, ldc, bt, s);
   if (e == hipSuccess && !(d.flags & OZ2_NO_FALLBACK))

@@ -81,6 +81,12 @@ struct Oz2Byte {
   double W38[OZ2_MAXB][4];
   double M38[4];
   double mtop;                    // 2^(38 (limbs - 1)) / M8, limbs = 3 for n <= 15, else 4
+  // n <= 15 (the fused kernel): the same W_i as 16 balanced base-256 digits, digit
+  // r of W_i in byte i of row r; their sums times 128; M8 in radix-2^32 limbs
+  int wb[16][4];
+  int woff[16];
+  double M32[4];
+  double mtop32;                  // 2^96 / M8
 };
 
 // Problems of a batch in the z dimension of a grid: elements between their
@@ -201,6 +207,11 @@ hipError_t oz2_launch_bytegemm(const Oz2Dims& d, const Oz2Layout& L, const Oz2By
 hipError_t oz2_launch_byte_crt(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
                                const double* A, int lda, double* C, int ldc, const Oz2Batch& bt,
                                hipStream_t s);
+// the products and the reconstruction in one kernel, where that is the faster
+// route (short k: see the definition); the fallback then reads A directly
+bool oz2_byte_fused_fits(const Oz2Dims& d, const Oz2Byte& c);
+hipError_t oz2_launch_byte_fused(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
+                                 double* C, int ldc, hipStream_t s);
 // all of Alg. 1 for `batch` problems of m, n, k <= 64 in one launch; iout
 // (normally null, a diagnostic): write the exact integers of the unflagged
 // outputs there, uint32 [batch][n][m][5], instead of C

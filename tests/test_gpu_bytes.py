@@ -140,3 +140,35 @@ def test_small_batches_digit_counts(m, n, k, r):
         for i in range(4):
             D = oz.matmul(Ad[i, :, :m].t(), Bd[i, :, :k].t(), r)
             assert torch.equal(C[i, :, :m].t(), D), (i, pad)
+
+
+# the fused products and reconstruction (k <= 256, tiles that fill the chip):
+# ragged edges of the 128 x 128 tiles, several turns of a workgroup, one to
+# four K-stages, odd leading dimensions, fallback entries beside C_in
+@pytest.mark.parametrize("m,n,k,r,pad,flags", [(2040, 1801, 70, 12, 0, 0), (1793, 2047, 256, 11, 1, 1),
+                                               (4300, 4100, 17, 10, 0, 1), (2047, 2047, 190, 12, 3, 9),
+                                               (2048, 2048, 129, 12, 0, 16)])
+def test_fused_short_k(m, n, k, r, pad, flags):
+    def edit(A, B):
+        A[m // 2, ::2] *= 1e200     # T2
+        A[m - 1, 1] = np.nan        # T1
+        B[2, n - 1] = np.inf
+        A[5] = 0.0
+        A[40:60] = np.round(A[40:60] * 4)    # few significant bits, exact zeros
+        B[:, 100:120] = np.round(B[:, 100:120] * 4)
+    _same(*_both(m, n, k, r, flags=flags, seed=k, pad=pad, edit=edit))
+
+
+def test_fused_short_k_subnormal_and_small_integers():
+    """results around and below the smallest normal number, in some rows and
+    columns only (the words' rounding), and integers of few bits"""
+    def edit(A, B):
+        A[:300] *= 2.0 ** -540
+        B[:, :400] *= 2.0 ** -482
+        B[:, 100:200] *= 2.0 ** -33
+        A[300:420] = np.sign(A[300:420])
+        B[:, 400:500] = np.sign(B[:, 400:500])
+    x, y = _both(2050, 1900, 60, 12, seed=1, edit=edit)
+    _same(x, y)
+    small = np.abs(x[:300, :400])
+    assert np.count_nonzero(small < 2.0 ** -1022) > 1000 and np.count_nonzero(small >= 2.0 ** -1022) > 100
