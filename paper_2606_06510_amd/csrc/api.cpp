@@ -197,7 +197,7 @@ bool build_const(int r, Oz2Const& c) {
 const int kByteModuli[OZ2_MAXB] = {256, 255, 253, 251, 247, 241, 239, 233, 229, 227,
                                    223, 217, 211, 199, 197, 193, 191, 181, 179};
 
-// 2^-k * floor-ish value of a big integer as a double (for ratios only)
+// a big integer as a double (for ratios only)
 double big_double(const Big& b) {
   double v = 0.0;
   for (size_t i = b.w.size(); i-- > 0;) v = v * 4294967296.0 + (double)b.w[i];
@@ -589,11 +589,9 @@ int run_deconstruct(ozaki2_plan_s& p, int side, hipStream_t s) {
   p.recorded = 0;
   hipError_t e = mark(p, 0, s);
   if (e == hipSuccess) e = oz2_launch_init(d, p.L, p.ws, side, kOne, s);
-  for (int one : {OZ2_SIDE_A, OZ2_SIDE_B}) {
-    if (!(side & one) || e != hipSuccess) continue;
-    e = codes ? oz2_launch_scan_codes(d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, one, kOne, s)
-              : oz2_launch_scan(d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, one, kOne, s);
-  }
+  if (e == hipSuccess)   // (codes: both sides, always)
+    e = codes ? oz2_launch_scan_codes(d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, kOne, s)
+              : oz2_launch_scan(d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, side, kOne, s);
   if (codes && e == hipSuccess) e = oz2_launch_rebase(d, p.L, p.ws, side, kOne, s);
   if (e == hipSuccess) e = mark(p, 1, s);
   if (codes && e == hipSuccess) e = oz2_launch_codegemm(d, p.L, p.ws, kOne, s);
@@ -618,12 +616,11 @@ int run_bytes(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c, const Oz2
   const int both = OZ2_SIDE_A | OZ2_SIDE_B;
   hipError_t e = oz2_launch_init(d, L, ws, both, bt, s);
   if (e == hipSuccess)
-    e = codes ? oz2_launch_scan_codes(d, L, ws, A, lda, B, ldb, both, bt, s)
+    e = codes ? oz2_launch_scan_codes(d, L, ws, A, lda, B, ldb, bt, s)
               : oz2_launch_scan(d, L, ws, A, lda, B, ldb, both, bt, s);
   if (codes && e == hipSuccess) e = oz2_launch_rebase(d, L, ws, both, bt, s);
   if (codes && e == hipSuccess) e = oz2_launch_codegemm(d, L, ws, bt, s);
-  if (e == hipSuccess) e = oz2_launch_scales(d, L, c, ws, both, bt, s);
-  if (e == hipSuccess) e = oz2_launch_byte_split(d, L, b, ws, A, lda, B, ldb, bt, s);
+  if (e == hipSuccess) e = oz2_launch_byte_split(d, L, c, b, ws, A, lda, B, ldb, bt, s);
   if (bt.count == 1 && oz2_byte_fused_fits(d, b)) {
     if (e == hipSuccess) e = oz2_launch_byte_fused(d, L, b, ws, C, ldc, s);
     if (e == hipSuccess && !(d.flags & OZ2_NO_FALLBACK))

@@ -3,6 +3,8 @@
 // products (bytegemm.hip is the GEMM between them; Oz2Byte the residue
 // system).  The quantised integers A~, B~ (Eq. (scale)), the flags and the
 // integer C~ are those of the plane route, so C is the same bit for bit.
+#include <algorithm>
+
 #include "oz2_device.h"
 
 namespace {
@@ -13,7 +15,10 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 // ---------------------------------------------------------------- split
 // One workgroup of 256 threads per 64 x 64 tile: thread t quantises row t/4,
 // k 16 (t%4) .. +15, and writes its 16 bytes of every modulus's plane (1 KiB
-// contiguous per wave store).
+// contiguous per wave store).  The row's scale (Eq. (scale)'s width less the
+// exponent) is formed here from the maxima; the tiles of k block 0 also leave
+// scales, T1 flags and the fallback list.  Tiles wholly beyond the matrix are
+// not written: their bytes reach padded outputs only.
 //
 // The residue of the quantised integer a (|a| <= 2^62): its eight balanced
 // base-256 digits (bytes of a + 0x0080..80, each minus 128) against the
@@ -26,13 +31,17 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 struct ByteSide {
   const double* X;
   int ld, rows, rows_pad, ntiles;
-  const int32_t* scale;
+  const unsigned long long* bits;   // row maxima
+  const uint32_t* rmax;             // code products' maxima, [cslabs][rows_pad]
+  int cslabs, budget;
+  unsigned long long fixedR;        // OZ2_SCALE_FIXED: 256 k, else 0
+  int32_t* scale;
   uint32_t* flags;
   uint8_t* planes;
   unsigned vec;
   int* count;
   int* list;
-  int listed;
+  int listed, all;     // FORCE_FALLBACK: no row is listed by its flags; all rows are (A)
   long long stride;    // elements between the problems of a batch
 };
 
@@ -44,15 +53,26 @@ __device__ __forceinline__ uint32_t low4(uint32_t a, uint32_t b, uint32_t c, uin
 
 template <bool TRANS>
 __device__ __forceinline__ void byte_tile(const Oz2Byte& c, const ByteSide& S, int tl, int k, int kp,
-                                          unsigned quant_tz, size_t z) {
-  const int nrb = S.rows_pad / 64;
+                                          unsigned quant_tz, size_t z, int i0, int i1) {
+  const int nrb = (S.rows + 63) / 64;
   const int t = threadIdx.x;
   const int row = (tl % nrb) * 64 + (t >> 2), l0 = (tl / nrb) * 64 + (t & 3) * 16;
   const bool inrow = row < S.rows;
   uint32_t* flags = zws(S.flags, z);
-  const uint32_t f = inrow ? flags[row] : 0u;
-  const int sc = inrow ? zws(S.scale, z)[row] : 0;
-  const bool zero = !inrow || (f & OZ2_T1);
+  const unsigned long long top = inrow ? zws(S.bits, z)[row] : 0ull;
+  const bool t1 = top >= kInfBits, zero = !inrow || t1;
+  int sc = 0;
+  if (!zero) {
+    unsigned long long R = S.fixedR;
+    if (!R)
+      for (int sl = 0; sl < S.cslabs; ++sl) R += zws(S.rmax, z)[(size_t)sl * S.rows_pad + row];
+    sc = width_of(R, S.budget) - (top ? exp_of_bits(top) : 0);
+  }
+  if (tl < nrb && i0 == 0 && (t & 3) == 0 && inrow) {
+    zws(S.scale, z)[row] = sc;
+    if (t1) atomicOr(flags + row, OZ2_T1);
+    if (S.all || (t1 && !S.listed)) zws(S.list, z)[atomicAdd(zws(S.count, z), 1)] = row;
+  }
   const double* X = S.X + (size_t)blockIdx.z * S.stride;
   double x[16];
   if (!TRANS && S.vec && !zero && l0 + 16 <= k) {
@@ -86,11 +106,12 @@ __device__ __forceinline__ void byte_tile(const Oz2Byte& c, const ByteSide& S, i
   }
   // the first tile to flag a row adds it to the fallback list (unless every
   // row is listed already)
-  if (t2 && !(atomicOr(flags + row, OZ2_T2) & (OZ2_T1 | OZ2_T2)) && !S.listed)
+  if (t2 && i0 == 0 && !(atomicOr(flags + row, OZ2_T2) & (OZ2_T1 | OZ2_T2)) && !S.listed)
     zws(S.list, z)[atomicAdd(zws(S.count, z), 1)] = row;
   uint8_t* dst = zws(S.planes, z) + ((size_t)(l0 >> 6) * S.rows_pad + row) * OZ2_KBLK + (l0 & 63);
   const size_t pstride = (size_t)S.rows_pad * kp;
-  for (int i = 0; i < c.n; ++i) {
+  dst += i0 * pstride;
+  for (int i = i0; i < i1; ++i) {
     const int w0 = c.dot[i][0], w1 = c.dot[i][1], tof = c.tof[i];
     const uint32_t mg = c.mg0[i], nm = c.nm[i];
     uint32_t u[16];
@@ -110,13 +131,14 @@ __device__ __forceinline__ void byte_tile(const Oz2Byte& c, const ByteSide& S, i
 }
 
 // B's tiles first (B was read last by the scans and may still be in the
-// memory-side cache), then A's
+// memory-side cache), then A's; y: a share of the moduli
 __global__ void __launch_bounds__(256)
-k_byte_split(Oz2Byte c, ByteSide SA, ByteSide SB, int k, int kp, unsigned quant_tz, size_t wsz) {
-  const int t = blockIdx.x;
+k_byte_split(Oz2Byte c, ByteSide SA, ByteSide SB, int k, int kp, unsigned quant_tz, int share,
+             size_t wsz) {
+  const int t = blockIdx.x, i0 = blockIdx.y * share, i1 = min(c.n, i0 + share);
   const size_t z = (size_t)blockIdx.z * wsz;
-  if (t < SB.ntiles) byte_tile<false>(c, SB, t, k, kp, quant_tz, z);
-  else byte_tile<true>(c, SA, t - SB.ntiles, k, kp, quant_tz, z);
+  if (t < SB.ntiles) byte_tile<false>(c, SB, t, k, kp, quant_tz, z, i0, i1);
+  else byte_tile<true>(c, SA, t - SB.ntiles, k, kp, quant_tz, z, i0, i1);
 }
 
 // ---------------------------------------------------------------- reconstruction
@@ -244,20 +266,30 @@ void launch_crt_n(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_
 
 }  // namespace
 
-hipError_t oz2_launch_byte_split(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
-                                 const double* A, int lda, const double* B, int ldb,
-                                 const Oz2Batch& bt, hipStream_t s) {
+hipError_t oz2_launch_byte_split(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c,
+                                 const Oz2Byte& b, uint8_t* ws, const double* A, int lda,
+                                 const double* B, int ldb, const Oz2Batch& bt, hipStream_t s) {
   const unsigned tz = (d.flags & 4u) ? 1u : 0u;   // OZ2_QUANT_TZ
-  const int listed = (d.flags & 16u) ? 1 : 0;     // OZ2_FORCE_FALLBACK
+  const int force = (d.flags & 16u) ? 1 : 0;      // OZ2_FORCE_FALLBACK
+  const unsigned long long fixedR = (d.flags & 2u) ? 256ull * (unsigned long long)d.k : 0ull;
   const bool vec = (uintptr_t)B % 16 == 0 && ldb % 2 == 0 && bt.sB % 2 == 0;
-  ByteSide SA{A, lda, d.m, d.mp, (d.mp / 64) * (d.kp / 64), (const int32_t*)(ws + L.sA),
-              (uint32_t*)(ws + L.flagsA), ws + L.planesA, 0u, (int*)(ws + L.counters),
-              (int*)(ws + L.listA), listed, bt.sA};
-  ByteSide SB{B, ldb, d.n, d.np, (d.np / 64) * (d.kp / 64), (const int32_t*)(ws + L.tB),
-              (uint32_t*)(ws + L.flagsB), ws + L.planesB, vec ? 1u : 0u,
-              (int*)(ws + L.counters) + 1, (int*)(ws + L.listB), listed, bt.sB};
-  hipLaunchKernelGGL(k_byte_split, dim3(SA.ntiles + SB.ntiles, 1, bt.count), dim3(256), 0, s, c, SA,
-                     SB, d.k, d.kp, tz, bt.ws);
+  const int nkb = d.kp / 64;
+  const ByteSide SA{A, lda, d.m, d.mp, (d.m + 63) / 64 * nkb, (const unsigned long long*)(ws + L.rowbits),
+                    (const uint32_t*)(ws + L.Rmax), d.cslabs, c.cA, fixedR, (int32_t*)(ws + L.sA),
+                    (uint32_t*)(ws + L.flagsA), ws + L.planesA, 0u, (int*)(ws + L.counters),
+                    (int*)(ws + L.listA), force, force, bt.sA};
+  const ByteSide SB{B, ldb, d.n, d.np, (d.n + 63) / 64 * nkb, (const unsigned long long*)(ws + L.colbits),
+                    (const uint32_t*)(ws + L.Kmax), d.cslabs, c.cB, fixedR, (int32_t*)(ws + L.tB),
+                    (uint32_t*)(ws + L.flagsB), ws + L.planesB, vec ? 1u : 0u,
+                    (int*)(ws + L.counters) + 1, (int*)(ws + L.listB), force, 0, bt.sB};
+  // Few tiles: the moduli in up to five shares, each reading the tile again, so that
+  // the chain of a tile's 15 to 19 residues does not set the time (256^3: 32
+  // tiles, 9.0 us in one share).
+  const long long tiles = (long long)(SA.ntiles + SB.ntiles) * bt.count;
+  const int shares = (int)std::max(1ll, std::min(5ll, 2ll * oz2_device_cus() / tiles));
+  const int share = (b.n + shares - 1) / shares;
+  hipLaunchKernelGGL(k_byte_split, dim3(SA.ntiles + SB.ntiles, (b.n + share - 1) / share, bt.count),
+                     dim3(256), 0, s, b, SA, SB, d.k, d.kp, tz, share, bt.ws);
   return hipGetLastError();
 }
 

@@ -15,28 +15,30 @@
 
 namespace {
 
-// zero the row (side A) / column (side B) maxima the scans and the code GEMM
-// accumulate with atomics, and the operand's fallback-list count (the list
-// is filled by k_scales (T1) and k_split (T2) of this deconstruction)
-__global__ void k_init(unsigned long long* rowbits, int mp, unsigned long long* colbits, int np,
-                       uint32_t* Rmax, uint32_t* Kmax, int cslabs, int* counters, int side, size_t wsz) {
-  const size_t z = (size_t)blockIdx.z * wsz;
-  rowbits = zws(rowbits, z);
-  colbits = zws(colbits, z);
-  Rmax = zws(Rmax, z);
-  Kmax = zws(Kmax, z);
-  counters = zws(counters, z);
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t nR = (size_t)cslabs * mp, nK = (size_t)cslabs * np;
+// zero what an operand's deconstruction accumulates into: the row (column)
+// maxima of the scans and the code GEMM (atomics), its flags and scales
+// (padded rows are read too) and its fallback-list count
+__global__ void k_init(uint8_t* ws, Oz2Layout L, int mp, int np, int cslabs, int side, size_t wsz) {
+  ws += (size_t)blockIdx.z * wsz;
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const size_t nR = (size_t)cslabs * mp, nK = (size_t)cslabs * np;
   if (side & OZ2_SIDE_A) {
-    if (i < (size_t)mp) rowbits[i] = 0;
-    if (i < nR) Rmax[i] = 0;
-    if (i == 0) counters[0] = 0;
+    if (i < (size_t)mp) {
+      ((unsigned long long*)(ws + L.rowbits))[i] = 0;
+      ((uint32_t*)(ws + L.flagsA))[i] = 0;
+      ((int32_t*)(ws + L.sA))[i] = 0;
+    }
+    if (i < nR) ((uint32_t*)(ws + L.Rmax))[i] = 0;
+    if (i == 0) ((int*)(ws + L.counters))[0] = 0;
   }
   if (side & OZ2_SIDE_B) {
-    if (i < (size_t)np) colbits[i] = 0;
-    if (i < nK) Kmax[i] = 0;
-    if (i == 0) counters[1] = 0;
+    if (i < (size_t)np) {
+      ((unsigned long long*)(ws + L.colbits))[i] = 0;
+      ((uint32_t*)(ws + L.flagsB))[i] = 0;
+      ((int32_t*)(ws + L.tB))[i] = 0;
+    }
+    if (i < nK) ((uint32_t*)(ws + L.Kmax))[i] = 0;
+    if (i == 0) ((int*)(ws + L.counters))[1] = 0;
   }
 }
 
@@ -165,7 +167,7 @@ __device__ __forceinline__ void take_cols(const double* tile, bool zero, double 
 // Codes for the max-magnitude pass, in two steps so that each operand's FP64
 // input is read once here (the scan and the codes share the read):
 //
-// 1. k_scan_codes_rows / _cols (one 64x64 tile of 64 rows or columns x 64 k
+// 1. k_scan_codes (one 64x64 tile of 64 rows or columns x 64 k
 //    per workgroup): the tile-row maxima of |x| (folded into the row maxima
 //    with atomicMax), their frexp exponents Et (int16 [k/64][rows]), and per
 //    element a byte relative to Et, stored in the K-blocked codes layout:
@@ -204,20 +206,25 @@ __device__ __forceinline__ uint32_t local_code(unsigned long long b, int Et) {
 // instruction covers 512 contiguous bytes of two columns); the 64 x 64 bytes
 // are transposed through LDS so that each thread stores 16 consecutive k of
 // one row.
-__global__ void __launch_bounds__(256) k_scan_codes_rows(const double* __restrict__ X, int ld,
-                                                         int rows, int nrb, int k, unsigned vec,
-                                                         unsigned long long* bits, int16_t* et,
-                                                         uint8_t* __restrict__ codes,
-                                                         Oz2Batch bt) {
-  X += (size_t)blockIdx.z * bt.sA;
-  bits = zws(bits, (size_t)blockIdx.z * bt.ws);
-  et = zws(et, (size_t)blockIdx.z * bt.ws);
-  codes = zws(codes, (size_t)blockIdx.z * bt.ws);
-  __shared__ __attribute__((aligned(16))) uint8_t T[64][80];
-  __shared__ unsigned long long mx[8][64];
+struct CodeSide {
+  const double* X;
+  int ld, rows, nrb;               // nrb: padded rows / 64
+  unsigned vec;
+  unsigned long long* bits;
+  int16_t* et;
+  uint8_t* codes;
+};
+__device__ __forceinline__ void scan_codes_rows(const CodeSide& S, const double* __restrict__ X, int k,
+                                                int blk, size_t z, uint8_t (*T)[80],
+                                                unsigned long long (*mx)[64]) {
+  const int ld = S.ld, rows = S.rows, nrb = S.nrb;
+  const unsigned vec = S.vec;
+  unsigned long long* bits = zws(S.bits, z);
+  int16_t* et = zws(S.et, z);
+  uint8_t* codes = zws(S.codes, z);
   const int rows_pad = nrb * 64;
   const int t = threadIdx.x;
-  const int bx = (int)(blockIdx.x % (unsigned)nrb), by = (int)(blockIdx.x / (unsigned)nrb);
+  const int bx = blk % nrb, by = blk / nrb;
   const int p = t & 31, g = t >> 5;
   const int r0 = bx * 64 + 2 * p, lbase = by * 64;
   double2 v[8];
@@ -278,22 +285,18 @@ __global__ void __launch_bounds__(256) k_scan_codes_rows(const double* __restric
 // columns t/32 + 8j with 16-byte loads (512 contiguous bytes of one column per
 // half-wave instruction); a column's tile maximum is a max-reduction over the
 // 32 lanes of a half-wave; the bytes are transposed through LDS as for A.
-__global__ void __launch_bounds__(256) k_scan_codes_cols(const double* __restrict__ X, int ld,
-                                                         int rows, int nrb, int k, unsigned vec,
-                                                         unsigned long long* bits, int16_t* et,
-                                                         uint8_t* __restrict__ codes,
-                                                         Oz2Batch bt) {
-  X += (size_t)blockIdx.z * bt.sB;
-  bits = zws(bits, (size_t)blockIdx.z * bt.ws);
-  et = zws(et, (size_t)blockIdx.z * bt.ws);
-  codes = zws(codes, (size_t)blockIdx.z * bt.ws);
-  __shared__ __attribute__((aligned(16))) uint8_t T[64][80];
+__device__ __forceinline__ void scan_codes_cols(const CodeSide& S, const double* __restrict__ X, int k,
+                                                int nkb, int blk, size_t z, uint8_t (*T)[80]) {
+  const int ld = S.ld, rows = S.rows, nrb = S.nrb;
+  const unsigned vec = S.vec;
+  unsigned long long* bits = zws(S.bits, z);
+  int16_t* et = zws(S.et, z);
+  uint8_t* codes = zws(S.codes, z);
   const int rows_pad = nrb * 64;
   const int t = threadIdx.x;
   // k-blocks fastest: consecutive workgroups read consecutive 512-byte pieces
   // of the same 64 columns (DRAM pages are filled in order)
-  const int nkb = (int)(gridDim.x / (unsigned)nrb);
-  const int by = (int)(blockIdx.x % (unsigned)nkb), bx = (int)(blockIdx.x / (unsigned)nkb);
+  const int by = blk % nkb, bx = blk / nkb;
   const int p = t & 31, kk = 2 * p, g = t >> 5;
   const int l = by * 64 + kk;
   double2 v[8];
@@ -337,6 +340,18 @@ __global__ void __launch_bounds__(256) k_scan_codes_cols(const double* __restric
   const int row = bx * 64 + (t >> 2), l0 = by * 64 + (t & 3) * 16;
   const uint4 o = *reinterpret_cast<const uint4*>(&T[t >> 2][(t & 3) * 16]);
   *reinterpret_cast<uint4*>(codes + kblocked(row, l0, rows_pad)) = o;
+}
+
+// both operands in one launch, A's tiles first (B, read last, may then still be
+// in the memory-side cache for the split)
+__global__ void __launch_bounds__(256) k_scan_codes(CodeSide SA, CodeSide SB, int k, int nkb, int nA,
+                                                    Oz2Batch bt) {
+  __shared__ __attribute__((aligned(16))) uint8_t T[64][80];
+  __shared__ unsigned long long mx[8][64];
+  const size_t z = (size_t)blockIdx.z * bt.ws;
+  const int b = blockIdx.x;
+  if (b < nA) scan_codes_rows(SA, SA.X + (size_t)blockIdx.z * bt.sA, k, b, z, T, mx);
+  else scan_codes_cols(SB, SB.X + (size_t)blockIdx.z * bt.sB, k, nkb, b - nA, z, T);
 }
 
 // code of one byte of step 1 given D = E - Et: with d = min(D + dt, 4), the
@@ -607,10 +622,8 @@ hipError_t oz2_launch_init(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, in
   if ((size_t)d.mp > n) n = d.mp;
   if ((size_t)d.np > n) n = d.np;
   unsigned blocks = (unsigned)((n + 255) / 256);
-  hipLaunchKernelGGL(k_init, dim3(blocks, 1, bt.count), dim3(256), 0, s,
-                     (unsigned long long*)(ws + L.rowbits), d.mp,
-                     (unsigned long long*)(ws + L.colbits), d.np, (uint32_t*)(ws + L.Rmax),
-                     (uint32_t*)(ws + L.Kmax), d.cslabs, (int*)(ws + L.counters), side, bt.ws);
+  hipLaunchKernelGGL(k_init, dim3(blocks, 1, bt.count), dim3(256), 0, s, ws, L, d.mp, d.np, d.cslabs,
+                     side, bt.ws);
   return hipGetLastError();
 }
 
@@ -637,22 +650,17 @@ hipError_t oz2_launch_scan(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, co
 }
 
 hipError_t oz2_launch_scan_codes(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
-                                 const double* A, int lda, const double* B, int ldb, int side,
+                                 const double* A, int lda, const double* B, int ldb,
                                  const Oz2Batch& bt, hipStream_t s) {
-  if (side & OZ2_SIDE_A) {
-    dim3 ga((d.mp / 64) * (d.kp / 64), 1, bt.count);
-    const unsigned vecA = ((uintptr_t)A % 16 == 0 && lda % 2 == 0 && bt.sA % 2 == 0) ? 1u : 0u;
-    hipLaunchKernelGGL(k_scan_codes_rows, ga, dim3(256), 0, s, A, lda, d.m, d.mp / 64, d.k, vecA,
-                       (unsigned long long*)(ws + L.rowbits), (int16_t*)(ws + L.etA),
-                       ws + L.codesA, bt);
-  }
-  if (side & OZ2_SIDE_B) {
-    dim3 gb((d.np / 64) * (d.kp / 64), 1, bt.count);
-    const unsigned vecB = ((uintptr_t)B % 16 == 0 && ldb % 2 == 0 && bt.sB % 2 == 0) ? 1u : 0u;
-    hipLaunchKernelGGL(k_scan_codes_cols, gb, dim3(256), 0, s, B, ldb, d.n, d.np / 64, d.k, vecB,
-                       (unsigned long long*)(ws + L.colbits), (int16_t*)(ws + L.etB),
-                       ws + L.codesB, bt);
-  }
+  const unsigned vecA = ((uintptr_t)A % 16 == 0 && lda % 2 == 0 && bt.sA % 2 == 0) ? 1u : 0u;
+  const unsigned vecB = ((uintptr_t)B % 16 == 0 && ldb % 2 == 0 && bt.sB % 2 == 0) ? 1u : 0u;
+  const CodeSide SA{A, lda, d.m, d.mp / 64, vecA, (unsigned long long*)(ws + L.rowbits),
+                    (int16_t*)(ws + L.etA), ws + L.codesA};
+  const CodeSide SB{B, ldb, d.n, d.np / 64, vecB, (unsigned long long*)(ws + L.colbits),
+                    (int16_t*)(ws + L.etB), ws + L.codesB};
+  const int nkb = d.kp / 64, nA = (d.mp / 64) * nkb, nB = (d.np / 64) * nkb;
+  hipLaunchKernelGGL(k_scan_codes, dim3(nA + nB, 1, bt.count), dim3(256), 0, s, SA, SB, d.k, nkb, nA,
+                     bt);
   return hipGetLastError();
 }
 

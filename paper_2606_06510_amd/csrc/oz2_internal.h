@@ -156,7 +156,7 @@ hipError_t oz2_launch_scan(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
 // scan + per-tile code bytes in one read of each operand, then the bytes
 // rebased to the row exponents (the codes of the max-magnitude pass)
 hipError_t oz2_launch_scan_codes(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
-                                 const double* A, int lda, const double* B, int ldb, int side,
+                                 const double* A, int lda, const double* B, int ldb,
                                  const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_rebase(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, int side,
                              const Oz2Batch& bt, hipStream_t s);
@@ -199,9 +199,9 @@ hipError_t oz2_launch_gemv(const Oz2Const& c, const Oz2Dims& d, const Oz2Layout&
                            int splits, bool reuse, hipStream_t s);
 // the byte-residue route: the split of both operands, the residue products,
 // the CRT reconstruction with the gather of the fallback's panel
-hipError_t oz2_launch_byte_split(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
-                                 const double* A, int lda, const double* B, int ldb,
-                                 const Oz2Batch& bt, hipStream_t s);
+hipError_t oz2_launch_byte_split(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c,
+                                 const Oz2Byte& b, uint8_t* ws, const double* A, int lda,
+                                 const double* B, int ldb, const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_bytegemm(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
                                const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_byte_crt(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,

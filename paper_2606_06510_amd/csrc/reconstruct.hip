@@ -456,12 +456,19 @@ hipError_t oz2_launch_crt_probe(const Oz2Const& c, const int16_t* res, const int
   return hipGetLastError();
 }
 
+// workgroups: 1024 over the batch, no more than the tiles there can be (an empty
+// launch of 1024 takes 2.4-4.6 us, one of 32 under 2)
+static unsigned fallback_grid(const Oz2Dims& d, int count) {
+  const long long tiles = 2ll * ((d.m + FB_T - 1) / FB_T) * ((d.n + FB_T - 1) / FB_T);
+  return (unsigned)std::max(1ll, std::min<long long>(tiles, 1024 / count));
+}
+
 hipError_t oz2_launch_fallback(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, const double* A,
                                int lda, const double* B, int ldb, double* C, int ldc,
                                const Oz2Batch& bt, hipStream_t s) {
   // the lists were filled by the deconstruction (k_scales: T1, k_split: T2)
   // the panel of flagged rows was gathered by the reconstruction launch
-  hipLaunchKernelGGL(k_fallback, dim3(std::max(1, 1024 / bt.count), 1, bt.count), dim3(256), 0, s, d,
+  hipLaunchKernelGGL(k_fallback, dim3(fallback_grid(d, bt.count), 1, bt.count), dim3(256), 0, s, d,
                      A, lda, B, ldb, C, ldc, (const int*)(ws + L.counters),
                      (const int*)(ws + L.listA), (const int*)(ws + L.listB),
                      (const uint32_t*)(ws + L.flagsA), (const double*)(ws + L.panel),
@@ -472,7 +479,7 @@ hipError_t oz2_launch_fallback(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws
 hipError_t oz2_launch_fallback_direct(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
                                       const double* A, int lda, const double* B, int ldb,
                                       double* C, int ldc, hipStream_t s) {
-  hipLaunchKernelGGL(k_fallback, dim3(1024), dim3(256), 0, s, d, A, lda, B, ldb, C, ldc,
+  hipLaunchKernelGGL(k_fallback, dim3(fallback_grid(d, 1)), dim3(256), 0, s, d, A, lda, B, ldb, C, ldc,
                      (const int*)(ws + L.counters), (const int*)(ws + L.listA),
                      (const int*)(ws + L.listB), (const uint32_t*)(ws + L.flagsA),
                      (const double*)nullptr, 0, Oz2Batch{1, 0, 0, 0, 0});
