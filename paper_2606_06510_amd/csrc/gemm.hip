@@ -457,7 +457,7 @@ k_resgemm(Oz2Const c, const uint8_t* __restrict__ PA, const uint8_t* __restrict_
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)LB;
   const int ntm = mp / TILE, ntn = np / TILE;
   const int tile = tile_of(tbase + blockIdx.x, ntm, ntn);
-  const int mi0 = mgroup * mpw, mi1 = min(c.r, mi0 + mpw);
+  const int mi0 = (mgroup + (int)blockIdx.y) * mpw, mi1 = min(c.r, mi0 + mpw);
   const int tm = tile % ntm, tn = tile / ntm;
   Ctx x;
   x.psA = (size_t)mp * kp;
@@ -625,7 +625,7 @@ k_resgemm_duo(Oz2Const c, const uint8_t* __restrict__ PA, const uint8_t* __restr
   const int ntm = mp / TILE, ntn = np / TILE;
   const int b = blockIdx.x, slot = b >> 3, half = slot & 1;
   const int tile = tile_of(tbase + (slot >> 1) * 8 + (b & 7), ntm, ntn);
-  const int mi0 = mgroup * mpw, mi1 = min(c.r, mi0 + mpw);
+  const int mi0 = (mgroup + (int)blockIdx.y) * mpw, mi1 = min(c.r, mi0 + mpw);
   const int tm = tile % ntm, tn = tile / ntm;
   Ctx x;
   x.psA = (size_t)mp * kp;
@@ -764,10 +764,13 @@ hipError_t oz2_launch_resgemm(const Oz2Dims& d, const Oz2Layout& L, const Oz2Con
     const int lds = duo ? DNB * DSTB : 0;
     if (duo) (void)hipFuncSetAttribute((const void*)kern,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    for (int g = 0; g < groups; ++g)
+    // a tile count below one round: all modulus groups in one launch (one after the
+    // other they leave most CUs idle: 2048^3, 64 tiles, four launches)
+    const int gy = tiles <= cus ? groups : 1;
+    for (int g = 0; g < groups; g += gy)
       for (int tb = 0; tb < tiles; tb += chunk) {
         const int nt = std::min(chunk, tiles - tb);
-        hipLaunchKernelGGL(kern, dim3(duo ? 2 * nt : nt), dim3(duo ? DNT : NT), lds, s, c,
+        hipLaunchKernelGGL(kern, dim3(duo ? 2 * nt : nt, gy), dim3(duo ? DNT : NT), lds, s, c,
                            ws + L.planesA, ws + L.planesB, d.mp, d.np, d.kp, kb, ke,
                            sl > 0 ? 1 : 0, mpw, g, tb, (uint32_t*)(ws + L.res));
         const hipError_t e = hipGetLastError();
