@@ -18,6 +18,8 @@
 // and column t/8, k 8 (t%8) .. of B.  Wave w owns the 16 x 16 output blocks
 // at block row w/2, block columns 2 (w%2) and 2 (w%2) + 1.  Persistent grid:
 // each workgroup walks problems b = blockIdx.x, += gridDim.x.
+#include <atomic>
+
 #include "oz2_tile.h"
 #include "oz2_device.h"
 
@@ -380,14 +382,24 @@ hipError_t oz2_launch_batched(const Oz2Const& c, int m, int n, int k, int batch,
                               int lda, long long sA, const double* B, int ldb, long long sB,
                               double* C, int ldc, long long sC, uint32_t* iout, hipStream_t s) {
   auto kern = iout ? k_batched<true> : k_batched<false>;
-  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)sizeof(Smem));
   const unsigned vecB = (uintptr_t)B % 16 == 0 && ldb % 2 == 0 && sB % 2 == 0;
   const unsigned vecC = (uintptr_t)C % 16 == 0 && ldc % 2 == 0 && sC % 2 == 0;
-  int per = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, NTB, sizeof(Smem)) != hipSuccess ||
-      per < 1)
-    per = 1;
+  // the attribute and the occupancy once per device and kernel (two runtime
+  // calls on every launch otherwise; a race repeats them)
+  static std::atomic<int> resident[2][64];
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  std::atomic<int>& slot = resident[iout ? 1 : 0][dev & 63];
+  int per = slot.load();
+  if (per == 0) {
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)sizeof(Smem));
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, NTB, sizeof(Smem)) != hipSuccess ||
+        per < 1)
+      per = 1;
+    slot.store(per);
+  }
   hipLaunchKernelGGL(kern, dim3(min(batch, per * oz2_device_cus())), dim3(NTB), sizeof(Smem), s, c.cA,
                      c.cB, m, n, k, batch, A, lda, sA, B, ldb, sB, C, ldc, sC, iout, vecB, vecC);
   return hipGetLastError();
