@@ -592,7 +592,7 @@ int run_deconstruct(ozaki2_plan_s& p, int side, hipStream_t s) {
   if (e == hipSuccess)   // (codes: both sides, always)
     e = codes ? oz2_launch_scan_codes(d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, kOne, s)
               : oz2_launch_scan(d, p.L, p.ws, p.A, p.lda, p.B, p.ldb, side, kOne, s);
-  if (codes && e == hipSuccess) e = oz2_launch_rebase(d, p.L, p.ws, side, kOne, s);
+  if (codes && e == hipSuccess) e = oz2_launch_rebase(d, p.L, p.ws, side, false, kOne, s);
   if (e == hipSuccess) e = mark(p, 1, s);
   if (codes && e == hipSuccess) e = oz2_launch_codegemm(d, p.L, p.ws, kOne, s);
   if (e == hipSuccess) e = mark(p, 2, s);
@@ -618,8 +618,10 @@ int run_bytes(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c, const Oz2
   if (e == hipSuccess)
     e = codes ? oz2_launch_scan_codes(d, L, ws, A, lda, B, ldb, bt, s)
               : oz2_launch_scan(d, L, ws, A, lda, B, ldb, both, bt, s);
-  if (codes && e == hipSuccess) e = oz2_launch_rebase(d, L, ws, both, bt, s);
-  if (codes && e == hipSuccess) e = oz2_launch_codegemm(d, L, ws, bt, s);
+  const bool small = codes && oz2_codegemm128_fits(d, bt);
+  if (codes && e == hipSuccess) e = oz2_launch_rebase(d, L, ws, both, small, bt, s);
+  if (codes && e == hipSuccess)
+    e = small ? oz2_launch_codegemm128(d, L, ws, bt, s) : oz2_launch_codegemm(d, L, ws, bt, s);
   if (e == hipSuccess) e = oz2_launch_byte_split(d, L, c, b, ws, A, lda, B, ldb, bt, s);
   if (bt.count == 1 && oz2_byte_fused_fits(d, b)) {
     if (e == hipSuccess) e = oz2_launch_byte_fused(d, L, b, ws, C, ldc, s);

@@ -259,6 +259,34 @@ __device__ __forceinline__ void small_issue(Stream& d, size_t kbA, size_t kbB, u
   d.pb += kbB;
 }
 
+// stages it0 .. it0 + n - 1 of T into acc.  A wave's share of stage `it` is four
+// DMA instructions, issued two stages ahead; after the barrier every share has
+// landed and stage it - 1 has been read by all, so its slot takes stage it + 2.
+__device__ __forceinline__ void small_stages(Stream& d, size_t kbA, size_t kbB, const uint8_t* fa0,
+                                             const uint8_t* fb0, uint32_t lds0, int T, int it0, int n,
+                                             v4i (&acc)[4][4]) {
+  int slot = it0 % SNB;
+  for (int it = it0; it < it0 + n; ++it) {
+    if (it + 1 < T) wait_vm<4>();
+    else wait_vm<0>();
+    bar();
+    if (it + SNB - 1 < T) small_issue(d, kbA, kbB, lds0 + (slot == 0 ? SNB - 1 : slot - 1) * SST);
+    const int so = slot * SST;
+    slot = slot == SNB - 1 ? 0 : slot + 1;
+    v4i fa[4], fb[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fa[i] = frag(fa0 + so + i * 16 * KS);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) fb[j] = frag(fb0 + so + j * 16 * KS);
+    wait_lgkm0();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
+  }
+}
+
 template <bool SHORT>
 __global__ void __launch_bounds__(SNT, 3)
 k_bytegemm128(Oz2Byte c, const uint8_t* __restrict__ PA, const uint8_t* __restrict__ PB, int mp,
@@ -295,39 +323,111 @@ k_bytegemm128(Oz2Byte c, const uint8_t* __restrict__ PA, const uint8_t* __restri
   const uint32_t off = SHORT ? c.off0[mi] : c.off7[mi];
   v4i acc[4][4];
   start(acc, off);
-  int it = 0, slot = 0;
   for (int k0 = 0; k0 < T; k0 += OZ2_KSLAB / KS) {
     if (k0) fold(acc, mg, nm, off);
-    const int end = it + min(T - k0, OZ2_KSLAB / KS);
-    for (; it < end; ++it) {
-      // this wave's share of stage `it` (four DMA instructions, issued two
-      // stages ahead); after the barrier every share has landed and stage
-      // it - 1 has been read by all, so its slot takes stage it + 2
-      if (it + 1 < T) wait_vm<4>();
-      else wait_vm<0>();
-      bar();
-      if (it + SNB - 1 < T) small_issue(d, kbA, kbB, lds0 + (slot == 0 ? SNB - 1 : slot - 1) * SST);
-      const int so = slot * SST;
-      slot = slot == SNB - 1 ? 0 : slot + 1;
-      v4i fa[4], fb[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) fa[i] = frag(fa0 + so + i * 16 * KS);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) fb[j] = frag(fb0 + so + j * 16 * KS);
-      wait_lgkm0();
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
-    }
+    small_stages(d, kbA, kbB, fa0, fb0, lds0, T, k0, min(T - k0, OZ2_KSLAB / KS), acc);
   }
   uint32_t wd[4][4];
   pack<SHORT>(acc, mg, nm, wd);
   store(res + (size_t)mi * mp * np + unit + lane * 16, cbs, wd);
 }
 
+// ------------------------------------------------ code products, 128 x 128 tiles
+// The max-magnitude pass on integer code bytes (0..16), where the E4M3 kernel's
+// 256 x 256 tiles are too few: the loop above for one "modulus", the
+// epilogue row and column maxima.  Exact: |sums| <= 256 k, one code slab.
+
+// One halving step of a maximum over lanes L and L^B: of the first 2 N entries of
+// u, lane L keeps the half selected by bit B of L.
+template <int N, int B>
+__device__ __forceinline__ void halve(int (&u)[16], int lane) {
+  const bool up = (lane & B) != 0;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const int keep = up ? u[k + N] : u[k], send = up ? u[k] : u[k + N];
+    u[k] = max(keep, __shfl_xor(send, B));
+  }
+}
+
+__global__ void __launch_bounds__(SNT, 3)
+k_codegemm128(const uint8_t* __restrict__ PA, const uint8_t* __restrict__ PB, int mp, int np, int kp,
+              int ntm, uint32_t* Rmax, uint32_t* Kmax, size_t wsz) {
+  __shared__ __attribute__((aligned(16))) uint8_t LB[SNB * SST];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)LB;
+  const int tm = (int)blockIdx.x % ntm, tn = (int)blockIdx.x / ntm;
+  const size_t kbA = (size_t)mp * KS, kbB = (size_t)np * KS, z = (size_t)blockIdx.z * wsz;
+  const int T = kp / KS;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  Stream d;
+  {
+    const int rb = lane >> 2;
+    d.vo = (uint32_t)(rb * KS + 16 * ((lane & 3) ^ swz16(rb))) + (uint32_t)w * 1024u;
+    d.mw = (uint32_t)w * 1024u;
+    d.pa = PA + z + (size_t)tm * ST * KS;
+    d.pb = PB + z + (size_t)tn * ST * KS;
+  }
+#pragma unroll
+  for (int t = 0; t < SNB - 1; ++t)
+    if (t < T) small_issue(d, kbA, kbB, lds0 + t * SST);
+  const int wr = w >> 1, wc = w & 1;
+  const int fo = (lane & 15) * KS + 16 * ((lane >> 4) ^ swz16(lane & 15));
+  v4i acc[4][4];
+  start(acc, 0);
+  small_stages(d, kbA, kbB, LB + wr * 64 * KS + fo, LB + SOP + wc * 64 * KS + fo, lds0, T, 0, T, acc);
+  // lane (g, c): rows 16 i + 4 g + e, columns 16 j + c of the wave's 64 x 64
+  const int g = lane >> 4, c = lane & 15;
+  int u[16], v[16];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      u[4 * i + e] = max(max(acc[i][0][e], acc[i][1][e]), max(acc[i][2][e], acc[i][3][e]));
+  halve<8, 8>(u, lane);
+  halve<4, 4>(u, lane);
+  halve<2, 2>(u, lane);
+  halve<1, 1>(u, lane);
+  // entry c of the 16: i = c / 4, e = c % 4
+  uint32_t* R = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(Rmax) + z) + tm * ST + wr * 64;
+  atomicMax(R + 16 * (c >> 2) + 4 * g + (c & 3), (uint32_t)u[0]);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    int x = acc[0][j][0];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x = max(x, acc[i][j][e]);
+    v[j] = x;
+  }
+  halve<2, 32>(v, lane);
+  halve<1, 16>(v, lane);
+  uint32_t* K = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(Kmax) + z) + tn * ST + wc * 64;
+  atomicMax(K + 16 * g + c, (uint32_t)v[0]);
+}
+
 }  // namespace
+
+// One code slab, and by the times below: 0.37 us per stage + 4 for a 128-tile
+// workgroup alone on its CU (0.80 with two beside it) against 0.82 + 6 for a
+// 256-tile one of the E4M3 kernel.
+bool oz2_codegemm128_fits(const Oz2Dims& d, const Oz2Batch& bt) {
+  if (d.cslabs != 1) return false;
+  const double cus = oz2_device_cus(), nk = d.kp / KS;
+  const double small = (double)((d.m + ST - 1) / ST) * ((d.n + ST - 1) / ST) * bt.count;
+  const double big = (double)(d.mp / BT) * (d.np / BT) * bt.count;
+  const double t_small = small <= cus ? 0.37 * nk + 4.0
+                                      : std::max(1.0, small / (3.0 * cus)) * (0.80 * nk + 1.8) + 3.0;
+  return t_small < std::ceil(big / cus) * (0.82 * nk + 6.0);
+}
+
+hipError_t oz2_launch_codegemm128(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
+                                  const Oz2Batch& bt, hipStream_t s) {
+  const int ntm = (d.m + ST - 1) / ST, ntn = (d.n + ST - 1) / ST;
+  hipLaunchKernelGGL(k_codegemm128, dim3(ntm * ntn, 1, bt.count), dim3(SNT), 0, s, ws + L.codesA,
+                     ws + L.codesB, d.mp, d.np, d.kp, ntm, (uint32_t*)(ws + L.Rmax),
+                     (uint32_t*)(ws + L.Kmax), bt.ws);
+  return hipGetLastError();
+}
 
 // Which kernel, and how many moduli a workgroup walks.  Measured times (us,
 // one MI355X) fit: a 256-tile workgroup 0.82 per K-stage + 3.3 per modulus

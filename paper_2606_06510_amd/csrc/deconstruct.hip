@@ -372,11 +372,13 @@ __global__ void __launch_bounds__(256) k_rebase(uint8_t* codesA, const int16_t* 
                                                 int mp, size_t nA, uint8_t* codesB,
                                                 const int16_t* __restrict__ etB,
                                                 const unsigned long long* __restrict__ bitsB,
-                                                int np, size_t nB, size_t wsz) {
+                                                int np, size_t nB, int integers, size_t wsz) {
   __shared__ uint8_t lut[5 * 256];
   for (int e = threadIdx.x; e < 5 * 256; e += blockDim.x)
-    lut[e] = (uint8_t)(__builtin_amdgcn_cvt_pk_fp8_f32(rebase_code((uint32_t)(e & 255), e >> 8),
-                                                       0.0f, 0, false) & 0xFF);
+  {
+    const float v = rebase_code((uint32_t)(e & 255), e >> 8);
+    lut[e] = integers ? (uint8_t)v : (uint8_t)(__builtin_amdgcn_cvt_pk_fp8_f32(v, 0.0f, 0, false) & 0xFF);
+  }
   __syncthreads();
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t z = (size_t)blockIdx.z * wsz;
@@ -665,7 +667,7 @@ hipError_t oz2_launch_scan_codes(const Oz2Dims& d, const Oz2Layout& L, uint8_t* 
 }
 
 hipError_t oz2_launch_rebase(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, int side,
-                             const Oz2Batch& bt, hipStream_t s) {
+                             bool integers, const Oz2Batch& bt, hipStream_t s) {
   const size_t nA = (side & OZ2_SIDE_A) ? (size_t)d.mp * (d.kp / 64) : 0;
   const size_t nB = (side & OZ2_SIDE_B) ? (size_t)d.np * (d.kp / 64) : 0;
   if (nA + nB == 0) return hipSuccess;
@@ -673,7 +675,7 @@ hipError_t oz2_launch_rebase(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, 
                      ws + L.codesA, (const int16_t*)(ws + L.etA),
                      (const unsigned long long*)(ws + L.rowbits), d.mp, nA, ws + L.codesB,
                      (const int16_t*)(ws + L.etB), (const unsigned long long*)(ws + L.colbits),
-                     d.np, nB, bt.ws);
+                     d.np, nB, integers ? 1 : 0, bt.ws);
   return hipGetLastError();
 }
 

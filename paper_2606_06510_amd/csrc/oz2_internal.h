@@ -158,9 +158,14 @@ hipError_t oz2_launch_scan(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
 hipError_t oz2_launch_scan_codes(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
                                  const double* A, int lda, const double* B, int ldb,
                                  const Oz2Batch& bt, hipStream_t s);
+// integers: code bytes 0..16 instead of their E4M3 encodings
 hipError_t oz2_launch_rebase(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, int side,
-                             const Oz2Batch& bt, hipStream_t s);
+                             bool integers, const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_codegemm(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, const Oz2Batch& bt, hipStream_t s);
+// the code products on integer code bytes in 128 x 128 tiles, where that is faster
+bool oz2_codegemm128_fits(const Oz2Dims& d, const Oz2Batch& bt);
+hipError_t oz2_launch_codegemm128(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
+                                  const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_scales(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c,
                              uint8_t* ws, int side, const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_tables(const Oz2Layout& L, const Oz2Const& c, uint8_t* ws, hipStream_t s);
