@@ -112,7 +112,6 @@ bool build_const(int r, Oz2Const& c) {
       c.fin[i] = 16;
     }
     c.finv[i] = 1.0f / (float)m;
-    c.finv_s[i] = s ? 1.0f / (float)s : 0.0f;
     c.dinv[i] = 1.0 / (double)m;
     // W_i = (M/m_i) * ((M/m_i)^-1 mod m_i)
     Big Mi(1);
@@ -121,12 +120,7 @@ bool build_const(int r, Oz2Const& c) {
     const int64_t inv = inv_mod(Mi.mod_small((uint32_t)m), m);
     Big Wi = Mi;
     Wi.mul_small((uint32_t)inv);
-    for (int j = 0; j < OZ2_NLIMB; ++j) c.W[i][j] = (double)Wi.word(j);
     for (int j = 0; j < 4; ++j) c.W38[i][j] = (double)Wi.bits(38 * j, 38);
-    Big Wf = Mi;
-    Wf.mul_small((uint32_t)((inv * c.fin[i]) % m));
-    for (int j = 0; j < 4; ++j) c.W38f[i][j] = (double)Wf.bits(38 * j, 38);
-    c.wfrac[i] = (double)inv / (double)m;   // W_i / M exactly = inv_i / m_i
   }
   c.P = pb;
   // kcheap: with digit maxima D0, D1 of the planes (both operands share the
@@ -155,37 +149,27 @@ bool build_const(int r, Oz2Const& c) {
   c.tabsz = off;
   Big Mh = M;
   Mh.shr1();
-  for (int j = 0; j < OZ2_NLIMB; ++j) {
-    c.Ml[j] = (double)M.word(j);
-    c.Mhalf[j] = (double)Mh.word(j);
-  }
   for (int j = 0; j < 4; ++j) {
     c.M38[j] = (double)M.bits(38 * j, 38);
     c.Mhalf38[j] = (double)Mh.bits(38 * j, 38);
   }
-  // the reconstruction kernels are specialised on r with nw = 3 (r <= 10),
-  // 4 (r <= 13), 5 words: [-M/2, M/2) must fit nw words of two's complement
+  // the GEMV's integers take nw = 3 (r <= 10), 4 (r <= 13), 5 words: [-M/2, M/2)
+  // must fit nw words of two's complement
   c.nw = r <= 10 ? 3 : (r <= 13 ? 4 : 5);
   if (M.bitlen() + 1 > 32 * c.nw) return false;
   double Md = 0.0;
   for (int j = OZ2_NLIMB - 1; j >= 0; --j) Md = Md * 4294967296.0 + (double)M.word(j);
-  c.mtop = std::ldexp(1.0, 32 * (c.nw - 1)) / Md;
   // radix-2^38 limbs (the reconstruction): [-M/2, M/2) must fit three limbs
   // (114 bits) for r <= 12 and four (152 bits) above
   const int nl38 = r <= 12 ? 3 : 4;
   if (M.bitlen() + 1 > 38 * nl38) return false;
   c.mtop38 = std::ldexp(1.0, 38 * (nl38 - 1)) / Md;
   // the offsets of the stored residues, folded into the CRT sums
-  // (integer sums: W38 limbs < 2^38 and W words < 2^32, offsets <= 576)
+  // (integer sums: W38 limbs < 2^38, offsets <= 576)
   for (int j = 0; j < 4; ++j) {
     int64_t k = 0;
     for (int i = 0; i < r; ++i) k += (int64_t)(ms[i] / 2 + 32) * (int64_t)c.W38[i][j];
     c.K38[j] = (double)k;   // < 2^52: exact
-  }
-  for (int j = 0; j < OZ2_NLIMB; ++j) {
-    int64_t k = 0;
-    for (int i = 0; i < r; ++i) k += (int64_t)(ms[i] / 2 + 32) * (int64_t)c.W[i][j];
-    c.Kw[j] = (double)k;    // < 2^46: exact
   }
   const int cc = (M.bitlen() - 1) + 6;     // floor(log2 M) + 6
   c.cA = cc / 2;
@@ -377,8 +361,6 @@ Oz2Layout make_byte_layout(const Oz2Dims& d, const Oz2Byte& c) {
   L.Kmax = take((size_t)d.cslabs * d.np * 4);
   L.sA = take((size_t)d.mp * 4);
   L.tB = take((size_t)d.np * 4);
-  L.eA = take((size_t)d.mp * 4);
-  L.eB = take((size_t)d.np * 4);
   L.counters = take(64);
   L.listA = take((size_t)d.mp * 4);
   L.listB = take((size_t)d.np * 4);

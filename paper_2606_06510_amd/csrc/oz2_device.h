@@ -72,12 +72,6 @@ __device__ __forceinline__ float code_of(double x, int E) {
   return (float)fmax(y, 1.0);
 }
 
-__device__ __forceinline__ uint32_t pack4_fp8(float a, float b, float c, float d) {
-  int w = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
-  w = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, w, true);
-  return (uint32_t)w;
-}
-
 // widths sigma = min(62, c - ceil(ell(R)/2)), ell(x) = ceil(log2 x) (0 for x <= 1)
 __device__ __forceinline__ int width_of(unsigned long long R, int budget) {
   int ell = (R > 1) ? (64 - __clzll((long long)(R - 1))) : 0;
@@ -106,34 +100,6 @@ __device__ __forceinline__ uint32_t gather_byte(uint32_t e0, uint32_t e1, uint32
   return __builtin_amdgcn_perm(x23, x01, 0x05040100u);
 }
 
-// 32-bit words of the two's complement integer in [-M/2, M/2) for r moduli
-// (log2 M = 76.0, 85.0, 94.0, 102.9, 111.8, 120.8, 129.7, 138.5, 147.4 for
-// r = 8..16; the host checks the same rule).
-template <int R>
-struct NWords {
-  static constexpr int value = R <= 10 ? 3 : (R <= 13 ? 4 : 5);
-};
-
-// Residue I of the 8 a thread holds for one modulus (int16 I of the uint4).
-template <int I>
-__device__ __forceinline__ double res_at(const uint4& v) {
-  constexpr int wi = I >> 1;
-  const uint32_t wd = wi == 0 ? v.x : wi == 1 ? v.y : wi == 2 ? v.z : v.w;
-  return (double)((I & 1) ? ((int32_t)wd >> 16) : (int32_t)(int16_t)(wd & 0xFFFFu));
-}
-
-// limbs j < NW-1 into [0, 2^32) with carries upward (every step exact:
-// integers below 2^48)
-template <int NW>
-__device__ __forceinline__ void normalise(double (&S)[NW]) {
-#pragma unroll
-  for (int j = 0; j < NW - 1; ++j) {
-    const double cy = floor(S[j] * 0x1p-32);
-    S[j] = fma(-cy, 0x1p32, S[j]);
-    S[j + 1] += cy;
-  }
-}
-
 // The staged residue format: 8 outputs of a thread per modulus in a 96-bit
 // record of three 32-bit words, output I in bits 12 I .. 12 I + 11, as
 // u = x + floor(m/2) + 32 (0 <= u <= m + 64 < 2^12 for |x| <= m/2 + 32).
@@ -151,74 +117,6 @@ __device__ __forceinline__ uint32_t slot_bits(const uint3& v) {
 template <int I>
 __device__ __forceinline__ double slot_at(const uint3& v) {
   return (double)slot_bits<I>(v);
-}
-
-// The sums S_j = sum_i x_i W_i[j] of the direct CRT sum, from int16
-// representatives (|x_i| <= 577) or from stored records (S_j starts at
-// -sum_i (floor(m_i/2) + 32) W_i[j] and adds u_i W_i[j]: the same integers,
-// exact at every step, every partial sum below 2^47).
-template <int R, int NW, int I>
-__device__ __forceinline__ void crt_sums(const Oz2Const& c, const uint4 (&x)[R], double (&S)[NW]) {
-#pragma unroll
-  for (int j = 0; j < NW; ++j) S[j] = 0.0;
-#pragma unroll
-  for (int i = 0; i < R; ++i) {
-    const double xi = res_at<I>(x[i]);
-#pragma unroll
-    for (int j = 0; j < NW; ++j) S[j] = fma(xi, c.W[i][j], S[j]);
-  }
-}
-template <int R, int NW, int I>
-__device__ __forceinline__ void crt_sums(const Oz2Const& c, const uint3 (&x)[R], double (&S)[NW]) {
-#pragma unroll
-  for (int j = 0; j < NW; ++j) S[j] = -c.Kw[j];
-#pragma unroll
-  for (int i = 0; i < R; ++i) {
-    const double ui = slot_at<I>(x[i]);
-#pragma unroll
-    for (int j = 0; j < NW; ++j) S[j] = fma(ui, c.W[i][j], S[j]);
-  }
-}
-
-// Exact integer of output I of a thread from its R residues (int16
-// representatives of magnitude <= 577, or stored records):
-// NW words, two's complement, little endian.
-template <int R, int NW, int I, class X>
-__device__ __forceinline__ void crt_words(const Oz2Const& c, const X (&x)[R], uint32_t (&w)[NW]) {
-  double S[NW];
-  crt_sums<R, NW, I>(c, x, S);
-  // quotient estimate q = rint(X / M) from the three top (unnormalised)
-  // limbs: |S_j| < 2^46, |X/M| <= sum |x_i| < 2^14, so the estimate of X/M
-  // is within 2^-36 of the true value; only within that of +-1/2 can q be
-  // off by one, and an exact range check below settles those.
-  double f = fma(S[NW - 2], 0x1p-32, S[NW - 1]);
-  f = fma(S[NW - 3], 0x1p-64, f);
-  f *= c.mtop;
-  const double q = rint(f);
-#pragma unroll
-  for (int j = 0; j < NW; ++j) S[j] = fma(-q, c.Ml[j], S[j]);
-  normalise<NW>(S);
-  if (fabs(f - q) > 0.49999) {
-    // exact range check, X in [-floor(M/2), ceil(M/2) - 1]:
-    //   P = X - M + floor(M/2) >= 0  <=>  X >= ceil(M/2)   -> X -= M
-    //   N = X + floor(M/2) < 0       <=>  X < -floor(M/2)  -> X += M
-    // (the sign of a normalised limb vector is the sign of its top limb)
-    double P[NW], N[NW];
-#pragma unroll
-    for (int j = 0; j < NW; ++j) {
-      P[j] = S[j] - c.Ml[j] + c.Mhalf[j];
-      N[j] = S[j] + c.Mhalf[j];
-    }
-    normalise<NW>(P);
-    normalise<NW>(N);
-    const double adj = (P[NW - 1] >= 0.0) ? -1.0 : ((N[NW - 1] < 0.0) ? 1.0 : 0.0);
-#pragma unroll
-    for (int j = 0; j < NW; ++j) S[j] = fma(adj, c.Ml[j], S[j]);
-    normalise<NW>(S);
-  }
-#pragma unroll
-  for (int j = 0; j < NW - 1; ++j) w[j] = (uint32_t)S[j];
-  w[NW - 1] = (uint32_t)(int32_t)S[NW - 1];
 }
 
 template <int NW>
@@ -461,15 +359,6 @@ __device__ __forceinline__ void crt38_sum(const Oz2Const& c, const double (&xi)[
   if (crt38_reduce<NB>(c, S)) crt38_fix<NB>(c, S);
 }
 
-// from int16 representatives (output I of the thread's eight)
-template <int R, int I, int NB>
-__device__ __forceinline__ void crt38_limbs(const Oz2Const& c, const uint4 (&x)[R],
-                                            double (&S)[NB]) {
-  double xi[R];
-#pragma unroll
-  for (int i = 0; i < R; ++i) xi[i] = res_at<I>(x[i]);
-  crt38_sum<R, NB>(c, xi, S);
-}
 // from stored records: the limb sums start at -K38 (the offsets' share) and
 // add u_i W38[i]: the same exact integers as from the representatives
 template <int R, int I, int NB>

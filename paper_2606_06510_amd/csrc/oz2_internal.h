@@ -30,27 +30,16 @@ struct Oz2Const {
   int rho1[OZ2_MAXR];
   int fin[OZ2_MAXR];          // final epilogue coefficient (1 square, 16 nonsquare)
   float finv[OZ2_MAXR];       // RN(1/m) in fp32
-  float finv_s[OZ2_MAXR];     // RN(1/s) in fp32 (square moduli)
   double dinv[OZ2_MAXR];      // RN(1/m) in fp64
   // direct CRT sum: X = sum_i x_i W_i - q M, W_i = (M/m_i) * ((M/m_i)^-1 mod m_i)
-  double W[OZ2_MAXR][OZ2_NLIMB];  // 32-bit words of W_i (exact integers in fp64)
-  double wfrac[OZ2_MAXR];         // W_i / M = inv_i / m_i rounded to fp64
-  double Ml[OZ2_NLIMB];           // 32-bit words of M
-  double Mhalf[OZ2_NLIMB];        // 32-bit words of floor(M/2)
   int nw;                         // words of the two's complement integer in [-M/2, M/2)
-  double mtop;                    // 2^(32 (nw - 1)) / M, rounded
-  // the same in radix-2^38 limbs: three for r <= 12 (114 bits), four above
-  // (152 bits); the reconstruction's exact integer
+  // in radix-2^38 limbs: three for r <= 12 (114 bits), four above (152 bits)
   double W38[OZ2_MAXR][4];
-  // the same for fin_i W_i mod M = (M/m_i) ((fin_i (M/m_i)^-1) mod m_i): a
-  // representative of C~/fin_i mod m_i times these gives the same sum mod M
-  double W38f[OZ2_MAXR][4];
   double M38[4], Mhalf38[4];
   double mtop38;                  // 2^(38 (limbs - 1)) / M, rounded
   // the staged residues are stored as u_i = x_i + floor(m_i/2) + 32 >= 0:
   // sum_i u_i W_i limb by limb minus these gives sum_i x_i W_i exactly
   double K38[4];                  // sum_i (floor(m_i/2) + 32) W38[i][l] (exact: < 2^52)
-  double Kw[OZ2_NLIMB];           // sum_i (floor(m_i/2) + 32) W[i][j] (exact: < 2^46)
   int cA, cB;                     // width budgets of the scaling rule
   // residue -> plane-bytes tables: entry toff[i] + d for the centred residue d
   int toff[OZ2_MAXR];             // (sum of the earlier moduli) + floor(m_i/2)
@@ -251,27 +240,3 @@ __host__ __device__ inline void oz2_digits(int d, int m, int s, int& d0, int& d1
     }
   }
 }
-
-// ---------------------------------------------------------------- device helpers
-#ifdef __HIPCC__
-// x mod m in [0, m) for |x| < 2^25 (float reciprocal estimate, one correction
-// each way: the estimate of x/m is within 0.02 of the true quotient).
-__device__ __forceinline__ int oz2_mod(int x, int m, float inv) {
-  int q = (int)floorf((float)x * inv);
-  int r = x - q * m;
-  r += (r < 0) ? m : 0;
-  r -= (r >= m) ? m : 0;
-  return r;
-}
-// x - m * rint(x/m): a representative of x mod m with |result| <= m/2 + 2,
-// for |x| < 2^25.
-__device__ __forceinline__ int oz2_red(int x, int m, float inv) {
-  int q = (int)rintf((float)x * inv);
-  return x - q * m;
-}
-// exact centred residue in [-floor(m/2), ceil(m/2) - 1] for |x| < 2^25
-__device__ __forceinline__ int oz2_centre(int x, int m, float inv) {
-  int r = oz2_mod(x, m, inv);
-  return (r >= ((m + 1) >> 1)) ? r - m : r;
-}
-#endif
