@@ -666,6 +666,11 @@ int pool_get(size_t need, void** out) {   // g_pool_mu held by the caller
   return OZ2_OK;
 }
 
+size_t pool_bytes() {   // g_pool_mu held by the caller
+  int dev = 0;
+  return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64 ? g_pool[dev].bytes : 0;
+}
+
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[64];
 
@@ -970,12 +975,19 @@ int ozaki2_dgemm_strided_batched(int m, int n, int k, const double* A, int lda, 
   const bool apart =
       !overlaps(C, ca, A, (size_t)(batch - 1) * strideA * sizeof(double) + span_bytes(m, k, lda)) &&
       !overlaps(C, ca, B, (size_t)(batch - 1) * strideB * sizeof(double) + span_bytes(k, n, ldb));
-  const int side = apart ? (int)std::min<size_t>({(size_t)batch, (size_t)65535,
-                                                  std::max<size_t>(1, kBatchBytes / L.total)})
-                         : 1;
+  int side = apart ? (int)std::min<size_t>({(size_t)batch, (size_t)65535,
+                                            std::max<size_t>(1, kBatchBytes / L.total)})
+                   : 1;
   std::lock_guard<std::mutex> g(g_pool_mu);
+  // fewer side by side where the pool cannot grow: a stream under capture
+  // takes what the pool holds, and memory may be short
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+  if (cap != hipStreamCaptureStatusNone)
+    side = (int)std::min<size_t>(side, std::max<size_t>(1, pool_bytes() / L.total));
   void* ws = nullptr;
   st = pool_get((size_t)side * L.total, &ws);
+  for (; st == OZ2_E_NOMEM && side > 1; st = pool_get((size_t)side * L.total, &ws)) side = (side + 1) / 2;
   if (st != OZ2_OK) return st;
   for (int b = 0; b < batch; b += side) {
     const Oz2Batch bt{std::min(side, batch - b), strideA, strideB, strideC, L.total};

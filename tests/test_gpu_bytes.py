@@ -110,6 +110,44 @@ def test_batches_side_by_side(case):
         assert torch.equal(C[i, :n, :m].t(), D), i
 
 
+def test_blocks_under_capture_take_the_pool_as_it_is():
+    """a batch captured when the internal workspace holds fewer problems than
+    would run side by side: no allocation, the same results on every replay"""
+    import paper_2606_06510_amd as oz
+    import torch
+    dev = device()
+    b, m, n, k, r = 7, 130, 70, 90, 12
+    gen = torch.Generator(device=dev).manual_seed(3)
+    A = torch.rand((b, k, m), generator=gen, dtype=torch.float64, device=dev) - 0.5
+    B = torch.rand((b, n, k), generator=gen, dtype=torch.float64, device=dev) - 0.5
+    A[2, ::2, 5] *= 1e200       # a fallback row in one problem
+    C, D = torch.zeros((b, n, m), dtype=torch.float64, device=dev), None
+
+    def call(count, out, stream=None):
+        oz.ozaki2_dgemm_strided_batched(m, n, k, A, m, m * k, B, k, n * k, out, m, m * n, count, r,
+                                        stream=stream)
+    oz.ozaki2_finalize()
+    call(2, C)                  # the pool holds two problems (1 MiB at least)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call(b, C, stream=side.cuda_stream)
+    seen = []
+    for i in range(3):
+        A.add_(0.25 * i)
+        C.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        seen.append((A.clone(), C.clone()))
+    for Ai, Ci in seen:
+        A.copy_(Ai)
+        D = torch.zeros_like(C)
+        call(b, D)
+        torch.cuda.synchronize()
+        assert torch.equal(Ci, D)
+
+
 @pytest.mark.parametrize("m,n,k", [(64, 64, 64), (1, 1, 1), (17, 64, 3), (64, 15, 33), (50, 49, 64)])
 @pytest.mark.parametrize("r", [8, 11, 12, 13, 16])
 def test_small_batches_digit_counts(m, n, k, r):
