@@ -765,8 +765,9 @@ hipError_t oz2_launch_resgemm(const Oz2Dims& d, const Oz2Layout& L, const Oz2Con
     if (duo) (void)hipFuncSetAttribute((const void*)kern,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     // a tile count below one round: all modulus groups in one launch (one after the
-    // other they leave most CUs idle: 2048^3, 64 tiles, four launches)
-    const int gy = tiles <= cus ? groups : 1;
+    // other they leave most CUs idle: 2048^3, 64 tiles, four launches); a whole round
+    // keeps its launches, whose workgroups start in step (4096^3: 1911 against 1925 us)
+    const int gy = tiles < cus ? groups : 1;
     for (int g = 0; g < groups; g += gy)
       for (int tb = 0; tb < tiles; tb += chunk) {
         const int nt = std::min(chunk, tiles - tb);
