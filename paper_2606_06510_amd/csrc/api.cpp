@@ -596,12 +596,17 @@ int run_bytes(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c, const Oz2
               const Oz2Batch& bt, hipStream_t s) {
   const bool codes = !(d.flags & OZ2_SCALE_FIXED);
   const int both = OZ2_SIDE_A | OZ2_SIDE_B;
-  hipError_t e = oz2_launch_init(d, L, ws, both, bt, s);
-  if (e == hipSuccess)
-    e = codes ? oz2_launch_scan_codes(d, L, ws, A, lda, B, ldb, bt, s)
-              : oz2_launch_scan(d, L, ws, A, lda, B, ldb, both, bt, s);
-  const bool small = codes && oz2_codegemm128_fits(d, bt);
-  if (codes && e == hipSuccess) e = oz2_launch_rebase(d, L, ws, both, small, bt, s);
+  const bool small = codes && oz2_codegemm128_fits(d, bt);   // integer code bytes
+  hipError_t e;
+  if ((small || !codes) && oz2_prep_fits(d, bt)) {
+    e = oz2_launch_prep(d, L, ws, A, lda, B, ldb, codes, bt, s);
+  } else {
+    e = oz2_launch_init(d, L, ws, both, bt, s);
+    if (e == hipSuccess)
+      e = codes ? oz2_launch_scan_codes(d, L, ws, A, lda, B, ldb, bt, s)
+                : oz2_launch_scan(d, L, ws, A, lda, B, ldb, both, bt, s);
+    if (codes && e == hipSuccess) e = oz2_launch_rebase(d, L, ws, both, small, bt, s);
+  }
   if (codes && e == hipSuccess)
     e = small ? oz2_launch_codegemm128(d, L, ws, bt, s) : oz2_launch_codegemm(d, L, ws, bt, s);
   if (e == hipSuccess) e = oz2_launch_byte_split(d, L, c, b, ws, A, lda, B, ldb, bt, s);

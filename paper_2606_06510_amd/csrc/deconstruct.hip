@@ -354,6 +354,94 @@ __global__ void __launch_bounds__(256) k_scan_codes(CodeSide SA, CodeSide SB, in
   else scan_codes_cols(SB, SB.X + (size_t)blockIdx.z * bt.sB, k, nkb, b - nA, z, T);
 }
 
+// Short rows (kp <= 1024), few of them: what init, scan, codes and rebase leave,
+// in one launch instead of three (each 2 to 5 us, bound by its latency, at
+// 256^3).  A workgroup of 1024 threads holds 16 whole rows of A or columns of B
+// in registers, 16 values per thread as four groups of four consecutive k, so
+// each operand is read once, its maxima need no atomics and the codes (bytes
+// 0..16) are formed from the row's exponent directly.  The arrays the later
+// launches accumulate into are cleared for the padded rows too.
+struct PrepSide {
+  const double* X;
+  int ld, rows, rows_pad;
+  unsigned vec;                    // 16-byte loads along k (B)
+  unsigned long long* bits;
+  uint32_t* flags;
+  int32_t* scale;
+  uint32_t* rmax;
+  uint8_t* codes;
+  int* count;
+};
+constexpr int PREP_ROWS = 16, PREP_T = 1024, PREP_K = 1024;
+
+template <bool TRANS, bool CODES>
+__device__ __forceinline__ void prep_rows(const PrepSide& S, const double* __restrict__ X, int k, int kp,
+                                          int blk, size_t z, unsigned long long (*red)[PREP_ROWS]) {
+  const int t = threadIdx.x;
+  // TRANS: 16 lanes on consecutive rows; otherwise a wave per column
+  const int i = TRANS ? t & 15 : t >> 6, q = TRANS ? t >> 4 : t & 63;
+  const int row = blk * PREP_ROWS + i;
+  const bool in = row < S.rows;
+  double x[4][4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int l = 4 * (q + 64 * g);
+    const double* p = X + (TRANS ? (size_t)row + (size_t)l * S.ld : (size_t)l + (size_t)row * S.ld);
+    if (!TRANS && S.vec && in && l + 4 <= k) {
+      const double2 a = reinterpret_cast<const double2*>(p)[0], b = reinterpret_cast<const double2*>(p)[1];
+      x[g][0] = a.x;
+      x[g][1] = a.y;
+      x[g][2] = b.x;
+      x[g][3] = b.y;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[g][e] = (in && l + e < k) ? p[TRANS ? (size_t)e * S.ld : (size_t)e] : 0.0;
+    }
+  }
+  unsigned long long mx = 0;
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) mx = max(mx, abs_bits(x[g][e]));
+  for (int o = 32; o >= (TRANS ? 16 : 1); o >>= 1)
+    mx = max(mx, (unsigned long long)__shfl_xor((long long)mx, o));
+  if (TRANS) {
+    if ((t & 63) < 16) red[t >> 6][i] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < PREP_T / 64; ++w) mx = max(mx, red[w][i]);
+  }
+  if (q == 0) {
+    zws(S.bits, z)[row] = mx;
+    zws(S.flags, z)[row] = 0;
+    zws(S.scale, z)[row] = 0;
+    zws(S.rmax, z)[row] = 0;
+    if (row == 0) *zws(S.count, z) = 0;
+  }
+  if (!CODES) return;
+  const bool none = mx == 0 || mx >= kInfBits;   // zero rows, padding, T1: codes 0
+  const int E = none ? 0 : exp_of_bits(mx);
+  uint8_t* codes = zws(S.codes, z);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int l = 4 * (q + 64 * g);
+    if (l >= kp) continue;
+    uint32_t w = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w |= (none ? 0u : (uint32_t)code_of(x[g][e], E)) << (8 * e);
+    *reinterpret_cast<uint32_t*>(codes + kblocked(row, l, S.rows_pad)) = w;
+  }
+}
+
+template <bool CODES>
+__global__ void __launch_bounds__(PREP_T) k_prep(PrepSide SA, PrepSide SB, int k, int kp, Oz2Batch bt) {
+  __shared__ unsigned long long red[PREP_T / 64][PREP_ROWS];
+  const size_t z = (size_t)blockIdx.z * bt.ws;
+  const int b = blockIdx.x, nA = SA.rows_pad / PREP_ROWS;
+  if (b < nA) prep_rows<true, CODES>(SA, SA.X + (size_t)blockIdx.z * bt.sA, k, kp, b, z, red);
+  else prep_rows<false, CODES>(SB, SB.X + (size_t)blockIdx.z * bt.sB, k, kp, b - nA, z, red);
+}
+
 // code of one byte of step 1 given D = E - Et: with d = min(D + dt, 4), the
 // ceiling above is (q + 2^d - 1 + sticky) >> d for every d in [0, 4]
 __device__ __forceinline__ float rebase_code(uint32_t y, int D) {
@@ -622,6 +710,30 @@ hipError_t oz2_launch_init(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, in
   unsigned blocks = (unsigned)((n + 255) / 256);
   hipLaunchKernelGGL(k_init, dim3(blocks, 1, bt.count), dim3(256), 0, s, ws, L, d.mp, d.np, d.cslabs,
                      side, bt.ws);
+  return hipGetLastError();
+}
+
+// Rows that fit a workgroup's registers, and few enough that launches count (us
+// per product, three launches -> one: 256^3 37.9 -> 29.3, 777 x 1301 x 995 87.0 ->
+// 77.7, 24 x (200 x 136 x 300) 72.0 -> 63.4, 60000 x 64 x 1000 663 -> 634).  At the
+// upper end it no longer matters: 8192^2 x 512 (fixed scaling) 945.4 -> 944.5, 20000 x
+// 24000 x 1024 6833.9 -> 6833.7.
+bool oz2_prep_fits(const Oz2Dims& d, const Oz2Batch& bt) {
+  return d.kp <= PREP_K && d.cslabs == 1 && (long long)(d.mp + d.np) * bt.count <= 1ll << 16;
+}
+
+hipError_t oz2_launch_prep(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, const double* A, int lda,
+                           const double* B, int ldb, bool codes, const Oz2Batch& bt, hipStream_t s) {
+  const unsigned vec = ((uintptr_t)B % 16 == 0 && ldb % 2 == 0 && bt.sB % 2 == 0) ? 1u : 0u;
+  const PrepSide SA{A, lda, d.m, d.mp, 0u, (unsigned long long*)(ws + L.rowbits),
+                    (uint32_t*)(ws + L.flagsA), (int32_t*)(ws + L.sA), (uint32_t*)(ws + L.Rmax),
+                    ws + L.codesA, (int*)(ws + L.counters)};
+  const PrepSide SB{B, ldb, d.n, d.np, vec, (unsigned long long*)(ws + L.colbits),
+                    (uint32_t*)(ws + L.flagsB), (int32_t*)(ws + L.tB), (uint32_t*)(ws + L.Kmax),
+                    ws + L.codesB, (int*)(ws + L.counters) + 1};
+  auto kern = codes ? k_prep<true> : k_prep<false>;
+  hipLaunchKernelGGL(kern, dim3((d.mp + d.np) / PREP_ROWS, 1, bt.count), dim3(PREP_T), 0, s, SA, SB, d.k,
+                     d.kp, bt);
   return hipGetLastError();
 }
 

@@ -150,6 +150,11 @@ hipError_t oz2_launch_scan_codes(const Oz2Dims& d, const Oz2Layout& L, uint8_t* 
 // integers: code bytes 0..16 instead of their E4M3 encodings
 hipError_t oz2_launch_rebase(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, int side,
                              bool integers, const Oz2Batch& bt, hipStream_t s);
+// init, scan, codes (integers) and rebase in one launch, for short rows and few
+// of them; without `codes` init and scan only
+bool oz2_prep_fits(const Oz2Dims& d, const Oz2Batch& bt);
+hipError_t oz2_launch_prep(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, const double* A, int lda,
+                           const double* B, int ldb, bool codes, const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_codegemm(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, const Oz2Batch& bt, hipStream_t s);
 // the code products on integer code bytes in 128 x 128 tiles, where that is faster
 bool oz2_codegemm128_fits(const Oz2Dims& d, const Oz2Batch& bt);

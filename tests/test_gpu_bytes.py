@@ -110,6 +110,24 @@ def test_batches_side_by_side(case):
         assert torch.equal(C[i, :n, :m].t(), D), i
 
 
+# the one-launch scan and codes of short rows: whole and partial groups of four
+# k, its last k and the first beyond it, partial blocks of 16 rows, odd leading
+# dimensions, scales by the products' maxima and fixed
+@pytest.mark.parametrize("m,n,k,pad", [(1, 17, 1, 0), (16, 33, 3, 1), (255, 240, 64, 0), (257, 130, 255, 3),
+                                       (100, 300, 1021, 2), (300, 100, 1024, 0), (129, 64, 1025, 0)])
+@pytest.mark.parametrize("flags", [0, 2])
+def test_short_rows_scan(m, n, k, pad, flags):
+    def edit(A, B):
+        A[m // 2] = 0.0
+        A[m - 1, k - 1] *= 2.0 ** 900
+        B[k // 2, n - 1] = np.inf
+        B[k - 1, n // 2] = 2.0 ** -1060        # a subnormal entry beside normal ones
+        if m > 8:
+            A[5] = 2.0 ** -1062 * np.arange(k)  # a row of subnormals
+            A[3, 0] = np.nan
+    _same(*_both(m, n, k, 12, flags=flags, seed=m, pad=pad, edit=edit))
+
+
 def test_blocks_under_capture_take_the_pool_as_it_is():
     """a batch captured when the internal workspace holds fewer problems than
     would run side by side: no allocation, the same results on every replay"""
