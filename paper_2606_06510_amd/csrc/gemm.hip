@@ -25,6 +25,7 @@
 // the exact integer accumulator is reduced mod m and multiplied by
 // c_this / c_next (mod m), so the next product continues the same residue.
 #include <algorithm>
+#include <type_traits>
 
 #include "oz2_tile.h"
 
@@ -448,7 +449,7 @@ __device__ __forceinline__ void store_residues_pair(uint32_t* wb, const uint32_t
 // continuous DMA stream.
 // CH bit 0: square moduli, bit 1: nonsquare moduli take the first chain
 // transition as a plain multiply (every modulus of that kind has k <= kcheap)
-template <int CH>
+template <int CH, bool MERGE>
 __global__ void __launch_bounds__(NT, 1)
 k_resgemm(Oz2Const c, const uint8_t* __restrict__ PA, const uint8_t* __restrict__ PB, int mp,
           int np, int kp, int kbeg, int kend, int accumulate, int mpw, int mgroup, int tbase,
@@ -457,7 +458,7 @@ k_resgemm(Oz2Const c, const uint8_t* __restrict__ PA, const uint8_t* __restrict_
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)LB;
   const int ntm = mp / TILE, ntn = np / TILE;
   const int tile = tile_of(tbase + blockIdx.x, ntm, ntn);
-  const int mi0 = (mgroup + (int)blockIdx.y) * mpw, mi1 = min(c.r, mi0 + mpw);
+  const int mi0 = (MERGE ? mgroup + (int)blockIdx.y : mgroup) * mpw, mi1 = min(c.r, mi0 + mpw);
   const int tm = tile % ntm, tn = tile / ntm;
   Ctx x;
   x.psA = (size_t)mp * kp;
@@ -615,7 +616,7 @@ __device__ __forceinline__ void duo_run(const Oz2Const* c, const Ctx& x, DuoDma&
 // grid: 2 x (tiles tbase .. tbase + gridDim.x / 2 - 1), the two halves of a
 // tile on the same XCD (blocks b and b + 8); the tile count of a launch is a
 // multiple of 8.
-template <int CH>
+template <int CH, bool MERGE>
 __global__ void __launch_bounds__(DNT, 2)
 k_resgemm_duo(Oz2Const c, const uint8_t* __restrict__ PA, const uint8_t* __restrict__ PB, int mp,
               int np, int kp, int kbeg, int kend, int accumulate, int mpw, int mgroup, int tbase,
@@ -625,7 +626,7 @@ k_resgemm_duo(Oz2Const c, const uint8_t* __restrict__ PA, const uint8_t* __restr
   const int ntm = mp / TILE, ntn = np / TILE;
   const int b = blockIdx.x, slot = b >> 3, half = slot & 1;
   const int tile = tile_of(tbase + (slot >> 1) * 8 + (b & 7), ntm, ntn);
-  const int mi0 = (mgroup + (int)blockIdx.y) * mpw, mi1 = min(c.r, mi0 + mpw);
+  const int mi0 = (MERGE ? mgroup + (int)blockIdx.y : mgroup) * mpw, mi1 = min(c.r, mi0 + mpw);
   const int tm = tile % ntm, tn = tile / ntm;
   Ctx x;
   x.psA = (size_t)mp * kp;
@@ -757,17 +758,23 @@ hipError_t oz2_launch_resgemm(const Oz2Dims& d, const Oz2Layout& L, const Oz2Con
     typedef void (*Kern)(Oz2Const, const uint8_t*, const uint8_t*, int, int, int, int, int, int,
                          int, int, int, uint32_t*);
     const bool duo = oz2_pair_records(d);
-    Kern kern = duo ? (ch == 3 ? k_resgemm_duo<3> : ch == 2 ? k_resgemm_duo<2>
-                       : ch == 1 ? k_resgemm_duo<1> : k_resgemm_duo<0>)
-                    : (ch == 3 ? k_resgemm<3> : ch == 2 ? k_resgemm<2>
-                       : ch == 1 ? k_resgemm<1> : k_resgemm<0>);
+    // a tile count below one round: all modulus groups in one launch (one after the
+    // other they leave most CUs idle: 2048^3, 64 tiles, four launches), by kernels
+    // of their own: the group index in the common ones moved their loops' code and
+    // took operand-stationary 4096^3 from 1911 to 1925 us
+    const bool merge = tiles < cus;
+    const int gy = merge ? groups : 1;
+    auto pick = [&](auto m) -> Kern {
+      constexpr bool M = decltype(m)::value;
+      return duo ? (ch == 3 ? k_resgemm_duo<3, M> : ch == 2 ? k_resgemm_duo<2, M>
+                    : ch == 1 ? k_resgemm_duo<1, M> : k_resgemm_duo<0, M>)
+                 : (ch == 3 ? k_resgemm<3, M> : ch == 2 ? k_resgemm<2, M>
+                    : ch == 1 ? k_resgemm<1, M> : k_resgemm<0, M>);
+    };
+    Kern kern = merge ? pick(std::true_type{}) : pick(std::false_type{});
     const int lds = duo ? DNB * DSTB : 0;
     if (duo) (void)hipFuncSetAttribute((const void*)kern,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    // a tile count below one round: all modulus groups in one launch (one after the
-    // other they leave most CUs idle: 2048^3, 64 tiles, four launches); a whole round
-    // keeps its launches, whose workgroups start in step (4096^3: 1911 against 1925 us)
-    const int gy = tiles < cus ? groups : 1;
     for (int g = 0; g < groups; g += gy)
       for (int tb = 0; tb < tiles; tb += chunk) {
         const int nt = std::min(chunk, tiles - tb);
