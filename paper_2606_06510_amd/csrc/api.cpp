@@ -617,8 +617,8 @@ int run_bytes(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c, const Oz2
     return hip_status(e);
   }
   if (e == hipSuccess) e = oz2_launch_bytegemm(d, L, b, ws, bt, s);
-  if (e == hipSuccess) e = oz2_launch_byte_crt(d, L, b, ws, A, lda, C, ldc, bt, s);
-  if (e == hipSuccess && !(d.flags & OZ2_NO_FALLBACK))
+  if (e == hipSuccess) e = oz2_launch_byte_crt(d, L, b, ws, A, lda, B, ldb, C, ldc, bt, s);
+  if (e == hipSuccess && !(d.flags & OZ2_NO_FALLBACK) && !oz2_byte_crt_takes_fallback(d, bt))
     e = oz2_launch_fallback(d, L, ws, A, lda, B, ldb, C, ldc, bt, s);
   return hip_status(e);
 }

@@ -6,6 +6,7 @@
 #include <algorithm>
 
 #include "oz2_device.h"
+#include "oz2_fallback.h"
 
 namespace {
 
@@ -154,13 +155,28 @@ k_byte_split(Oz2Byte c, ByteSide SA, ByteSide SB, int k, int kp, unsigned quant_
 // (see bytegemm.hip); moduli outermost, so that each is loaded and used once
 // and its weights stay in scalar registers.  The results go through LDS, so
 // that a store instruction writes 512 contiguous bytes of a column.
-template <int N, bool ACC>
+//
+// FB: the workgroups from ncrt on are the native fallback's, which write
+// the flagged entries that the others leave (A read directly, no panel).
+template <int N, bool ACC, bool FB>
 __global__ void __launch_bounds__(256)
 k_byte_crt(Oz2Byte c, Oz2Dims d, const uint8_t* __restrict__ res, const int32_t* __restrict__ sA,
            const int32_t* __restrict__ tB, const uint32_t* __restrict__ fA,
            const uint32_t* __restrict__ fB, double* C, int ldc, const double* __restrict__ A,
            int lda, const int* __restrict__ counters, const int* __restrict__ listA,
-           double* __restrict__ panel, int cap, int nrow, Oz2Batch bt) {
+           double* __restrict__ panel, int cap, int nrow, const double* __restrict__ B, int ldb,
+           const int* __restrict__ listB, int ncrt, Oz2Batch bt) {
+  if constexpr (FB) {
+    if ((int)blockIdx.x >= ncrt) {
+      __shared__ FbShared fs;
+      const size_t z = (size_t)blockIdx.z * bt.ws;
+      const int na = zws(counters, z)[0], nb = zws(counters, z)[1];
+      fallback_tiles<32>(fs, d, A + (size_t)blockIdx.z * bt.sA, lda, B + (size_t)blockIdx.z * bt.sB, ldb,
+                         C + (size_t)blockIdx.z * bt.sC, ldc, na, nb, zws(listA, z), zws(listB, z),
+                         zws(fA, z), nullptr, 0, (int)blockIdx.x - ncrt, (int)gridDim.x - ncrt);
+      return;
+    }
+  }
   constexpr int NB = N <= 15 ? 3 : 4;
   __shared__ double tr[16][129];
   const size_t z = (size_t)blockIdx.z * bt.ws;
@@ -250,18 +266,26 @@ k_byte_crt(Oz2Byte c, Oz2Dims d, const uint8_t* __restrict__ res, const int32_t*
   }
 }
 
+int crt_blocks(const Oz2Dims& d) { return ((d.m + 127) / 128) * ((d.n + 15) / 16); }
+
 template <int N>
 void launch_crt_n(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
-                  const double* A, int lda, double* C, int ldc, const Oz2Batch& bt, hipStream_t s) {
-  const int nrow = (d.m + 127) / 128, ncol = (d.n + 15) / 16;
-  const bool gather = !(d.flags & 8u);   // OZ2_NO_FALLBACK: no fallback, no panel
-  auto kern = (d.flags & 1u) ? k_byte_crt<N, true> : k_byte_crt<N, false>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((size_t)nrow * ncol), 1, bt.count), dim3(256), 0, s, c, d,
+                  const double* A, int lda, const double* B, int ldb, double* C, int ldc,
+                  const Oz2Batch& bt, hipStream_t s) {
+  const int nrow = (d.m + 127) / 128, ncrt = crt_blocks(d);
+  const bool fb = oz2_byte_crt_takes_fallback(d, bt);
+  // OZ2_NO_FALLBACK: no fallback, no panel
+  const bool gather = !(d.flags & 8u) && !fb;
+  const bool acc = (d.flags & 1u) != 0;
+  auto kern = fb ? (acc ? k_byte_crt<N, true, true> : k_byte_crt<N, false, true>)
+                 : (acc ? k_byte_crt<N, true, false> : k_byte_crt<N, false, false>);
+  const int nfb = fb ? std::max(1, std::min(2 * ((d.m + 63) / 64) * ((d.n + 31) / 32), 256 / bt.count)) : 0;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(ncrt + nfb), 1, bt.count), dim3(256), 0, s, c, d,
                      ws + L.res, (const int32_t*)(ws + L.sA), (const int32_t*)(ws + L.tB),
                      (const uint32_t*)(ws + L.flagsA), (const uint32_t*)(ws + L.flagsB), C, ldc, A,
                      lda, (const int*)(ws + L.counters), (const int*)(ws + L.listA),
                      gather ? (double*)(ws + L.panel) : nullptr, d.mp < OZ2_FBCAP ? d.mp : OZ2_FBCAP,
-                     nrow, bt);
+                     nrow, B, ldb, (const int*)(ws + L.listB), ncrt, bt);
 }
 
 }  // namespace
@@ -293,19 +317,26 @@ hipError_t oz2_launch_byte_split(const Oz2Dims& d, const Oz2Layout& L, const Oz2
   return hipGetLastError();
 }
 
+// One launch less where few workgroups reconstruct (us per product: 256^3 29.2 -> 28.1,
+// 24 x (200 x 136 x 300), 432 workgroups, 63.9 -> 61.1); the fallback's registers and LDS
+// cost the others more once they share CUs (777 x 1301 x 995, 574: 77.8 -> 78.5).
+bool oz2_byte_crt_takes_fallback(const Oz2Dims& d, const Oz2Batch& bt) {
+  return !(d.flags & 8u) && (long long)crt_blocks(d) * bt.count <= 2ll * oz2_device_cus();
+}
+
 hipError_t oz2_launch_byte_crt(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
-                               const double* A, int lda, double* C, int ldc, const Oz2Batch& bt,
-                               hipStream_t s) {
+                               const double* A, int lda, const double* B, int ldb, double* C, int ldc,
+                               const Oz2Batch& bt, hipStream_t s) {
   switch (c.n) {
-    case 10: launch_crt_n<10>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
-    case 11: launch_crt_n<11>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
-    case 12: launch_crt_n<12>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
-    case 13: launch_crt_n<13>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
-    case 15: launch_crt_n<15>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
-    case 16: launch_crt_n<16>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
-    case 17: launch_crt_n<17>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
-    case 18: launch_crt_n<18>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
-    case 19: launch_crt_n<19>(d, L, c, ws, A, lda, C, ldc, bt, s); break;
+    case 10: launch_crt_n<10>(d, L, c, ws, A, lda, B, ldb, C, ldc, bt, s); break;
+    case 11: launch_crt_n<11>(d, L, c, ws, A, lda, B, ldb, C, ldc, bt, s); break;
+    case 12: launch_crt_n<12>(d, L, c, ws, A, lda, B, ldb, C, ldc, bt, s); break;
+    case 13: launch_crt_n<13>(d, L, c, ws, A, lda, B, ldb, C, ldc, bt, s); break;
+    case 15: launch_crt_n<15>(d, L, c, ws, A, lda, B, ldb, C, ldc, bt, s); break;
+    case 16: launch_crt_n<16>(d, L, c, ws, A, lda, B, ldb, C, ldc, bt, s); break;
+    case 17: launch_crt_n<17>(d, L, c, ws, A, lda, B, ldb, C, ldc, bt, s); break;
+    case 18: launch_crt_n<18>(d, L, c, ws, A, lda, B, ldb, C, ldc, bt, s); break;
+    case 19: launch_crt_n<19>(d, L, c, ws, A, lda, B, ldb, C, ldc, bt, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -203,9 +203,11 @@ hipError_t oz2_launch_byte_split(const Oz2Dims& d, const Oz2Layout& L, const Oz2
                                  const double* B, int ldb, const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_bytegemm(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
                                const Oz2Batch& bt, hipStream_t s);
+// (where few workgroups: the fallback itself in the same launch)
+bool oz2_byte_crt_takes_fallback(const Oz2Dims& d, const Oz2Batch& bt);
 hipError_t oz2_launch_byte_crt(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
-                               const double* A, int lda, double* C, int ldc, const Oz2Batch& bt,
-                               hipStream_t s);
+                               const double* A, int lda, const double* B, int ldb, double* C, int ldc,
+                               const Oz2Batch& bt, hipStream_t s);
 // the products and the reconstruction in one kernel, where that is the faster
 // route (short k: see the definition); the fallback then reads A directly
 bool oz2_byte_fused_fits(const Oz2Dims& d, const Oz2Byte& c);

@@ -228,3 +228,17 @@ def test_fused_short_k_subnormal_and_small_integers():
     _same(x, y)
     small = np.abs(x[:300, :400])
     assert np.count_nonzero(small < 2.0 ** -1022) > 1000 and np.count_nonzero(small >= 2.0 ** -1022) > 100
+
+
+# the fallback inside the reconstruction's launch (up to two of its workgroups
+# per CU: 1024 x 1024) and in a launch of its own beyond: flagged rows and
+# columns, more of them than one tile, C_in, all rows, none
+@pytest.mark.parametrize("m,n,k", [(1, 18, 5), (200, 333, 70), (1024, 1024, 96), (1024, 1040, 96)])
+@pytest.mark.parametrize("flags", [0, 1, 8, 17])
+def test_fallback_beside_the_reconstruction(m, n, k, flags):
+    def edit(A, B):
+        A[m // 3:m // 3 + 70, ::2] *= 1e200   # T2
+        A[m - 1, k - 1] = np.inf              # T1
+        B[1, n // 2] = np.nan
+        B[::2, n - 1] *= 1e-200
+    _same(*_both(m, n, k, 12, flags=flags, seed=n, pad=1, edit=edit))
