@@ -380,10 +380,9 @@ Oz2Layout make_byte_layout(const Oz2Dims& d, const Oz2Byte& c) {
 constexpr size_t kBatchBytes = (size_t)512 << 20;
 
 // ------------------------------------------------------------ batched GEMV
-// Y = A X with X of nrhs <= 16 columns (the fused kernel of gemv.hip): k in
-// chunks of 128, 128 rows of A per workgroup, and enough k-splits that every
-// split spans at most 32768 k (exact FP32 accumulation) and the row blocks
-// times the splits cover about 256 workgroups.
+// Y = A X with X of nrhs <= 16 columns (gemv.hip): the padded sizes, and enough
+// k-splits that every split spans at most 32768 k (a wave's int32 sums stay
+// exact) and the row blocks times the splits cover about 256 workgroups.
 constexpr int kGemvRhs = 16, kGemvK = 128, kGemvRows = 128;
 
 struct GemvShape {
@@ -429,6 +428,8 @@ Oz2Layout make_gemv_layout(const GemvShape& g, const Oz2Const& c) {
   L.counters = take(64);
   L.listA = take((size_t)d.mp * 4);
   L.listB = take((size_t)d.np * 4);
+  // (the sizes of X's digits and the splits' integers are upper bounds: the
+  // workspace a caller sized once stays valid)
   L.tabs = take((size_t)c.tabsz * 4);
   L.xfrag = take((size_t)g.chunks * c.P * 2048);
   L.part = take((size_t)g.splits * c.r * d.mp * kGemvRhs * 2);
