@@ -454,7 +454,8 @@ __device__ __forceinline__ float rebase_code(uint32_t y, int D) {
 // one k-block (threads [0, nA) on A, then B), four 16-byte loads in flight.
 // Since d = min(D + dt, 4) depends on D only through min(D, 4), the E4M3 code
 // of every byte for every D is a 5 x 256-byte table, built per workgroup in
-// LDS; a byte then costs a shift, an add and one LDS byte read.
+// LDS; a byte then costs a shift, an add and one LDS byte read.  (An all-zero
+// segment's D may be negative: oz2_rebase_row.)
 __global__ void __launch_bounds__(256) k_rebase(uint8_t* codesA, const int16_t* __restrict__ etA,
                                                 const unsigned long long* __restrict__ bitsA,
                                                 int mp, size_t nA, uint8_t* codesB,
@@ -499,7 +500,7 @@ __global__ void __launch_bounds__(256) k_rebase(uint8_t* codesA, const int16_t* 
     for (int u = 0; u < 4; ++u) q[u] = make_uint4(0u, 0u, 0u, 0u);
     return;
   }
-  const uint8_t* t = lut + 256 * min(exp_of_bits(b) - et_i, 4);
+  const uint8_t* t = lut + 256 * oz2_rebase_row(exp_of_bits(b), et_i);
   auto word = [t](uint32_t w) {
     return (uint32_t)t[w & 0xFFu] | ((uint32_t)t[(w >> 8) & 0xFFu] << 8) |
            ((uint32_t)t[(w >> 16) & 0xFFu] << 16) | ((uint32_t)t[w >> 24] << 24);

@@ -220,6 +220,16 @@ hipError_t oz2_launch_batched(const Oz2Const& c, int m, int n, int k, int batch,
                               int lda, long long sA, const double* B, int ldb, long long sB,
                               double* C, int ldc, long long sC, uint32_t* iout, hipStream_t s);
 
+// ---------------------------------------------------------------- code rebase
+// Row of k_rebase's table for a 64-k segment whose own maximum has exponent Et
+// (0 where all of it is zero) in a row whose maximum has exponent E: min(E - Et, 4).
+// An all-zero segment of a row below 1/2 has Et = 0 > E; its bytes are zero, of
+// code 0 in every row of the table, so row 0 serves it.
+__host__ __device__ inline int oz2_rebase_row(int E, int Et) {
+  const int d = E - Et;
+  return d < 0 ? 0 : d > 4 ? 4 : d;
+}
+
 // ---------------------------------------------------------------- digit rule
 // Digit planes of a centred residue d of m (the E4M3-exact layouts of the
 // "frozen plane kernel" section):

@@ -128,6 +128,30 @@ def test_short_rows_scan(m, n, k, pad, flags):
     _same(*_both(m, n, k, 12, flags=flags, seed=m, pad=pad, edit=edit))
 
 
+@pytest.mark.parametrize("flags", [0, 32])   # 32: OZ2_KEEP_RESIDUES, the plane route
+def test_zero_blocks_in_rows_of_small_entries(flags):
+    """rows and columns below 1/2 with whole zero blocks of 64 k (banded,
+    block-sparse operands), beyond the rows that one workgroup holds: exact
+    against the oracle"""
+    import oracle
+    import paper_2606_06510_amd as oz
+    rng = np.random.default_rng(9)
+    m, n, k = 70, 66, 1300
+    A, B = 1e-3 * (rng.random((m, k)) + 0.1), 1e-12 * (rng.random((k, n)) + 0.1)
+    A[:, 64:128] = 0.0
+    A[5, 128:1280] = 0.0
+    A[6, :1280] = 0.0
+    A[7] *= 1e-290
+    B[640:704, ::2] = 0.0
+    B[192:256, 3] *= 1e-3
+    dev = device()
+    C = oz.matmul(oz.to_device_colmajor(A, dev), oz.to_device_colmajor(B, dev), 12, flags=flags)
+    got, res = oz.from_device_colmajor(C), oracle.dgemm(A, B, 12)
+    emu = (~np.isin(np.arange(m), res.fallback_rows))[:, None] & ~np.isin(np.arange(n), res.fallback_cols)
+    assert emu.mean() > 0.9
+    assert np.array_equal(bits(got)[emu], bits(res.C)[emu])
+
+
 def test_blocks_under_capture_take_the_pool_as_it_is():
     """a batch captured when the internal workspace holds fewer problems than
     would run side by side: no allocation, the same results on every replay"""

@@ -10,6 +10,8 @@ path runs (GPU):
   (Eq. (garner)) and the rounded values its correctly rounded quotient;
 * the single-launch batched kernel, in its integer-writing instantiation,
   must form the oracle's integers for every unflagged output;
+* and its rounding must be the correctly rounded quotient of those integers
+  next to the magnitudes where a join of its limbs leaves the exact range;
 * a plan created with OZ2_TIME_STAGES reports six stage times and its
   results stay bit-exact."""
 import numpy as np
@@ -107,6 +109,61 @@ def test_batched_kernel_integers(r):
                     assert int(got[b, j, i]) == 0
                 else:
                     assert int(got[b, j, i]) == int(res.X[i, j]), (b, i, j)
+
+
+def _near_power(r, bound, rng, count):
+    """A [count][3], B [count][3] whose exact integers A~ B~ are +-2^bound plus or
+    minus offsets below 2^(bound - 21).  a1 and b2 set the scales (codes 16 beside
+    ones, so the widths do not depend on the small entries); a1 b1 comes near the
+    target, a3 b3 closes all but the last 32 bits."""
+    top = np.array([1.0 - 2.0 ** -20, 2.0 ** -40, 2.0 ** -40])
+    t = oracle.dgemm(top[None, :], top[[1, 0, 2], None], r)
+    s, u = int(t.sA[0]), int(t.tB[0])
+    A, B, X = np.zeros((count, 3)), np.zeros((count, 3)), []
+    for q in range(count):
+        near = int(rng.integers(1, 1 << 52)) << max(0, int(rng.integers(0, bound - 72)))
+        goal = (1 << bound) + (near if q % 4 == 3 else -near)
+        a1 = int(np.ldexp(1.0 - int(rng.integers(1, 1 << 20)) * 2.0 ** -40, s))
+        b2 = int(np.ldexp(1.0 - int(rng.integers(1, 1 << 20)) * 2.0 ** -40, u))
+        a2, a3 = int(rng.integers(1, 4)), int(rng.integers(1 << 30, 1 << 31))
+        b1 = (goal - a2 * b2) // a1
+        b3 = (goal - a2 * b2 - a1 * b1) // a3
+        sign = 1 if q % 2 else -1
+        A[q] = [np.ldexp(float(sign * v), -s) for v in (a1, a2, a3)]
+        B[q] = [np.ldexp(float(v), -u) for v in (b1, b2, b3)]
+        X.append(sign * (a1 * b1 + a2 * b2 + a3 * b3))
+    return A, B, X, s, u
+
+
+def _batch_of_dots(A, B, r):
+    import torch
+    import paper_2606_06510_amd as oz
+    dev = device()
+    nb, k = A.shape
+    Ad, Bd = torch.from_numpy(A).to(dev), torch.from_numpy(B).to(dev)
+    C = torch.zeros(nb, dtype=torch.float64, device=dev)
+    oz.ozaki2_dgemm_strided_batched(1, 1, k, Ad, 1, k, Bd, k, k, C, 1, 1, nb, r)
+    torch.cuda.synchronize()
+    return C.cpu().numpy()
+
+
+@pytest.mark.parametrize("r,bound", [(9, 77), (10, 77), (11, 77), (12, 77), (13, 77), (13, 109),
+                                     (14, 109), (16, 77), (16, 109)])
+def test_batched_kernel_rounding_next_to_its_joins(r, bound):
+    """k_batched joins limbs of 2^88, 2^56, 2^24; a joined value of -2^21 in front
+    of the next limb is where the sum falls to just under 2^53"""
+    A, B, X, s, u = _near_power(r, bound, np.random.default_rng(r), 256)
+    for q in range(0, 256, 16):       # the crafted integers are the path's
+        assert int(oracle.dgemm(A[q][None, :], B[q][:, None], r).X[0, 0]) == X[q]
+    want = np.array([garner.round_scaled(x, s + u) for x in X])
+    assert np.array_equal(bits(_batch_of_dots(A, B, r)), bits(want))
+
+
+def test_batched_kernel_rounding_of_one_product():
+    A, B = np.array([[-0.9999999432648118]]), np.array([[0.9999998702456414]])
+    want = oracle.dgemm(A, B, 12).C
+    assert want[0, 0] == -0.9999998135104605
+    assert np.array_equal(bits(_batch_of_dots(A, B, 12)), bits(want[0]))
 
 
 def test_stage_times_query():
