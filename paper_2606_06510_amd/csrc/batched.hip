@@ -165,10 +165,12 @@ __device__ __forceinline__ void limbs4_words(const double (&S)[4], uint32_t (&w)
 }
 
 // RN-even binary64 value of X 2^-e from normalised limbs, rounded once: limbs
-// are joined from the top while the joined value is below 2^21 (the join stays
-// exact below 2^53); the first join beyond that adds the next limb and, as a
-// half, whether anything below it is nonzero (at 2^53 and above rounding
-// boundaries fall on integers).  Subnormal results take the word routine.
+// are joined from the top while the joined value is in [-2^21, 2^21) (the join
+// stays exact: at most 2^53 in magnitude); the first join beyond that adds the
+// next limb and, as a half, whether anything below it is nonzero (at 2^53 and
+// above rounding boundaries fall on integers).  -2^21 belongs to the exact
+// joins: with the next limb it lies below 2^53 in magnitude, where a half is
+// itself a boundary.  Subnormal results take the word routine.
 __device__ __forceinline__ double round4(const double (&S)[4], int e) {
   double v = S[3];
   int sh = 88;
@@ -176,7 +178,7 @@ __device__ __forceinline__ double round4(const double (&S)[4], int e) {
 #pragma unroll
   for (int j = 2; j >= 0; --j) {
     const bool rest = j == 2 ? (S[1] != 0.0 || S[0] != 0.0) : (j == 1 && S[0] != 0.0);
-    const bool small = fabs(v) < 0x1p21;
+    const bool small = v >= -0x1p21 && v < 0x1p21;
     const double next = fma(v, j == 0 ? 0x1p24 : 0x1p32, S[j] + ((!small && rest) ? 0.5 : 0.0));
     v = done ? v : next;
     sh = done ? sh : (j == 2 ? 56 : j == 1 ? 24 : 0);
