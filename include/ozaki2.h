@@ -101,7 +101,10 @@ enum {
  * Uses a library-internal, grow-only workspace per device (hipMalloc'd on
  * first use and when a call needs more; released by ozaki2_finalize).  Calls
  * on one device share it, so concurrent calls on different streams must use
- * ozaki2_dgemm_ex with workspaces of their own.
+ * ozaki2_dgemm_ex with workspaces of their own.  A call under stream capture
+ * takes the workspace as it is; the graph replays on that memory, which later
+ * calls that need more leave allocated until ozaki2_finalize (replay the graph
+ * no more after it, and not concurrently with other calls of the device).
  * Returns OZ2_OK or an error code; on error nothing is enqueued. */
 int ozaki2_dgemm(int m, int n, int k, const double* A, int lda, const double* B,
                  int ldb, double* C, int ldc, int num_moduli, void* stream);
@@ -138,7 +141,8 @@ int ozaki2_dgemm_static(int m, int n, int k, const double* A, int lda, const dou
 /* batch independent products C_b = A_b * B_b, A_b = A + b*strideA (elements),
  * likewise B_b, C_b; each with the layout rules above.  Strides must keep the
  * output matrices disjoint.  Internal workspace as for ozaki2_dgemm; beyond
- * 64 x 64 x 64 as many problems run side by side as 512 MiB of it hold. */
+ * 64 x 64 x 64 as many problems run side by side as 512 MiB of it hold (under
+ * stream capture, as many as the workspace held at that time). */
 int ozaki2_dgemm_strided_batched(int m, int n, int k, const double* A, int lda,
                                  long long strideA, const double* B, int ldb,
                                  long long strideB, double* C, int ldc,
@@ -245,7 +249,8 @@ int ozaki2_plan_query(ozaki2_plan_t plan, int what, void* host_out, size_t bytes
 
 const char* ozaki2_status_string(int status);
 
-/* Releases the internal workspaces of ozaki2_dgemm (synchronises). */
+/* Releases the internal workspaces of ozaki2_dgemm and
+ * ozaki2_dgemm_strided_batched, those of captured graphs too (synchronises). */
 void ozaki2_finalize(void);
 
 #ifdef __cplusplus

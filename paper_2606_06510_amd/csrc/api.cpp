@@ -14,6 +14,7 @@
 #include "../../include/ozaki2.h"
 #include "../../include/ozaki2_probes.h"
 #include "oz2_internal.h"
+#include "oz2_pool.h"
 
 namespace {
 
@@ -638,38 +639,39 @@ int run_reconstruct(ozaki2_plan_s& p, double* C, int ldc, hipStream_t s) {
   return hip_status(e);
 }
 
-// internal grow-only workspace of ozaki2_dgemm, per device.  Callers hold
-// g_pool_mu from pool_get until their work is enqueued: a grow synchronises
-// the device before it frees the old buffer, so work enqueued under the lock
-// has finished with it by then, whichever thread grows the pool next.
-struct Pool {
-  void* ptr = nullptr;
-  size_t bytes = 0;
-};
+// internal grow-only workspace of ozaki2_dgemm, per device (oz2_pool.h).
+// Callers hold g_pool_mu from pool_get until their work is enqueued: a grow
+// synchronises the device before it frees the old buffer, so work enqueued
+// under the lock has finished with it by then, whichever thread grows the pool
+// next.
 std::mutex g_pool_mu;
-Pool g_pool[64];
+Oz2Pool g_pool[64];
 
-int pool_get(size_t need, void** out) {   // g_pool_mu held by the caller
+struct HipMem {
+  bool alloc(void** p, size_t bytes) {
+    if (hipMalloc(p, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+  }
+  void free(void* p) { (void)hipFree(p); }
+  bool sync() { return hipDeviceSynchronize() == hipSuccess; }
+};
+
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+  return cap != hipStreamCaptureStatusNone;
+}
+
+int pool_get(size_t need, bool under_capture, void** out) {   // g_pool_mu held by the caller
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return OZ2_E_DEVICE;
-  Pool& P = g_pool[dev];
-  if (P.bytes < need) {
-    if (P.ptr) {
-      if (hipDeviceSynchronize() != hipSuccess) return OZ2_E_DEVICE;
-      (void)hipFree(P.ptr);
-      P.ptr = nullptr;
-      P.bytes = 0;
-    }
-    size_t grow = std::max(need, (size_t)1 << 20);
-    if (hipMalloc(&P.ptr, grow) != hipSuccess) {
-      (void)hipGetLastError();
-      P.ptr = nullptr;
-      return OZ2_E_NOMEM;
-    }
-    P.bytes = grow;
+  HipMem mem;
+  switch (g_pool[dev].get(need, under_capture, mem, out)) {
+    case Oz2Pool::kOk: return OZ2_OK;
+    case Oz2Pool::kNoMem: return OZ2_E_NOMEM;
+    default: return OZ2_E_DEVICE;
   }
-  *out = P.ptr;
-  return OZ2_OK;
 }
 
 size_t pool_bytes() {   // g_pool_mu held by the caller
@@ -909,7 +911,7 @@ int ozaki2_dgemm(int m, int n, int k, const double* A, int lda, const double* B,
   if (st != OZ2_OK) return st;
   std::lock_guard<std::mutex> g(g_pool_mu);
   void* ws = nullptr;
-  st = pool_get(need, &ws);
+  st = pool_get(need, capturing((hipStream_t)stream), &ws);
   if (st != OZ2_OK) return st;
   return ozaki2_dgemm_ex(m, n, k, A, lda, B, ldb, C, ldc, num_moduli, 0, ws, need, stream);
 }
@@ -987,13 +989,14 @@ int ozaki2_dgemm_strided_batched(int m, int n, int k, const double* A, int lda, 
   std::lock_guard<std::mutex> g(g_pool_mu);
   // fewer side by side where the pool cannot grow: a stream under capture
   // takes what the pool holds, and memory may be short
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-  if (cap != hipStreamCaptureStatusNone)
-    side = (int)std::min<size_t>(side, std::max<size_t>(1, pool_bytes() / L.total));
+  const bool cap = capturing(s);
+  if (cap) side = (int)std::min<size_t>(side, std::max<size_t>(1, pool_bytes() / L.total));
   void* ws = nullptr;
-  st = pool_get((size_t)side * L.total, &ws);
-  for (; st == OZ2_E_NOMEM && side > 1; st = pool_get((size_t)side * L.total, &ws)) side = (side + 1) / 2;
+  st = pool_get((size_t)side * L.total, cap, &ws);
+  while (st == OZ2_E_NOMEM && side > 1) {
+    side = (side + 1) / 2;
+    st = pool_get((size_t)side * L.total, cap, &ws);
+  }
   if (st != OZ2_OK) return st;
   for (int b = 0; b < batch; b += side) {
     const Oz2Batch bt{std::min(side, batch - b), strideA, strideB, strideC, L.total};
@@ -1049,15 +1052,26 @@ void ozaki2_finalize(void) {
   int cur = 0;
   (void)hipGetDevice(&cur);
   for (int d = 0; d < ndev && d < 64; ++d) {
-    if (!g_pool[d].ptr) continue;
-    if (hipSetDevice(d) == hipSuccess) {
-      (void)hipDeviceSynchronize();
-      (void)hipFree(g_pool[d].ptr);
-    }
-    g_pool[d].ptr = nullptr;
-    g_pool[d].bytes = 0;
+    if (!g_pool[d].ptr && !g_pool[d].held) continue;
+    if (hipSetDevice(d) != hipSuccess) continue;
+    (void)hipDeviceSynchronize();
+    HipMem mem;
+    g_pool[d].release(mem);
   }
   (void)hipSetDevice(cur);
+}
+
+// (declared in oz2_internal.h)
+int oz2_pool_buffers(void** out, int max) {
+  std::lock_guard<std::mutex> g(g_pool_mu);
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return -1;
+  auto add = [&](void* p) {
+    if (p && n < max) out[n++] = p;
+  };
+  add(g_pool[dev].ptr);
+  for (const Oz2Pool::Held* h = g_pool[dev].held; h; h = h->next) add(h->ptr);
+  return n;
 }
 
 size_t ozaki2_plan_query_bytes(ozaki2_plan_t p, int what) {

@@ -132,6 +132,11 @@ struct Oz2Layout {
 // 256 if the query fails)
 int oz2_device_cus();
 
+// The internal workspace buffers held on the current device, the current one
+// first (a diagnostic for tests; not part of the public ABI): at most max of
+// them into out, their number returned, -1 without a device.
+extern "C" int oz2_pool_buffers(void** out, int max);
+
 // ---------------------------------------------------------------- launchers
 // Each returns hipGetLastError() of its launches.  `side` of the per-operand
 // deconstruct launchers: OZ2_SIDE_A, OZ2_SIDE_B or both.

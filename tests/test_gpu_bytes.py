@@ -190,6 +190,51 @@ def test_blocks_under_capture_take_the_pool_as_it_is():
         assert torch.equal(Ci, D)
 
 
+def test_a_captured_workspace_outlives_growing_calls():
+    """a batch captured on a small workspace, then the same batch called plainly,
+    which grows it: the captured buffer stays allocated (looked up on the host
+    before the graph runs again) and the graph still gives the right results"""
+    import ctypes
+    import paper_2606_06510_amd as oz
+    import torch
+    dev = device()
+    b, m, n, k, r = 9, 140, 75, 80, 12
+    gen = torch.Generator(device=dev).manual_seed(4)
+    A = torch.rand((b, k, m), generator=gen, dtype=torch.float64, device=dev) - 0.5
+    B = torch.rand((b, n, k), generator=gen, dtype=torch.float64, device=dev) - 0.5
+    C, D = (torch.zeros((b, n, m), dtype=torch.float64, device=dev) for _ in range(2))
+
+    def call(count, out, stream=None):
+        oz.ozaki2_dgemm_strided_batched(m, n, k, A, m, m * k, B, k, n * k, out, m, m * n, count, r,
+                                        stream=stream)
+
+    def buffers():
+        out = (ctypes.c_void_p * 8)()
+        return out[:oz.load().oz2_pool_buffers(out, 8)]
+    oz.ozaki2_finalize()
+    assert buffers() == []
+    call(2, C)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call(b, C, stream=side.cuda_stream)
+    taken = buffers()
+    assert len(taken) == 1
+    for i in range(3):
+        A.add_(0.25 * i)
+        C.zero_()
+        call(b, D)
+        torch.cuda.synchronize()
+        assert taken[0] in buffers() and len(buffers()) == 2
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C, D), i
+    del graph
+    oz.ozaki2_finalize()
+    assert buffers() == []
+
+
 @pytest.mark.parametrize("m,n,k", [(64, 64, 64), (1, 1, 1), (17, 64, 3), (64, 15, 33), (50, 49, 64)])
 @pytest.mark.parametrize("r", [8, 11, 12, 13, 16])
 def test_small_batches_digit_counts(m, n, k, r):

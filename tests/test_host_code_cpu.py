@@ -3,8 +3,6 @@ the ranges that kernels index with, and bookkeeping that no GPU run can show."""
 import os
 import subprocess
 
-import pytest
-
 from paper_2606_06510_amd.build import CSRC, hipcc
 
 
@@ -45,3 +43,59 @@ int main() {
 }
 """)
     assert out == "0 4 0"
+
+
+def test_pool_keeps_what_a_capture_has_taken(tmp_path):
+    """the internal workspace grows by freeing its buffer after a
+    synchronisation, but a buffer taken under capture stays allocated until
+    release, and stays in use where no larger one can be had"""
+    out = run_host(tmp_path, r"""
+#include <cstdio>
+#include <cstdlib>
+#include <set>
+#include "oz2_pool.h"
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s", __LINE__, #x); return 1; } } while (0)
+struct Fake {
+  std::set<void*> live;
+  char space[64];
+  int next = 0, syncs = 0;
+  bool full = false, broken = false;
+  bool alloc(void** p, size_t) {
+    if (full) return false;
+    live.insert(*p = &space[next++]);
+    return true;
+  }
+  void free(void* p) { if (!live.erase(p)) std::abort(); }
+  bool sync() { ++syncs; return !broken; }
+  bool has(void* p) const { return live.count(p) != 0; }
+};
+int main() {
+  Fake mem;
+  Oz2Pool pool;
+  const size_t MiB = (size_t)1 << 20;
+  void *a, *b, *c, *d, *e;
+  CHECK(pool.get(10, false, mem, &a) == Oz2Pool::kOk && pool.bytes == MiB);
+  CHECK(pool.get(2 * MiB, false, mem, &b) == Oz2Pool::kOk);       // plain growth
+  CHECK(!mem.has(a) && mem.has(b) && mem.syncs == 1);
+  CHECK(pool.get(MiB, true, mem, &c) == Oz2Pool::kOk && c == b);  // a capture takes b
+  CHECK(pool.get(2 * MiB, false, mem, &c) == Oz2Pool::kOk && c == b);
+  mem.full = true;                                                // no room for more
+  CHECK(pool.get(4 * MiB, false, mem, &c) == Oz2Pool::kNoMem);
+  CHECK(mem.has(b) && pool.get(2 * MiB, false, mem, &c) == Oz2Pool::kOk && c == b);
+  mem.full = false;
+  CHECK(pool.get(4 * MiB, false, mem, &c) == Oz2Pool::kOk && c != b);
+  CHECK(mem.has(b) && mem.has(c));                                // b stays for its graph
+  CHECK(pool.get(8 * MiB, false, mem, &d) == Oz2Pool::kOk);       // c was nobody's
+  CHECK(mem.has(b) && !mem.has(c) && mem.has(d));
+  CHECK(pool.get(8 * MiB, true, mem, &e) == Oz2Pool::kOk && e == d);
+  CHECK(pool.get(9 * MiB, true, mem, &e) == Oz2Pool::kOk);        // (a capture that may allocate)
+  CHECK(pool.get(10 * MiB, false, mem, &a) == Oz2Pool::kOk);
+  CHECK(mem.live.size() == 4 && mem.has(b) && mem.has(d) && mem.has(e) && mem.has(a));
+  mem.broken = true;
+  CHECK(pool.get(11 * MiB, false, mem, &c) == Oz2Pool::kDevice && mem.has(a));
+  pool.release(mem);
+  CHECK(mem.live.empty() && !pool.ptr && !pool.held && pool.bytes == 0);
+  std::printf("ok");
+}
+""")
+    assert out == "ok"
