@@ -78,41 +78,46 @@ __device__ __forceinline__ void fallback_tiles(
       }
     }
     __syncthreads();
-    // slab loads: thread t takes A entries (row e % 64, k e / 64) and B
-    // entries (column e / 32, k e % 32) for e = t + 256 q; outside -> 0.  Two
-    // slabs are in flight: with one, each slab of 32 k waited out the memory
-    // latency (50 flagged rows of 6000 x 4000: 94 tiles, 390 us)
+    // Slab loads: thread t takes A entries (row t % 64, k t / 64 + 4 q) and B
+    // entries (column t / 32 + 8 q, k t % 32).  Two slabs are in flight: with one,
+    // each slab of 32 k waited out the memory latency (50 flagged rows of 6000 x
+    // 4000: 94 tiles, 390 us).  No load stands under a branch, where it could not
+    // be counted and both slabs were waited for at each: rows and columns beyond
+    // the tile's are read at its first place (their sums are not stored), and
+    // the slabs that k may cut short have a loop of their own, with clamped k
+    // and zeros beyond it.
+    const double* pa = As + max(arow[t & 63], 0);
+    const double* pb[FC / 8];
+#pragma unroll
+    for (int q = 0; q < FC / 8; ++q) pb[q] = B + (size_t)max(colid[(t >> 5) + 8 * q], 0) * ldb + (t & 31);
     struct Slab {
       double a[8], b[FC / 8];
     };
-    auto load = [&](int l0, Slab& s) {
+    auto load = [&](int l0, Slab& s, auto whole) {
+      const double* p = pa + (size_t)(l0 + (t >> 6)) * ldas;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int e = t + 256 * q;
-        const int i = arow[e & 63], l = l0 + (e >> 6);
-        s.a[q] = (i >= 0 && l < d.k) ? As[(size_t)i + (size_t)l * ldas] : 0.0;
-      }
+      for (int q = 0; q < 8; ++q)
+        s.a[q] = whole ? p[(size_t)(4 * q) * ldas] : pa[(size_t)min(l0 + (t >> 6) + 4 * q, d.k - 1) * ldas];
+      const int lb = whole ? l0 : min(l0, d.k - 1 - (t & 31));
 #pragma unroll
-      for (int q = 0; q < FC / 8; ++q) {
-        const int e = t + 256 * q;
-        const int j = colid[e >> 5], lb = l0 + (e & 31);
-        s.b[q] = (j >= 0 && lb < d.k) ? B[(size_t)lb + (size_t)j * ldb] : 0.0;
-      }
+      for (int q = 0; q < FC / 8; ++q) s.b[q] = pb[q][lb];
     };
     v4d cacc[2][NJ];
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
       for (int bj = 0; bj < NJ; ++bj) cacc[bi][bj] = v4d{0.0, 0.0, 0.0, 0.0};
-    auto step = [&](int l0, Slab& s) {
+    // slab l0 from s; s then takes slab l0 + 64 (if `more`); whole: both end at k or before
+    auto step = [&](int l0, Slab& s, bool more, auto whole) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        const int e = t + 256 * q;
-        sa[e >> 6][e & 63] = s.a[q];
-        if (q < FC / 8) sb[e >> 5][e & 31] = s.b[q < FC / 8 ? q : 0];
+        const int l = (t >> 6) + 4 * q;
+        sa[l][t & 63] = whole || l0 + l < d.k ? s.a[q] : 0.0;
+        if (q < FC / 8)
+          sb[(t >> 5) + 8 * q][t & 31] = whole || l0 + (t & 31) < d.k ? s.b[q < FC / 8 ? q : 0] : 0.0;
       }
       __syncthreads();
-      if (l0 + 2 * FB_K < d.k) load(l0 + 2 * FB_K, s);
+      if (more) load(l0 + 2 * FB_K, s, whole);
 #pragma unroll
       for (int kk = 0; kk < FB_K; kk += 4) {
         const double a0 = sa[kk + kr][wr + cl], a1 = sa[kk + kr][wr + 16 + cl];
@@ -126,11 +131,18 @@ __device__ __forceinline__ void fallback_tiles(
       __syncthreads();
     };
     Slab even, odd;
-    load(0, even);
-    if (FB_K < d.k) load(FB_K, odd);
-    for (int l0 = 0; l0 < d.k; l0 += 2 * FB_K) {
-      step(l0, even);
-      if (l0 + FB_K < d.k) step(l0 + FB_K, odd);
+    const std::true_type whole{};
+    const std::false_type cut{};
+    load(0, even, cut);
+    load(FB_K, odd, cut);
+    int l0 = 0;
+    for (; d.k - l0 >= 4 * FB_K; l0 += 2 * FB_K) {
+      step(l0, even, true, whole);
+      step(l0 + FB_K, odd, true, whole);
+    }
+    for (; l0 < d.k; l0 += 2 * FB_K) {
+      step(l0, even, d.k - l0 > 2 * FB_K, cut);
+      if (d.k - l0 > FB_K) step(l0 + FB_K, odd, d.k - l0 > 3 * FB_K, cut);
     }
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)

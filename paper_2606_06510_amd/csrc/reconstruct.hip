@@ -257,24 +257,31 @@ k_fallback(Oz2Dims d, const double* __restrict__ A, int lda, const double* __res
            const int* __restrict__ listB, const uint32_t* __restrict__ fA,
            const double* __restrict__ panel, int cap, Oz2Batch bt) {
   __shared__ FbShared S;
+  // The problem of the batch varies fastest: with few tiles each, the busy
+  // workgroups are the first of the grid and get a CU of their own (problem
+  // after problem, 40 x (300 x 300 x 2000) with three flagged rows each took 1195
+  // us, now 1066)
   {
-    const size_t z = (size_t)blockIdx.z * bt.ws;
+    const size_t z = (size_t)blockIdx.x * bt.ws;
     counters = zws(counters, z);
     listA = zws(listA, z);
     listB = zws(listB, z);
     fA = zws(fA, z);
     if (panel) panel = zws(panel, z);
-    A += (size_t)blockIdx.z * bt.sA;
-    B += (size_t)blockIdx.z * bt.sB;
-    C += (size_t)blockIdx.z * bt.sC;
+    A += (size_t)blockIdx.x * bt.sA;
+    B += (size_t)blockIdx.x * bt.sB;
+    C += (size_t)blockIdx.x * bt.sC;
   }
   const int na = counters[0], nb = counters[1];
   // 64 x 32 tiles where 64 x 64 ones would leave half of the chip idle (the
   // sums' order within an entry does not depend on the tile)
   const long long wide = (long long)((na + FB_T - 1) / FB_T) * ((d.n + FB_T - 1) / FB_T) +
                          (long long)((d.m + FB_T - 1) / FB_T) * ((nb + FB_T - 1) / FB_T);
-  if (wide <= 128) fallback_tiles<32>(S, d, A, lda, B, ldb, C, ldc, na, nb, listA, listB, fA, panel, cap, (int)blockIdx.x, (int)gridDim.x);
-  else fallback_tiles<64>(S, d, A, lda, B, ldb, C, ldc, na, nb, listA, listB, fA, panel, cap, (int)blockIdx.x, (int)gridDim.x);
+  const int first = blockIdx.y, stride = gridDim.y;
+  if (wide <= 128)
+    fallback_tiles<32>(S, d, A, lda, B, ldb, C, ldc, na, nb, listA, listB, fA, panel, cap, first, stride);
+  else
+    fallback_tiles<64>(S, d, A, lda, B, ldb, C, ldc, na, nb, listA, listB, fA, panel, cap, first, stride);
 }
 
 __global__ void k_fill(double* C, int m, int n, int ldc) {
@@ -353,11 +360,12 @@ hipError_t oz2_launch_crt_probe(const Oz2Const& c, const int16_t* res, const int
   return hipGetLastError();
 }
 
-// workgroups: 1024 over the batch, no more than the tiles there can be (an empty
-// launch of 1024 takes 2.4-4.6 us, one of 32 under 2)
+// workgroups of each problem: two per CU over the batch, which are resident
+// together, and no more than the tiles there can be (an empty launch of 1024 takes
+// 2.4-4.6 us, one of 32 under 2)
 static unsigned fallback_grid(const Oz2Dims& d, int count) {
   const long long tiles = 2ll * ((d.m + FB_T - 1) / FB_T) * ((d.n + 31) / 32);
-  return (unsigned)std::max(1ll, std::min<long long>(tiles, 1024 / count));
+  return (unsigned)std::max(1ll, std::min<long long>(tiles, 2 * oz2_device_cus() / count));
 }
 
 hipError_t oz2_launch_fallback(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, const double* A,
@@ -365,7 +373,7 @@ hipError_t oz2_launch_fallback(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws
                                const Oz2Batch& bt, hipStream_t s) {
   // the lists were filled by the deconstruction (k_scales: T1, k_split: T2)
   // the panel of flagged rows was gathered by the reconstruction launch
-  hipLaunchKernelGGL(k_fallback, dim3(fallback_grid(d, bt.count), 1, bt.count), dim3(256), 0, s, d,
+  hipLaunchKernelGGL(k_fallback, dim3(bt.count, fallback_grid(d, bt.count)), dim3(256), 0, s, d,
                      A, lda, B, ldb, C, ldc, (const int*)(ws + L.counters),
                      (const int*)(ws + L.listA), (const int*)(ws + L.listB),
                      (const uint32_t*)(ws + L.flagsA), (const double*)(ws + L.panel),
@@ -376,7 +384,7 @@ hipError_t oz2_launch_fallback(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws
 hipError_t oz2_launch_fallback_direct(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
                                       const double* A, int lda, const double* B, int ldb,
                                       double* C, int ldc, hipStream_t s) {
-  hipLaunchKernelGGL(k_fallback, dim3(fallback_grid(d, 1)), dim3(256), 0, s, d, A, lda, B, ldb, C, ldc,
+  hipLaunchKernelGGL(k_fallback, dim3(1, fallback_grid(d, 1)), dim3(256), 0, s, d, A, lda, B, ldb, C, ldc,
                      (const int*)(ws + L.counters), (const int*)(ws + L.listA),
                      (const int*)(ws + L.listB), (const uint32_t*)(ws + L.flagsA),
                      (const double*)nullptr, 0, Oz2Batch{1, 0, 0, 0, 0});

@@ -311,3 +311,36 @@ def test_fallback_beside_the_reconstruction(m, n, k, flags):
         B[1, n // 2] = np.nan
         B[::2, n - 1] *= 1e-200
     _same(*_both(m, n, k, 12, flags=flags, seed=n, pad=1, edit=edit))
+
+
+# the native FP64 of flagged entries at the edges of its slabs of 32 k (two in
+# flight, a loop of its own for those k cuts short), beside the reconstruction
+# and in its own launch, 64 x 32 and 64 x 64 tiles, rows within and beyond the
+# gathered panel.  Row 0 of A and column 0 of B, which stand in for what lies
+# outside a tile, are not finite.
+@pytest.mark.parametrize("k", [1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 161, 223, 257])
+@pytest.mark.parametrize("m,n,flags", [(70, 40, 0), (150, 66, 16), (1040, 1040, 0), (1040, 1040, 16)])
+def test_fallback_slab_edges(m, n, k, flags):
+    import paper_2606_06510_amd as oz
+    rng = np.random.default_rng(k)
+    A, B = rng.random((m, k)) - 0.5, rng.random((k, n)) - 0.5
+    A[0], B[k - 1, 0] = np.nan, np.inf
+    A[m // 3, ::2] *= 1e-200
+    A[m - 1, k - 1] = -np.inf
+    B[::2, n // 2] *= 1e-200
+    dev = device()
+    C = oz.from_device_colmajor(oz.matmul(oz.to_device_colmajor(A, dev), oz.to_device_colmajor(B, dev), 12,
+                                          flags=flags))
+    with np.errstate(invalid="ignore"):
+        ref, den = A @ B, np.abs(A) @ np.abs(B)
+    rows = np.full(m, bool(flags & 16))
+    rows[[0, m // 3, m - 1]] = True
+    cols = np.isin(np.arange(n), [0, n // 2])
+    native = rows[:, None] | cols
+    assert np.array_equal(np.isnan(C), np.isnan(ref))
+    inf = np.isinf(ref)
+    assert np.array_equal(C[inf], ref[inf])
+    ok = native & np.isfinite(ref)
+    # two dot products of k terms, each within k u / (1 - k u) of the exact one
+    assert np.all(np.abs(C - ref)[ok] <= 2.02 * (k + 1) * 2.0 ** -53 * den[ok])
+    assert np.all(np.abs(C - ref)[~native] <= 1e-13 * np.sqrt(k))
