@@ -52,9 +52,14 @@ __device__ __forceinline__ int row_scale(unsigned long long b, int width) {
 
 // ---------------------------------------------------------------- scan
 __global__ void k_gemv_init(unsigned long long* rowbits, uint32_t* flagsA, int mp, int m, int* counters,
-                            int* listA, int keepA, int force) {
+                            int* listA, int keepA, int force, unsigned long long* colbits,
+                            uint32_t* flagsB, int nrb) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0) counters[1] = 0;
+  if (i < nrb) {
+    colbits[i] = 0;
+    flagsB[i] = 0;
+  }
   if (keepA) return;
   if (i == 0) counters[0] = force ? m : 0;
   if (i < mp) {
@@ -64,32 +69,49 @@ __global__ void k_gemv_init(unsigned long long* rowbits, uint32_t* flagsA, int m
   if (force && i < m) listA[i] = i;
 }
 
+// the largest of the workgroup's 256 values
+__device__ __forceinline__ unsigned long long block_max(unsigned long long mx, unsigned long long* red) {
+  const int t = threadIdx.x;
+  for (int off = 32; off; off >>= 1) mx = max(mx, (unsigned long long)__shfl_xor((long long)mx, off));
+  if ((t & 63) == 0) red[t >> 6] = mx;
+  __syncthreads();
+  return max(max(red[0], red[1]), max(red[2], red[3]));
+}
+
 // Workgroups 0 .. nrb-1: column b of X, its maximum, scale, flags and
 // reversed digits: 8 bytes per (l, b) at [l/2][b][l%2], zeros for b >= nrhs and
 // l >= k.  The others: the row maxima of A, 512 rows x kchunk columns each
 // (hidden under them, one workgroup per column is enough for X).
+// xs > 1 workgroups per column where they are not hidden (see the launch): only
+// their parts' maxima here, the rest in k_gemv_digits.
 __global__ void __launch_bounds__(256)
 k_gemv_scan(const double* __restrict__ A, int lda, int m, int k, int kchunk, unsigned vec, int gx,
             unsigned long long* rowbits, const double* __restrict__ X, int ldx, int nrhs, int nrb,
             int kp, int width, unsigned tz, int force, int32_t* tB, uint32_t* flagsB, int* countB,
-            int* listB, uint64_t* __restrict__ xd) {
-  const int blk = (int)blockIdx.x - nrb;
+            int* listB, uint64_t* __restrict__ xd, int xs, unsigned long long* colbits) {
+  const int blk = (int)blockIdx.x - nrb * xs;
   if (blk >= 0) {
     scan_rows_block(A, lda, m, k, kchunk, vec, rowbits, blk % gx, blk / gx);
     return;
   }
   __shared__ unsigned long long red[4];
   __shared__ unsigned flagged;
-  const int b = blockIdx.x, t = threadIdx.x;
+  const int b = blockIdx.x % nrb, t = threadIdx.x;
   const double* x = X + (size_t)b * ldx;
   unsigned long long mx = 0;
+  if (xs > 1) {
+    const int part = blockIdx.x / nrb, per = (k + xs - 1) / xs;
+    const int l1 = min((long long)k, (long long)per * (part + 1));
+    if (b < nrhs)
+      for (long long l = (long long)per * part + t; l < l1; l += 256) mx = max(mx, abs_bits(x[l]));
+    mx = block_max(mx, red);
+    if (t == 0) atomicMax(colbits + b, mx);
+    return;
+  }
   if (b < nrhs)
     for (int l = t; l < k; l += 256) mx = max(mx, abs_bits(x[l]));
-  for (int off = 32; off; off >>= 1) mx = max(mx, (unsigned long long)__shfl_xor((long long)mx, off));
-  if ((t & 63) == 0) red[t >> 6] = mx;
   if (t == 0) flagged = 0;
-  __syncthreads();
-  mx = max(max(red[0], red[1]), max(red[2], red[3]));
+  mx = block_max(mx, red);
   const bool t1 = mx >= kInfBits;
   const int sc = row_scale(mx, width);
   bool any = false;
@@ -107,6 +129,32 @@ k_gemv_scan(const double* __restrict__ A, int lda, int m, int k, int kchunk, uns
     flagsB[b] = f;
     if (f && !force) listB[atomicAdd(countB, 1)] = b;
   }
+}
+
+// The digits, scales and flags of X from the columns' maxima, GD rows l and all
+// columns per workgroup (consecutive threads write consecutive bytes).
+constexpr int GD = 512;
+__global__ void __launch_bounds__(256)
+k_gemv_digits(const double* __restrict__ X, int ldx, int k, int nrhs, int nrb, int kp, int width,
+              unsigned tz, int force, const unsigned long long* __restrict__ colbits, int32_t* tB,
+              uint32_t* flagsB, int* countB, int* listB, uint64_t* __restrict__ xd) {
+  const int t = threadIdx.x, b = (t >> 1) & (nrb - 1);   // 2 nrb divides 256
+  const unsigned long long mx = colbits[b];
+  const bool t1 = mx >= kInfBits;
+  const int sc = row_scale(mx, width);
+  const int l0 = (int)blockIdx.x * GD, l1 = min(kp, l0 + GD);
+  bool any = false;
+  for (int l = l0 + 2 * (t / (2 * nrb)) + (t & 1); l < l1; l += 256 / nrb) {
+    bool t2 = false;
+    const uint64_t v = (b < nrhs && l < k && !t1) ? digits(X[(size_t)b * ldx + l], sc, tz, t2) : 0ull;
+    any |= t2;
+    xd[((size_t)(l >> 1) * nrb + b) * 2 + (l & 1)] = __builtin_bswap64(v);
+  }
+  const bool first = blockIdx.x == 0 && t < 2 * nrb && !(t & 1) && b < nrhs;
+  if (first) tB[b] = sc;
+  // a T1 column by the first workgroup, a T2 one by the first to flag it
+  const uint32_t f = t1 ? (first ? OZ2_T1 : 0u) : (any ? OZ2_T2 : 0u);
+  if (f && !(atomicOr(flagsB + b, f) & (OZ2_T1 | OZ2_T2)) && !force) listB[atomicAdd(countB, 1)] = b;
 }
 
 // ---------------------------------------------------------------- product
@@ -359,18 +407,30 @@ hipError_t oz2_launch_gemv(const Oz2Const& c, const Oz2Dims& d, const Oz2Layout&
   auto* counters = (int*)(ws + L.counters);
   auto* listA = (int*)(ws + L.listA);
   auto* tB = (int32_t*)(ws + L.tB);
+  auto* colbits = (unsigned long long*)(ws + L.colbits);
+  auto* flagsB = (uint32_t*)(ws + L.flagsB);
   hipLaunchKernelGGL(k_gemv_init, dim3((d.mp + 255) / 256), dim3(256), 0, s, rowbits, flagsA, d.mp,
-                     d.m, counters, listA, reuse ? 1 : 0, force);
+                     d.m, counters, listA, reuse ? 1 : 0, force, colbits, flagsB, nrb);
   // rows: 512 per workgroup; k chunks sized for at most about 4096 workgroups
   const int gx = (d.m + 511) / 512;
   int kchunk = 32;
   while ((long long)gx * ((d.k + kchunk - 1) / kchunk) > 4096 && kchunk < 4096) kchunk *= 2;
   const int gy = (d.k + kchunk - 1) / kchunk;
   const unsigned vec = ((uintptr_t)A % 16 == 0 && lda % 2 == 0) ? 1u : 0u;
-  hipLaunchKernelGGL(k_gemv_scan, dim3((unsigned)(nrb + (reuse ? 0 : gx * gy))), dim3(256), 0, s, A, lda,
-                     d.m, d.k, kchunk, vec, gx, rowbits, X, ldx, d.n, nrb, d.kp, wb, tz, force, tB,
-                     (uint32_t*)(ws + L.flagsB), counters + 1, (int*)(ws + L.listB),
-                     (uint64_t*)(ws + L.xfrag));
+  // One workgroup per column of X takes 3 us per 1000 k.  It lies under the row
+  // maxima of A where those are as long (16384^2 x 8: 781 us, 778 split); else,
+  // from the k on where a launch more costs less, X is split over the chip (us, one
+  // workgroup -> split: 1000 x 8000 x 8 69 -> 64, 1000 x 4000 x 8 49 -> 51; 16384 x
+  // 16384 x 8 with A's scales kept 427 -> 409; 64 x 10^6 x 16 3484 -> 516).
+  const bool hidden = !reuse && d.m >= 8192;
+  const int xs = !hidden && d.k > 8192 ? std::min(256, (d.k + 2047) / 2048) : 1;
+  hipLaunchKernelGGL(k_gemv_scan, dim3((unsigned)(nrb * xs + (reuse ? 0 : gx * gy))), dim3(256), 0, s, A,
+                     lda, d.m, d.k, kchunk, vec, gx, rowbits, X, ldx, d.n, nrb, d.kp, wb, tz, force, tB,
+                     flagsB, counters + 1, (int*)(ws + L.listB), (uint64_t*)(ws + L.xfrag), xs, colbits);
+  if (xs > 1)
+    hipLaunchKernelGGL(k_gemv_digits, dim3((d.kp + GD - 1) / GD), dim3(256), 0, s, X, ldx, d.k, d.n, nrb,
+                       d.kp, wb, tz, force, colbits, tB, flagsB, counters + 1, (int*)(ws + L.listB),
+                       (uint64_t*)(ws + L.xfrag));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const GemvArgs a{A, lda, d.m, d.k, d.n, splits, wa, da + db - 1, d.mp, force, ldy, tz, rowbits,

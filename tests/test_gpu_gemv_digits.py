@@ -9,7 +9,7 @@ from tests.gpu_util import bits, device
 pytestmark = pytest.mark.gpu
 
 
-def _compare(A, X, r, pad, flags=0):
+def _compare(A, X, r, pad, flags=0, reuse=False):
     import paper_2606_06510_amd as oz
     import torch
     dev = device()
@@ -21,7 +21,12 @@ def _compare(A, X, r, pad, flags=0):
         T[:, :M.shape[0]] = torch.from_numpy(np.ascontiguousarray(M.T)).to(dev)
         return T[:, :M.shape[0]].t()
     Ad, Xd, Y, C = put(A), put(X), put(np.full((m, n), np.nan)), put(np.full((m, n), np.nan))
-    oz.gemv(Ad, Xd, r, flags=flags, Y=Y)
+    if reuse:      # another X first: A's side of the workspace stays
+        ws = torch.empty(oz.ozaki2_gemv_workspace_bytes(m, k, n, r), dtype=torch.uint8, device=dev)
+        oz.gemv(Ad, torch.ones_like(Xd).t().contiguous().t(), r, flags=flags, Y=Y, workspace=ws)
+        oz.gemv(Ad, Xd, r, flags=flags | oz.OZ2_REUSE_A_SCALES, Y=Y, workspace=ws)
+    else:
+        oz.gemv(Ad, Xd, r, flags=flags, Y=Y)
     plan = oz.Plan(m, n, k, r, oz.OZ2_SCALE_FIXED | flags, device=dev)
     plan.deconstruct(Ad, Xd)
     plan.residue_gemm()
@@ -52,3 +57,22 @@ def test_extreme_digits(r, k):
     A = np.resize(v, (40, k)) * np.where(np.arange(40) % 2, 1.0, -1.0)[:, None]
     X = np.resize(v[::-1], (k, 5)) * np.where(np.arange(5) % 2, -1.0, 1.0)
     _compare(A, X, r, 0)
+
+
+# X split over several workgroups per column (k above 8192, few rows or A's
+# scales kept): partial chunks, columns that are flagged (by an entry of the
+# last chunk, by infinities, and a zero one), the rows at which it is not split
+@pytest.mark.parametrize("reuse", [False, True])
+@pytest.mark.parametrize("m,n,k", [(3, 1, 8192), (3, 1, 8193), (5, 3, 8705), (70, 16, 20000), (33, 7, 70001),
+                                   (8191, 2, 8200), (8192, 2, 8200)])
+@pytest.mark.parametrize("flags", [0, 8])    # flagged entries native, or the integers' values
+def test_split_columns(m, n, k, reuse, flags):
+    rng = np.random.default_rng(m + k)
+    A, X = rng.random((m, k)) - 0.5, rng.random((k, n)) - 0.5
+    A[m // 2, ::2] *= 1e250
+    if n > 1:
+        X[k - 1, 0] = 1e-300
+        X[k // 2, n - 1] = -np.inf
+    if n > 2:
+        X[:, 1] = 0.0
+    _compare(A, X, 12, 1 if m == 5 else 0, flags=flags, reuse=reuse)
