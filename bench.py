@@ -210,24 +210,13 @@ def main():
         del tplan
     nfb = plan.query(oz.OZ2_Q_FALLBACK_COUNT)
 
-    # the one-call product (byte residues on int8 MFMA, the same C bit for bit)
-    # on the same operands and output, with a workspace of its own (the plan
-    # keeps its tables in its workspace)
     one_call = None
     if not fused:
         ws1 = torch.empty(plan.ws_bytes, dtype=torch.uint8, device=dev)
-        for _ in range(2):
-            oz.matmul(Ad, Bd, r, flags=flags, C=Cd, workspace=ws1)
-        torch.cuda.synchronize()
-        t0 = time.perf_counter()
-        for _ in range(args.steps):
-            oz.matmul(Ad, Bd, r, flags=flags, C=Cd, workspace=ws1)
-        torch.cuda.synchronize()
-        ms_one = (time.perf_counter() - t0) * 1e3 / args.steps
-        one_call = {"ms_per_call": round(ms_one, 4),
-                    "tflops": round(2.0 * m * n * k / (ms_one * 1e-3) / 1e12, 3),
-                    "dtype": "int8 MFMA -> exact int -> f64"}
-        log(f"{args.steps} one-call products: {ms_one:.3f} ms per call")
+        one_call = one_call_line(
+            lambda C: oz.matmul(Ad, Bd, r, flags=flags, C=C, workspace=ws1), lambda: step(plan), Cd,
+            torch.cuda.synchronize, args.steps, bool(flags & oz.OZ2_ACCUMULATE), 2.0 * m * n * k)
+        log(f"{args.steps} one-call products: {one_call['ms_per_call']} ms per call")
         del ws1
 
     flop = 2.0 * m * n * k
@@ -349,6 +338,32 @@ def main():
                 "deconstruct_hbm": round(out["deconstruct_gbs_algorithmic"] / peaks["hbm_copy_gbs"], 4),
                 "reconstruct_hbm": round(out["reconstruct_gbs_algorithmic"] / peaks["hbm_copy_gbs"], 4)}
     print(json.dumps(out))
+
+
+def one_call_line(product, plan_step, Cd, sync, steps, accumulate, flop):
+    """The one-call product (byte residues on int8 MFMA) on the plan's operands,
+    with a workspace and an output of its own: Cd stays the plan's, whose values
+    are checked against the oracle.  Afterwards one pass of each from the same C:
+    the two routes give the same bits."""
+    import torch
+    C = torch.empty_like(Cd)
+    C.copy_(Cd)
+    for _ in range(2):
+        product(C)
+    sync()
+    t0 = time.perf_counter()
+    for _ in range(steps):
+        product(C)
+    sync()
+    ms = (time.perf_counter() - t0) * 1e3 / steps
+    if accumulate:
+        C.copy_(Cd)
+    product(C)
+    plan_step()
+    sync()
+    same = torch.equal(C.t().contiguous().view(torch.int64), Cd.t().contiguous().view(torch.int64))
+    return {"ms_per_call": round(ms, 4), "tflops": round(flop / (ms * 1e-3) / 1e12, 3),
+            "dtype": "int8 MFMA -> exact int -> f64", "same_bits_as_plan": same}
 
 
 def stationary_line(args, cfg, r, dev, A, B):
