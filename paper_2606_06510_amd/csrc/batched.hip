@@ -251,7 +251,8 @@ k_batched(int cA, int cB, int m, int n, int k, int batch, const double* __restri
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   Smem& S = *reinterpret_cast<Smem*>(smem);
   const bool full = m == 64 && n == 64 && k == 64;
-  for (int b = blockIdx.x; b < batch; b += gridDim.x) {
+  // (unsigned: the last step goes beyond `batch`, which may be close to 2^31)
+  for (unsigned b = blockIdx.x; b < (unsigned)batch; b += gridDim.x) {
     // (opaque per problem: the addresses derived from it are formed anew
     // instead of being kept, spilled, across the loop)
     int t = threadIdx.x;
