@@ -382,13 +382,14 @@ void launch_n(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* w
 
 }  // namespace
 
-// At most 15 moduli (16 residue bytes, |X| < 2^112) and, by measurement, at least
-// 12 (with fewer the staged residues cost less: 2048^2 x 64 at n = 10 72 us staged
-// against 76); k up to 256 (above); and tiles that fill the CUs, in whole turns
-// while there are few (2048^2: 256 tiles, 97 -> 91; 1500^2: 144 tiles, 78 -> 90;
-// 3000^2: 576 tiles in three turns, 163 -> 168).
+// At most 15 moduli (16 residue bytes, |X| < 2^112), which is r <= 12; k up to 256
+// (above); and tiles that fill the CUs, in whole turns while there are few (2048^2:
+// 256 tiles, 97 -> 91; 1500^2: 144 tiles, 78 -> 90; 3000^2: 576 tiles in three turns,
+// 163 -> 168).  With the fewest moduli too (us, staged -> fused, r = 8: 2048^2 x 64 55 ->
+// 47, 4096^2 x 256 187 -> 162, 20000^2 x 64 2469 -> 2163, 30000^2 x 16 5570 -> 4792; r = 9:
+// 16384^2 x 256 2238 -> 2178).
 bool oz2_byte_fused_fits(const Oz2Dims& d, const Oz2Byte& c) {
-  if (c.n < 12 || c.n > 15 || d.kp > 256) return false;
+  if (c.n > 15 || d.kp > 256) return false;
   const long long cus = oz2_device_cus();
   const long long tiles = (long long)((d.m + FT - 1) / FT) * ((d.n + FT - 1) / FT);
   const long long turns = (tiles + cus - 1) / cus;
@@ -398,6 +399,8 @@ bool oz2_byte_fused_fits(const Oz2Dims& d, const Oz2Byte& c) {
 hipError_t oz2_launch_byte_fused(const Oz2Dims& d, const Oz2Layout& L, const Oz2Byte& c, uint8_t* ws,
                                  double* C, int ldc, hipStream_t s) {
   switch (c.n) {
+    case 10: launch_n<10>(d, L, c, ws, C, ldc, s); break;
+    case 11: launch_n<11>(d, L, c, ws, C, ldc, s); break;
     case 12: launch_n<12>(d, L, c, ws, C, ldc, s); break;
     case 13: launch_n<13>(d, L, c, ws, C, ldc, s); break;
     case 15: launch_n<15>(d, L, c, ws, C, ldc, s); break;

@@ -284,6 +284,20 @@ def test_fused_short_k(m, n, k, r, pad, flags):
     _same(*_both(m, n, k, r, flags=flags, seed=k, pad=pad, edit=edit))
 
 
+# the same with the fewest moduli: 10 and 11 residue bytes, the last word of a
+# lane's residues partly or wholly zero
+@pytest.mark.parametrize("m,n,k,r,pad,flags", [(2040, 1801, 70, 8, 0, 0), (2047, 2047, 256, 8, 1, 1),
+                                               (4300, 4100, 17, 9, 0, 1), (1793, 2047, 129, 9, 3, 9)])
+def test_fused_short_k_few_moduli(m, n, k, r, pad, flags):
+    def edit(A, B):
+        A[m // 2, ::2] *= 1e200     # T2
+        B[2, n - 1] = np.nan        # T1
+        A[:300] *= 2.0 ** -520      # results around the smallest normal number
+        B[:, :400] *= 2.0 ** -500
+        A[40:60] = np.round(A[40:60] * 4)
+    _same(*_both(m, n, k, r, flags=flags, seed=k, pad=pad, edit=edit))
+
+
 def test_fused_short_k_subnormal_and_small_integers():
     """results around and below the smallest normal number, in some rows and
     columns only (the words' rounding), and integers of few bits"""
