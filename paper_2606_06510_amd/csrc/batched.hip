@@ -178,7 +178,7 @@ __device__ __forceinline__ double round4(const double (&S)[4], int e) {
 #pragma unroll
   for (int j = 2; j >= 0; --j) {
     const bool rest = j == 2 ? (S[1] != 0.0 || S[0] != 0.0) : (j == 1 && S[0] != 0.0);
-    const bool small = v >= -0x1p21 && v < 0x1p21;
+    const bool small = fabs(v + 0.5) < 0x1p21;   // (v is an integer)
     const double next = fma(v, j == 0 ? 0x1p24 : 0x1p32, S[j] + ((!small && rest) ? 0.5 : 0.0));
     v = done ? v : next;
     sh = done ? sh : (j == 2 ? 56 : j == 1 ? 24 : 0);
