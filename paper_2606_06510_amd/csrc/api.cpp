@@ -347,9 +347,8 @@ Oz2Layout make_layout(const Oz2Dims& d, const Oz2Const& c) {
   return L;
 }
 
-// The byte-residue route's carve-up of the same workspace: c.n byte planes in
-// the place of the E4M3 planes, one byte per output and modulus in the place
-// of 12 bits; never larger than make_layout's (n <= P, n <= 1.5 r).
+// The batched calls' carve-up per problem: c.n byte planes in the place of the E4M3
+// planes, one byte per output and modulus in the place of 12 bits.
 Oz2Layout make_byte_layout(const Oz2Dims& d, const Oz2Byte& c) {
   Oz2Layout L{};
   size_t o = 0;
@@ -882,8 +881,9 @@ int ozaki2_dgemm_ex(int m, int n, int k, const double* A, int lda, const double*
   if (!(flags & (OZ2_FUSED | OZ2_KEEP_RESIDUES))) {
     Oz2Byte b;
     if (!make_byte(num_moduli, b)) return OZ2_E_INVALID;
-    return run_bytes(p.d, make_byte_layout(p.d, b), p.c, b, (uint8_t*)workspace, A, lda, B, ldb, C, ldc,
-                     kOne, s);
+    // in the plan's carve-up (n <= P planes per operand, n <= 1.5 r bytes per
+    // output), so that the tables of a plan on the same workspace stay as they are
+    return run_bytes(p.d, p.L, p.c, b, (uint8_t*)workspace, A, lda, B, ldb, C, ldc, kOne, s);
   }
   p.ws = (uint8_t*)workspace;
   p.A = A;

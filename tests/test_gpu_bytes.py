@@ -358,3 +358,28 @@ def test_fallback_slab_edges(m, n, k, flags):
     # two dot products of k terms, each within k u / (1 - k u) of the exact one
     assert np.all(np.abs(C - ref)[ok] <= 2.02 * (k + 1) * 2.0 ** -53 * den[ok])
     assert np.all(np.abs(C - ref)[~native] <= 1e-13 * np.sqrt(k))
+
+
+@pytest.mark.parametrize("flags", [0, 2])
+def test_one_call_product_on_a_plans_workspace(flags):
+    """the one-call product between two passes of a plan, on the plan's own
+    workspace: the plan's tables, built by its first pass, are still there"""
+    import paper_2606_06510_amd as oz
+    import torch
+    m, n, k, r = 1000, 900, 70, 12      # short k: the residues are the larger part
+    rng = np.random.default_rng(6)
+    dev = device()
+    Ad = oz.to_device_colmajor(rng.random((m, k)) - 0.5, dev)
+    Bd = oz.to_device_colmajor(rng.random((k, n)) - 0.5, dev)
+    plan = oz.Plan(m, n, k, r, flags, device=dev)
+    C = [oz.colmajor_empty(m, n, device=dev) for _ in range(3)]
+
+    def run(out):
+        plan.deconstruct(Ad, Bd)
+        plan.residue_gemm()
+        plan.reconstruct(out)
+    run(C[0])
+    oz.matmul(Ad, Bd, r, flags=flags, C=C[1], workspace=plan.workspace)
+    run(C[2])
+    torch.cuda.synchronize()
+    assert torch.equal(C[0], C[1]) and torch.equal(C[0], C[2])
