@@ -79,9 +79,9 @@ int ozaki2_probe_crt(int num_moduli, const short* residues, const int* shifts, i
  * exact integer it reconstructs for every output whose row and column are
  * not flagged: words = uint32 [batch][n][m][5] (device, two's complement,
  * little endian; entries of flagged rows / columns are left untouched).
- * Same A, B conventions as ozaki2_dgemm_strided_batched.  Uses the library's
- * internal workspace for the plane tables.  OZ2_E_INVALID for sizes outside
- * 1..64, a negative batch or stride, lda < m, ldb < k or a null pointer. */
+ * Same A, B conventions as ozaki2_dgemm_strided_batched.  OZ2_E_INVALID for
+ * sizes outside 1..64, a negative batch or stride, lda < m, ldb < k or a null
+ * pointer. */
 int ozaki2_probe_batched_integers(int m, int n, int k, const double* A, int lda,
                                   long long strideA, const double* B, int ldb, long long strideB,
                                   int batch, int num_moduli, unsigned* words, void* stream);

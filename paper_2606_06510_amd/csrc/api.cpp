@@ -428,8 +428,9 @@ Oz2Layout make_gemv_layout(const GemvShape& g, const Oz2Const& c) {
   L.counters = take(64);
   L.listA = take((size_t)d.mp * 4);
   L.listB = take((size_t)d.np * 4);
-  // (the sizes of X's digits and the splits' integers are upper bounds: the
-  // workspace a caller sized once stays valid)
+  // (sized for tables, X's planes and residues of r moduli, upper bounds of what the
+  // digits and the splits' integers take: the workspace a caller sized once stays
+  // valid)
   L.tabs = take((size_t)c.tabsz * 4);
   L.xfrag = take((size_t)g.chunks * c.P * 2048);
   L.part = take((size_t)g.splits * c.r * d.mp * kGemvRhs * 2);
@@ -558,11 +559,11 @@ hipError_t mark(ozaki2_plan_s& p, int i, hipStream_t s) {
   return e;
 }
 
+const Oz2Batch kOne{1, 0, 0, 0, 0};
+
 // Phase 1 for the operands in `side` (OZ2_SIDE_A, OZ2_SIDE_B or both).  One
 // operand alone only under OZ2_SCALE_FIXED, where its scales do not depend on
 // the other operand (no max-magnitude pass).
-const Oz2Batch kOne{1, 0, 0, 0, 0};
-
 int run_deconstruct(ozaki2_plan_s& p, int side, hipStream_t s) {
   const Oz2Dims& d = p.d;
   // Each operand is read once for its scan and code bytes (one kernel), and
@@ -579,7 +580,7 @@ int run_deconstruct(ozaki2_plan_s& p, int side, hipStream_t s) {
   if (e == hipSuccess) e = mark(p, 1, s);
   if (codes && e == hipSuccess) e = oz2_launch_codegemm(d, p.L, p.ws, kOne, s);
   if (e == hipSuccess) e = mark(p, 2, s);
-  if (e == hipSuccess) e = oz2_launch_scales(d, p.L, p.c, p.ws, side, kOne, s);
+  if (e == hipSuccess) e = oz2_launch_scales(d, p.L, p.c, p.ws, side, s);
   if (e == hipSuccess && !p.tables) {
     e = oz2_launch_tables(p.L, p.c, p.ws, s);
     p.tables = e == hipSuccess;
@@ -930,8 +931,9 @@ int ozaki2_dgemm_static(int m, int n, int k, const double* A, int lda, const dou
   void* ws = nullptr;
   st = scratch_address(&ws);
   if (st != OZ2_OK) return st;
-  // every kernel of the staged path clears what it accumulates into (k_init)
-  // and rebuilds the plane tables, so the previous call's contents do not matter
+  // the byte route's first launch clears what later ones accumulate into (k_prep or
+  // k_init), and what is read unwritten (plane rows beyond the matrix) reaches
+  // padded outputs only, so the previous call's contents do not matter
   return ozaki2_dgemm_ex(m, n, k, A, lda, B, ldb, C, ldc, num_moduli, 0, ws, need, stream);
 }
 

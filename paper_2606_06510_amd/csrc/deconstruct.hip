@@ -515,21 +515,7 @@ __global__ void k_scales(Oz2Dims d, const unsigned long long* __restrict__ rowbi
                          const uint32_t* __restrict__ Rmax, const uint32_t* __restrict__ Kmax,
                          int32_t* sA, int32_t* tB, int32_t* eA, int32_t* eB, uint32_t* fA,
                          uint32_t* fB, int cA, int cB, int* counters, int* listA, int* listB,
-                         int side, size_t wsz) {
-  const size_t z = (size_t)blockIdx.z * wsz;
-  rowbits = zws(rowbits, z);
-  colbits = zws(colbits, z);
-  Rmax = zws(Rmax, z);
-  Kmax = zws(Kmax, z);
-  sA = zws(sA, z);
-  tB = zws(tB, z);
-  eA = zws(eA, z);
-  eB = zws(eB, z);
-  fA = zws(fA, z);
-  fB = zws(fB, z);
-  counters = zws(counters, z);
-  listA = zws(listA, z);
-  listB = zws(listB, z);
+                         int side) {
   int idx = blockIdx.x * blockDim.x + threadIdx.x;
   bool fixed = (d.flags & 2u) != 0;   // OZ2_SCALE_FIXED
   const bool force = (d.flags & 16u) != 0;   // OZ2_FORCE_FALLBACK: every row of A natively
@@ -789,14 +775,15 @@ hipError_t oz2_launch_rebase(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, 
 }
 
 hipError_t oz2_launch_scales(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c,
-                             uint8_t* ws, int side, const Oz2Batch& bt, hipStream_t s) {
+                             uint8_t* ws, int side, hipStream_t s) {
   unsigned blocks = (unsigned)((d.mp + d.np + 255) / 256);
-  hipLaunchKernelGGL(k_scales, dim3(blocks, 1, bt.count), dim3(256), 0, s, d,
+  hipLaunchKernelGGL(k_scales, dim3(blocks), dim3(256), 0, s, d,
                      (const unsigned long long*)(ws + L.rowbits),
                      (const unsigned long long*)(ws + L.colbits), (const uint32_t*)(ws + L.Rmax),
                      (const uint32_t*)(ws + L.Kmax), (int32_t*)(ws + L.sA), (int32_t*)(ws + L.tB),
-                     (int32_t*)(ws + L.eA), (int32_t*)(ws + L.eB), (uint32_t*)(ws + L.flagsA), (uint32_t*)(ws + L.flagsB), c.cA, c.cB,
-                     (int*)(ws + L.counters), (int*)(ws + L.listA), (int*)(ws + L.listB), side, bt.ws);
+                     (int32_t*)(ws + L.eA), (int32_t*)(ws + L.eB), (uint32_t*)(ws + L.flagsA),
+                     (uint32_t*)(ws + L.flagsB), c.cA, c.cB, (int*)(ws + L.counters),
+                     (int*)(ws + L.listA), (int*)(ws + L.listB), side);
   return hipGetLastError();
 }
 

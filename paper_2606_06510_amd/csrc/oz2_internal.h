@@ -166,7 +166,7 @@ bool oz2_codegemm128_fits(const Oz2Dims& d, const Oz2Batch& bt);
 hipError_t oz2_launch_codegemm128(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws,
                                   const Oz2Batch& bt, hipStream_t s);
 hipError_t oz2_launch_scales(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c,
-                             uint8_t* ws, int side, const Oz2Batch& bt, hipStream_t s);
+                             uint8_t* ws, int side, hipStream_t s);
 hipError_t oz2_launch_tables(const Oz2Layout& L, const Oz2Const& c, uint8_t* ws, hipStream_t s);
 hipError_t oz2_launch_split(const Oz2Dims& d, const Oz2Layout& L, const Oz2Const& c, uint8_t* ws,
                             const double* A, int lda, const double* B, int ldb, int side,

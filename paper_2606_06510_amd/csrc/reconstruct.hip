@@ -371,8 +371,8 @@ static unsigned fallback_grid(const Oz2Dims& d, int count) {
 hipError_t oz2_launch_fallback(const Oz2Dims& d, const Oz2Layout& L, uint8_t* ws, const double* A,
                                int lda, const double* B, int ldb, double* C, int ldc,
                                const Oz2Batch& bt, hipStream_t s) {
-  // the lists were filled by the deconstruction (k_scales: T1, k_split: T2)
-  // the panel of flagged rows was gathered by the reconstruction launch
+  // the lists were filled by the deconstruction (k_scales: T1, k_split: T2;
+  // k_byte_split: both), the panel of flagged rows by the reconstruction launch
   hipLaunchKernelGGL(k_fallback, dim3(bt.count, fallback_grid(d, bt.count)), dim3(256), 0, s, d,
                      A, lda, B, ldb, C, ldc, (const int*)(ws + L.counters),
                      (const int*)(ws + L.listA), (const int*)(ws + L.listB),
