@@ -25,8 +25,6 @@
 
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-
 constexpr int NTB = 512;
 
 // plane rows of 64 k bytes, 16-byte chunks swizzled (conflict-free fragments)
@@ -47,8 +45,7 @@ __device__ __forceinline__ uint8_t* spot(uint8_t (*pl)[64], int row, int ch) {  
 // fragment: rows base + L%16, k 16 (L/16) .. +15
 __device__ __forceinline__ v4i frag(const uint8_t (*pl)[64], int base, int lane) {
   const int r = lane & 15;
-  const uint4 v = *reinterpret_cast<const uint4*>(pl[base + r] + 16 * ((lane >> 4) ^ swz16(r)));
-  return v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w};
+  return frag(pl[base + r] + 16 * ((lane >> 4) ^ swz16(r)));
 }
 
 __device__ __forceinline__ v4i mfma(v4i a, v4i b, v4i c) {
@@ -74,9 +71,7 @@ __device__ __forceinline__ void digits8(const double (&x)[8], int sc, bool zero,
     const double xj = zero ? 0.0 : x[j];
     const double a = rint(ldexp(xj, sc));
     t2 |= (xj != 0.0) && (a == 0.0);
-    const double h = floor(a * 0x1p-32);
-    const uint64_t v = (((uint64_t)(uint32_t)(int)h << 32) | (uint32_t)fma(-h, 0x1p32, a)) +
-                       0x0080808080808080ull;
+    const uint64_t v = digit_bytes(a);
     lo[j] = (uint32_t)v;
     hi[j] = (uint32_t)(v >> 32);
     // digits 6 and 7 (still offset: digit 6 is byte 6 less 128)

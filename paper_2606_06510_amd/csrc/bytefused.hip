@@ -31,17 +31,11 @@
 
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int KS = OZ2_KBLK;
 constexpr int FT = 128, FNT = 512, FNB = 8;    // tile, threads, ring depth
 constexpr int FOP = FT * KS, FST = 2 * FOP;    // 8 KiB per operand and stage
-
-__device__ __forceinline__ v4i frag(const uint8_t* p) {
-  const uint4 v = *reinterpret_cast<const uint4*>(p);
-  return v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w};
-}
 
 // swap the upper half of a's lanes (odd 16-lane rows) with the lower half
 // (even rows) of b's

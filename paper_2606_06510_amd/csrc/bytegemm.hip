@@ -31,7 +31,6 @@
 
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int KS = OZ2_KBLK;
@@ -48,12 +47,6 @@ __device__ __forceinline__ uint32_t reduce(uint32_t a, uint32_t mg, uint32_t nm)
   uint32_t q = __umulhi(a, mg);
   if (!SHORT) q >>= 7;
   return __umul24(q, nm) + a;
-}
-
-__device__ __forceinline__ uint32_t pack_low(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-  const uint32_t lo = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);
-  const uint32_t hi = __builtin_amdgcn_perm(d, c, 0x04000c0cu);
-  return lo | hi;
 }
 
 // mid-stream reduction (k beyond one exact slab): back to [0, m) plus the offset
@@ -88,7 +81,7 @@ __device__ __forceinline__ void pack(const v4i (&acc)[NI][NJ], uint32_t mg, uint
       uint32_t v[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = reduce<SHORT>((uint32_t)acc[i][j][e], mg, nm);
-      w[j][i] = pack_low(v[0], v[1], v[2], v[3]);
+      w[j][i] = low4(v[0], v[1], v[2], v[3]);
     }
 }
 
@@ -101,13 +94,6 @@ __device__ __forceinline__ void store(uint8_t* dst, size_t cbs, const uint32_t (
       __builtin_nontemporal_store(
           u32x4{w[j][4 * h], w[j][4 * h + 1], w[j][4 * h + 2], w[j][4 * h + 3]},
           reinterpret_cast<u32x4*>(dst + j * cbs + h * 1024));
-}
-
-// operand fragment of 16 rows x 64 k: lane L holds row L%16, k 16 (L/16) .. +15
-// (the logical chunk L/16 of the row at its swizzled place)
-__device__ __forceinline__ v4i frag(const uint8_t* p) {
-  const uint4 v = *reinterpret_cast<const uint4*>(p);
-  return v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w};
 }
 
 // ------------------------------------------------ 256 x 256 tiles, ping-pong

@@ -7,6 +7,7 @@
 
 #include "oz2_device.h"
 #include "oz2_fallback.h"
+#include "oz2_tile.h"
 
 namespace {
 
@@ -45,12 +46,6 @@ struct ByteSide {
   int listed, all;     // FORCE_FALLBACK: no row is listed by its flags; all rows are (A)
   long long stride;    // elements between the problems of a batch
 };
-
-__device__ __forceinline__ uint32_t low4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-  const uint32_t lo = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);
-  const uint32_t hi = __builtin_amdgcn_perm(d, c, 0x04000c0cu);
-  return lo | hi;
-}
 
 template <bool TRANS>
 __device__ __forceinline__ void byte_tile(const Oz2Byte& c, const ByteSide& S, int tl, int k, int kp,
@@ -99,9 +94,7 @@ __device__ __forceinline__ void byte_tile(const Oz2Byte& c, const ByteSide& S, i
     const double y = ldexp(x[j], sc);
     const double a = quant_tz ? trunc(y) : rint(y);
     t2 |= (x[j] != 0.0) && (a == 0.0);
-    const double h = floor(a * 0x1p-32);
-    const uint64_t v = (((uint64_t)(uint32_t)(int)h << 32) | (uint32_t)fma(-h, 0x1p32, a)) +
-                       0x0080808080808080ull;
+    const uint64_t v = digit_bytes(a);
     lo[j] = (uint32_t)v ^ 0x80808080u;
     hi[j] = (uint32_t)(v >> 32) ^ 0x00808080u;
   }

@@ -40,10 +40,7 @@ __device__ __forceinline__ uint64_t digits(double x, int sc, unsigned tz, bool& 
   const double y = ldexp(x, sc);
   const double a = tz ? trunc(y) : rint(y);
   t2 = (x != 0.0) && (a == 0.0);
-  const double h = floor(a * 0x1p-32);
-  const uint64_t v = (((uint64_t)(uint32_t)(int)h << 32) | (uint32_t)fma(-h, 0x1p32, a)) +
-                     0x0080808080808080ull;
-  return v ^ 0x0080808080808080ull;
+  return digit_bytes(a) ^ 0x0080808080808080ull;
 }
 
 __device__ __forceinline__ int row_scale(unsigned long long b, int width) {

@@ -100,6 +100,13 @@ __device__ __forceinline__ int centred_residue(double ah, double al, double m, d
   return (int)fma(-q, m, t);
 }
 
+// The balanced base-256 digits of the integer a, |a| <= 2^62, lowest byte first:
+// digits 0..6 plus 128 each, digit 7 as it is.
+__device__ __forceinline__ uint64_t digit_bytes(double a) {
+  const double h = floor(a * 0x1p-32);
+  return (((uint64_t)(uint32_t)(int)h << 32) | (uint32_t)fma(-h, 0x1p32, a)) + 0x0080808080808080ull;
+}
+
 // bytes p of four table entries, packed (element j in byte j)
 __device__ __forceinline__ uint32_t gather_byte(uint32_t e0, uint32_t e1, uint32_t e2, uint32_t e3,
                                                 uint32_t sel) {

@@ -1,12 +1,14 @@
-// Device helpers shared by the LDS-ring GEMMs of gemm.hip (E4M3 planes) and
-// bytegemm.hip (byte residues): pinned barriers and waits, the LDS DMA and its
-// chunk swizzle, and the block -> tile mapping.
+// Device helpers shared by the LDS-ring GEMMs of gemm.hip (E4M3 planes),
+// bytegemm.hip and bytefused.hip (byte residues), and by the other byte kernels:
+// pinned barriers and waits, the LDS DMA and its chunk swizzle, int8 fragments,
+// byte packing, and the block -> tile mapping.
 #pragma once
 #include "oz2_internal.h"
 
 namespace {
 
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
+typedef int v4i __attribute__((ext_vector_type(4)));
 
 // s_barrier pinned in the instruction stream: the scheduler moves nothing
 // (not even register-only MFMAs) across it, so the phases below stay phases
@@ -30,6 +32,20 @@ __device__ __forceinline__ int swz(int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 
 // of 32-row fragments above is two-way conflicted there (four extra cycles
 // per read, the matrix unit busy 60% of the cycles at 4096^3).
 __device__ __forceinline__ int swz16(int r) { return (-(r >> 2)) & 3; }
+
+// operand fragment of 16 rows x 64 k: lane L holds row L%16, k 16 (L/16) .. +15
+// (the logical chunk L/16 of the row at its swizzled place)
+__device__ __forceinline__ v4i frag(const uint8_t* p) {
+  const uint4 v = *reinterpret_cast<const uint4*>(p);
+  return v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w};
+}
+
+// the low bytes of four words, packed
+__device__ __forceinline__ uint32_t low4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  const uint32_t lo = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);
+  const uint32_t hi = __builtin_amdgcn_perm(d, c, 0x04000c0cu);
+  return lo | hi;
+}
 
 // global_load_lds_dwordx4: lane L's 16 bytes land at M0 + 16 L.  The sc1
 // cache policy (streaming operands with no reuse inside the CU's vector L1)
