@@ -53,6 +53,9 @@ def parse():
     ap.add_argument("--stage-steps", type=int, default=3,
                     help="extra steps on a stage-timed plan for the six-way split")
     ap.add_argument("--no-probes", action="store_true", help="skip the measured-peak probes")
+    ap.add_argument("--no-one-call", action="store_true",
+                    help="skip the one-call product beside the staged steps (profiles of the "
+                         "steps alone: the two routes share kernels)")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run one plain 1 GiB copy kernel (rocprofv3 counter calibration)")
     ap.add_argument("--stationary", action="store_true",
@@ -211,7 +214,7 @@ def main():
     nfb = plan.query(oz.OZ2_Q_FALLBACK_COUNT)
 
     one_call = None
-    if not fused:
+    if not (fused or args.no_one_call):
         ws1 = torch.empty(plan.ws_bytes, dtype=torch.uint8, device=dev)
         one_call = one_call_line(
             lambda C: oz.matmul(Ad, Bd, r, flags=flags, C=C, workspace=ws1), lambda: step(plan), Cd,

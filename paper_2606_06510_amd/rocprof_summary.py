@@ -218,7 +218,8 @@ def _algorithmic(m, n, k, r, pstore, acc=False):
     (and C read once more when accumulating)."""
     ea, eb = m * k, k * n
     return {
-        "k_scan_codes_rows": 9 * ea,              # A read (8 B), code byte written (1 B)
+        "k_scan_codes": 9 * (ea + eb),            # operand read (8 B), code byte written (1 B)
+        "k_scan_codes_rows": 9 * ea,              # (traces of one launch per operand)
         "k_scan_codes_cols": 9 * eb,
         "k_rebase": 2 * (ea + eb),                # code bytes read and rewritten in place
         "k_split": (8 + pstore) * (ea + eb),      # operand read, plane bytes written

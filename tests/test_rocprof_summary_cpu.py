@@ -134,6 +134,7 @@ def test_algorithmic_bytes():
     m, n, k, r, p = 300, 200, 100, 12, 30
     alg = rs._algorithmic(m, n, k, r, p)
     assert alg["k_scan_codes_rows"] == 9 * m * k and alg["k_scan_codes_cols"] == 9 * k * n
+    assert alg["k_scan_codes"] == 9 * (m * k + k * n)
     assert alg["k_rebase"] == 2 * (m * k + k * n)
     assert alg["k_split"] == (8 + p) * (m * k + k * n)
     for pair in ("false", "true"):
