@@ -11,7 +11,7 @@ namespace {
 // 64 x 32) output tiles walked by a grid-stride loop over the device-side counts (no host
 // synchronisation; every workgroup exits when the tiles are exhausted).  A
 // tile stages 64 rows x 32 k of A and 32 k x 64 columns of B through LDS (the
-// next slab's loads held in registers while the current one is multiplied);
+// next two slabs' loads held in registers while the current one is multiplied);
 // each wave owns a 32 x 32 quarter as 2 x 2 blocks of
 // v_mfma_f64_16x16x4_f64: A[i][k] from lane i + 16 k, B[k][j] from lane
 // j + 16 k, and D[i][j] in lane j + 16 (i % 4), element i / 4.  The products
